@@ -186,13 +186,13 @@ def work(c):
 
     if kind == "pcg":
         return {"bytes": c["iters"] * cg(8), "flops": c["iters"] * n * (ax + 16)}
-    if kind == "velocity":  # about 25 FP32 steps and 6 FP64 residuals
-        return {"bytes": 25 * cg(4) + 6 * n * 8 * (geo + 5 * nf), "flops": n * nf * (25 * (ax + 16) + 6 * ax)}
+    if kind == "velocity":  # about 13 FP32 steps and 6 FP64 residuals
+        return {"bytes": 13 * cg(4) + 6 * n * 8 * (geo + 5 * nf), "flops": n * nf * (13 * (ax + 16) + 6 * ax)}
     if kind == "pressure":  # per step an operator, a preconditioner (r in, z out, box factors) and the basis twice
         steps, box = 30, lx + 2 if c["precond"] == "schwarz_overlap" else lx
         words = 8 + 2 * shared + 2 + 3 * (box * box + box) / lx ** 3 + 2 * (c["restart"] / 2 + 2)
         return {"bytes": steps * n * 8 * words, "flops": steps * n * (ax + 12 * box ** 4 / lx ** 3 + 4 * c["restart"])}
-    steps = 2 * 60  # forward and adjoint solve
+    steps = 2 * 330  # forward and adjoint solve, about 330 steps each at lx = 8
     return {"bytes": steps * cg(8), "flops": steps * n * (ax + 16)}
 
 
