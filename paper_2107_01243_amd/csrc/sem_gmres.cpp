@@ -225,8 +225,8 @@ static sem_status schwarz_setup_base(sem_coef c, sem_gs g, hipStream_t st)
     SEM_TRY(dalloc(&Z.ell_ci, eci.size()));
     SEM_TRY(dalloc(&Z.ell_val, evl.size()));
     SEM_TRY(dalloc(&Z.dinv0, (size_t)nv));
-    SEM_TRY(dalloc(&Z.cv, (size_t)6 * nv));
-    SEM_TRY(dalloc(&Z.cpart, (size_t)(2 + sem_coarse_split()) * ((nv + 255) / 256)));
+    SEM_TRY(dalloc(&Z.cv, (size_t)sem_coarse_words(nv)));
+    SEM_TRY(dalloc(&Z.cpart, (size_t)sem_coarse_partials(nv)));
     HIP_TRY(hipMemcpy(Z.ell_ci, eci.data(), eci.size() * 4, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(Z.ell_val, evl.data(), evl.size() * 8, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(Z.dinv0, dg.data(), dg.size() * 8, hipMemcpyHostToDevice));
@@ -332,9 +332,9 @@ static sem_status schwarz_apply(sem_coef c, sem_gs g, double *z, const double *r
     HIP_TRY(fns(lx).fdm(&F, st));
     SEM_TRY(launch_gs<double>(z, 1, g, nullptr, nullptr, st));
     const int64_t nv = Z.nv;
-    double *x0 = Z.cv;
-    const CoarseArgs CC{Z.ell_ci, Z.ell_val, Z.width, Z.dinv0, Z.part, Z.v_ptr, Z.v_idx, Z.v_dir,
-                        x0, Z.cv + nv, Z.cv + 2 * nv, Z.cv + 3 * nv, Z.cv + 4 * nv, Z.cv + 5 * nv, Z.cpart, nv};
+    double *x0 = Z.cv + 8 * nv;
+    const CoarseArgs CC{Z.ell_ci, Z.ell_val, Z.width, Z.dinv0, Z.part, Z.v_ptr, Z.v_idx, Z.v_dir, x0, x0 + nv,
+                        (CoarseRec *)Z.cv, (CoarseRec *)Z.cv + nv, Z.cpart + 4, Z.cpart, nv};
     HIP_TRY(sem_launch_coarse_cg(&CC, coarse_iters, st));
     const ProlongArgs PA{z, Z.mult, Z.lin, x0, Z.cvert, c->nelv};
     HIP_TRY(fns(lx).prolong(&PA, st));

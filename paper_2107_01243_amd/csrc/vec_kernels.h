@@ -204,6 +204,11 @@ struct CornerArgs {
 // padding value 0 with the row's own column).  The right-hand side is gathered from
 // the per-element restriction sums: b[v] = sum over (e, c) at vertex v, ascending e
 // (0 at Dirichlet vertices).
+// Per vertex, what the neighbouring rows of a single-reduction CG step read.
+struct __attribute__((aligned(32))) CoarseRec {
+    double r, w, s, d;  // residual, A D r, A p, Jacobi inverse D
+};
+
 struct CoarseArgs {
     const int32_t *ci;
     const double *val;
@@ -213,8 +218,10 @@ struct CoarseArgs {
     const int64_t *vptr;   // [nv + 1]
     const int32_t *vidx;   // e * 8 + c
     const uint8_t *vdir;   // [nv]
-    double *x, *r, *z, *p0, *p1, *q;
-    double *partial;       // [3][grid]: (r, z) in two slots, (p, q)
+    double *x, *p;
+    CoarseRec *rec0, *rec1;
+    double *partial;       // [2 slots][2][grid]: (r, u), (u, w)
+    double *scal;          // [2 slots][2]: gamma, alpha
     int64_t nv;
 };
 

@@ -26,6 +26,12 @@ namespace sem {
 #ifndef SEM_VCH
 #define SEM_VCH 2
 #endif
+#ifndef SEM_ARN_G
+#define SEM_ARN_G 1024
+#endif
+#ifndef SEM_ARN_R
+#define SEM_ARN_R 2
+#endif
 
 constexpr int VT = 256;   // lanes per workgroup of the streaming kernels
 // Streaming kernels: workgroup b handles the contiguous chunk [b*CHUNK, (b+1)*CHUNK)
@@ -281,6 +287,61 @@ __global__ __launch_bounds__(VT) void k_comb(CombArgs A)
     }
 }
 
+__device__ __forceinline__ double wave_sum(double v)
+{
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+
+constexpr int log2up(int m) { return m <= 1 ? 0 : 1 + log2up((m + 1) / 2); }
+
+// Sums over the wave of M rows held one value per lane and row (M a power of two, at
+// most 64): on return lane l holds in v[0] the sum of row l >> (6 - log2 M).  Each stage
+// (OFF = 32, 16, ...) exchanges half of the rows still held, so M rows cost
+// M - 1 + 6 - log2 M exchanges (63 for 64 rows) instead of the 6 M of one butterfly per
+// row, and the exchanges of a stage are independent of each other.
+template <int M, int OFF = 32, int MT>
+__device__ __forceinline__ void wave_sum_rows(double (&v)[MT])
+{
+    if constexpr (OFF > 0) {
+        if constexpr (M > 1) {
+            const bool up = threadIdx.x & OFF;
+#pragma unroll
+            for (int i = 0; i < M / 2; ++i) {
+                const double give = up ? v[i] : v[i + M / 2], keep = up ? v[i + M / 2] : v[i];
+                v[i] = keep + __shfl_xor(give, OFF, 64);
+            }
+            wave_sum_rows<M / 2, OFF / 2>(v);
+        } else {
+            v[0] += __shfl_xor(v[0], OFF, 64);
+            wave_sum_rows<1, OFF / 2>(v);
+        }
+    }
+}
+
+// Sum of one row of per-workgroup partials over a wave, fixed order, four loads in
+// flight per lane.
+__device__ __forceinline__ double wave_row_sum(const double *row, int64_t nblk)
+{
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+    int64_t b = threadIdx.x & 63;
+    for (; b + 192 < nblk; b += 256) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) a[u] += row[b + 64 * u];
+    }
+    for (int u = 0; b < nblk; b += 64, ++u) a[u & 3] += row[b];
+    return wave_sum((a[0] + a[1]) + (a[2] + a[3]));
+}
+
+// Basis vector i of m at point t, streamed non-temporally; zero past the end.  The passes
+// below hold MV >= m vectors in registers (MV a few sizes up to 32), the spare ones with
+// zero coefficients or unused sums.
+__device__ __forceinline__ double basis_load(const double *V, int64_t ld, int i, int m, int64_t t)
+{
+    return i < m ? __builtin_nontemporal_load(V + i * ld + t) : 0.0;
+}
+
 // Arnoldi pass (see ArnArgs).  Each workgroup streams one contiguous chunk of
 // points; every lane keeps the m basis values of its point in registers, so the
 // combination and the dots of the combined vector need one read of each vector.
@@ -297,47 +358,42 @@ __global__ __launch_bounds__(VT) void k_arn(ArnArgs A, int64_t chunk)
         for (int i = 0; i < MV; ++i) c[i] = (i < m) ? A.coef[i] : 0.0;
         if constexpr (MODE == 2) sc = A.scale[0];
     }
-    double acc[MV + 1];
+    constexpr int LG = log2up(MV), M2 = 1 << LG;
+    double acc[M2], nn = 0.0;
 #pragma unroll
-    for (int i = 0; i <= MV; ++i) acc[i] = 0.0;
+    for (int i = 0; i < M2; ++i) acc[i] = 0.0;
     const int64_t t0 = (int64_t)blockIdx.x * chunk;
     const int64_t t1 = min(A.n, t0 + chunk);
     for (int64_t t = t0 + threadIdx.x; t < t1; t += VT) {
         double v[MV];
 #pragma unroll
-        for (int i = 0; i < MV; ++i) v[i] = (i < m) ? __builtin_nontemporal_load(A.V + i * A.ld + t) : 0.0;
+        for (int i = 0; i < MV; ++i) v[i] = basis_load(A.V, A.ld, i, m, t);
         double y = A.w[t];
         if constexpr (MODE != 0) {
 #pragma unroll
-            for (int i = 0; i < MV; ++i)
-                if (i < m) y = fma(-c[i], v[i], y);
+            for (int i = 0; i < MV; ++i) y = fma(-c[i], v[i], y);
             if constexpr (MODE == 2) y *= sc;
             A.y[t] = y;
         }
         if constexpr (MODE != 2) {
             const double yo = A.owner[t] ? y : 0.0;
 #pragma unroll
-            for (int i = 0; i < MV; ++i)
-                if (i < m) acc[i] = fma(v[i], yo, acc[i]);
-            acc[MV] = fma(y, yo, acc[MV]);
+            for (int i = 0; i < MV; ++i) acc[i] = fma(v[i], yo, acc[i]);
+            nn = fma(y, yo, nn);
         }
     }
     if constexpr (MODE != 2) {
-        __shared__ double sh[VT / 64][MV + 1];
+        // rows: the m dots (transposed wave sums), then the squared norm
+        __shared__ double sh[VT / 64][M2 + 1];
         const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-        for (int i = 0; i <= MV; ++i) {
-            if (i < m || i == MV) {
-                double x = acc[i];
-#pragma unroll
-                for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-                if (lane == 0) sh[wave][i] = x;
-            }
-        }
+        wave_sum_rows<M2>(acc);
+        const double yy = wave_sum(nn);
+        if ((lane & ((1 << (6 - LG)) - 1)) == 0) sh[wave][lane >> (6 - LG)] = acc[0];
+        if (lane == 0) sh[wave][M2] = yy;
         __syncthreads();
         const int q = threadIdx.x;
         if (q <= m) {
-            const int src = (q < m) ? q : MV;
+            const int src = (q < m) ? q : M2;
             double x = 0.0;
 #pragma unroll
             for (int w4 = 0; w4 < VT / 64; ++w4) x += sh[w4][src];
@@ -356,10 +412,7 @@ __global__ __launch_bounds__(RT) void k_arn_finish(const double *partial, int64_
     __shared__ double sh[ARN_MAXV + 1];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (int q = wave; q < nq; q += RT / 64) {
-        double s = 0.0;
-        for (int64_t b = lane; b < nblk; b += 64) s += partial[(int64_t)q * nblk + b];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+        const double s = wave_row_sum(partial + (int64_t)q * nblk, nblk);
         if (lane == 0) {
             out[q] = s;
             sh[q] = s;
@@ -382,47 +435,48 @@ __global__ __launch_bounds__(RT) void k_arn_finish(const double *partial, int64_
 template <int MV>
 __global__ __launch_bounds__(VT) void k_dcgs_dots(DcgsArgs A, int64_t chunk)
 {
-    constexpr int NR = 2 * MV + 3;
     const int j = A.j;
-    double ua[MV], wb[MV], uu = 0.0, uw = 0.0, ww = 0.0;
+    constexpr int LG = log2up(2 * MV), M2 = 1 << LG;
+    double ab[M2], uu = 0.0, uw = 0.0, ww = 0.0;  // V^T u (from 0), V^T w (from MV)
 #pragma unroll
-    for (int i = 0; i < MV; ++i) ua[i] = wb[i] = 0.0;
+    for (int i = 0; i < M2; ++i) ab[i] = 0.0;
     const int64_t t0 = (int64_t)blockIdx.x * chunk;
     const int64_t t1 = min(A.n, t0 + chunk);
     for (int64_t t = t0 + threadIdx.x; t < t1; t += VT) {
         double v[MV];
 #pragma unroll
-        for (int i = 0; i < MV; ++i) v[i] = (i < j) ? __builtin_nontemporal_load(A.V + i * A.ld + t) : 0.0;
+        for (int i = 0; i < MV; ++i) v[i] = basis_load(A.V, A.ld, i, j, t);
         const double u = A.u[t], w = A.w[t];
         const bool own = A.owner[t] != 0;
         const double uo = own ? u : 0.0, wo = own ? w : 0.0;
 #pragma unroll
-        for (int i = 0; i < MV; ++i)
-            if (i < j) {
-                ua[i] = fma(v[i], uo, ua[i]);
-                wb[i] = fma(v[i], wo, wb[i]);
-            }
+        for (int i = 0; i < MV; ++i) {
+            ab[i] = fma(v[i], uo, ab[i]);
+            ab[MV + i] = fma(v[i], wo, ab[MV + i]);
+        }
         uu = fma(u, uo, uu);
         uw = fma(u, wo, uw);
         ww = fma(w, wo, ww);
     }
-    // rows: a_0..a_{j-1}, (u,u), b_0..b_{j-1}, (u,w), (w,w)
-    __shared__ double sh[VT / 64][NR];
+    // rows: a_0..a_{j-1}, (u,u), b_0..b_{j-1}, (u,w), (w,w).  The sums are formed
+    // transposed (wave_sum_rows): with one butterfly per row this reduction took most of
+    // the 41 us of a 30-vector pass over 2e5 points.
+    __shared__ double sh[VT / 64][2 * MV + 3];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    auto put = [&](int q, double x) {
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-        if (lane == 0) sh[wave][q] = x;
-    };
-#pragma unroll
-    for (int i = 0; i < MV; ++i)
-        if (i < j) {
-            put(i, ua[i]);
-            put(j + 1 + i, wb[i]);
-        }
-    put(j, uu);
-    put(2 * j + 1, uw);
-    put(2 * j + 2, ww);
+    wave_sum_rows<M2>(ab);
+    uu = wave_sum(uu);
+    uw = wave_sum(uw);
+    ww = wave_sum(ww);
+    if ((lane & ((1 << (6 - LG)) - 1)) == 0) {
+        const int q = lane >> (6 - LG);
+        if (q < j) sh[wave][q] = ab[0];
+        else if (q >= MV && q - MV < j) sh[wave][j + 1 + q - MV] = ab[0];
+    }
+    if (lane == 0) {
+        sh[wave][j] = uu;
+        sh[wave][2 * j + 1] = uw;
+        sh[wave][2 * j + 2] = ww;
+    }
     __syncthreads();
     const int q = threadIdx.x;
     if (q < 2 * j + 3) {
@@ -451,15 +505,14 @@ __global__ __launch_bounds__(VT) void k_dcgs_update(DcgsArgs A, int64_t chunk)
     for (int64_t t = t0 + threadIdx.x; t < t1; t += VT) {
         double v[MV];
 #pragma unroll
-        for (int i = 0; i < MV; ++i) v[i] = (i < j) ? __builtin_nontemporal_load(A.V + i * A.ld + t) : 0.0;
+        for (int i = 0; i < MV; ++i) v[i] = basis_load(A.V, A.ld, i, j, t);
         const double u = A.u[t];
         double q = u, y = A.w[t];
 #pragma unroll
-        for (int i = 0; i < MV; ++i)
-            if (i < j) {
-                q = fma(-ca[i], v[i], q);
-                y = fma(-cc[i], v[i], y);
-            }
+        for (int i = 0; i < MV; ++i) {
+            q = fma(-ca[i], v[i], q);
+            y = fma(-cc[i], v[i], y);
+        }
         y = fma(-del, u, y);
         A.u[t] = q * irho;
         A.w[t] = y * inu;
@@ -477,24 +530,17 @@ __global__ __launch_bounds__(RT) void k_dcgs_finish(const double *partial, int64
     const int nq = 2 * j + 3;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (int q = wave; q < nq; q += RT / 64) {
-        double s = 0.0;
-        for (int64_t b = lane; b < nblk; b += 64) s += partial[(int64_t)q * nblk + b];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+        const double s = wave_row_sum(partial + (int64_t)q * nblk, nblk);
         if (lane == 0) {
             out[q] = s;
             sh[q] = s;
         }
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const double *a = sh, *b = sh + j + 1;
-        double aa = sh[j], ab = sh[2 * j + 1], bb = sh[2 * j + 2];
-        for (int i = 0; i < j; ++i) {
-            aa = fma(-a[i], a[i], aa);
-            ab = fma(-a[i], b[i], ab);
-            bb = fma(-b[i], b[i], bb);
-        }
+    if (threadIdx.x < 64) {  // lane i holds a_i and b_i (j < 32)
+        const double a = lane < j ? sh[lane] : 0.0, b = lane < j ? sh[j + 1 + lane] : 0.0;
+        const double aa = sh[j] - wave_sum(a * a), ab = sh[2 * j + 1] - wave_sum(a * b);
+        const double bb = sh[2 * j + 2] - wave_sum(b * b);
         const double rho = aa > 0.0 ? sqrt(aa) : 0.0;
         const double gam = rho > 0.0 ? ab / rho : 0.0;
         const double del = rho > 0.0 ? gam / rho : 0.0;
@@ -502,16 +548,18 @@ __global__ __launch_bounds__(RT) void k_dcgs_finish(const double *partial, int64
         nn = nn > 0.0 ? nn : 0.0;
         const double nu = sqrt(nn);
         double *cf = out + nq;
-        for (int i = 0; i < j; ++i) {
-            cf[i] = a[i];
-            cf[j + i] = fma(-del, a[i], b[i]);
+        if (lane < j) {
+            cf[lane] = a;
+            cf[j + lane] = fma(-del, a, b);
         }
-        cf[2 * j] = rho > 0.0 ? 1.0 / rho : 0.0;
-        cf[2 * j + 1] = del;
-        cf[2 * j + 2] = nu > 0.0 ? 1.0 / nu : 0.0;
-        cf[2 * j + 3] = rho;
-        cf[2 * j + 4] = gam;
-        cf[2 * j + 5] = nu;
+        if (lane == 0) {
+            cf[2 * j] = rho > 0.0 ? 1.0 / rho : 0.0;
+            cf[2 * j + 1] = del;
+            cf[2 * j + 2] = nu > 0.0 ? 1.0 / nu : 0.0;
+            cf[2 * j + 3] = rho;
+            cf[2 * j + 4] = gam;
+            cf[2 * j + 5] = nu;
+        }
     }
 }
 
@@ -556,125 +604,246 @@ __global__ __launch_bounds__(VT) void k_corner(CornerArgs A)
     }
 }
 
-// Sum of the nblk per-workgroup partials in one fixed order, returned to every lane
-// of the workgroup.  Each workgroup of a launch computes the same value, so a
-// kernel can use a grid-wide reduction of the previous launch without a separate
-// scalar kernel (the coarse system has only a few hundred partials).
-__device__ __forceinline__ double all_sum(const double *part, int64_t nblk, double *sh)
+// ---- coarse solve: a fixed number of Jacobi-CG steps on A0 x = b from x = 0.
+//
+// The system is small (one unknown per element vertex) and its time is launches and
+// dependent memory round trips, not bytes.  Two forms, chosen by nv in
+// sem_launch_coarse_cg:
+//  * k_ccg_small: the whole solve in one workgroup, for systems that its registers and
+//    LDS hold (nv <= 1536, rows of at most 28 entries).  Per step 1.2 us at nv <= 512,
+//    1.6 us at 1000, 3.4 us at 1331, against 5.0-5.8 us of a launch per step.
+//  * k_ccg_start + k_ccg_step: one launch per step in the single-reduction form; 5.9 us
+//    per step at 2197 vertices, 6.4 us at 15,625 (10.6 and 11.1 us with the two
+//    launches per step of the textbook form; the one-workgroup form needs the matrix
+//    read again every step there, 27 x 12 bytes per row through one compute unit).
+
+// Right-hand side of vertex v, gathered from the per-element restriction sums.
+__device__ __forceinline__ double coarse_rhs(const CoarseArgs &A, int64_t v)
 {
-    double s = 0.0;
-    for (int64_t q = threadIdx.x; q < nblk; q += VT) s += part[q];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
-    __syncthreads();
-    double v = sh[0];
-#pragma unroll
-    for (int q = 1; q < VT / 64; ++q) v += sh[q];
-    __syncthreads();
-    return v;
+    double b = 0.0;
+    if (!A.vdir[v])
+        for (int64_t q = A.vptr[v]; q < A.vptr[v + 1]; ++q) b += A.part[A.vidx[q]];
+    return b;
 }
 
-__device__ __forceinline__ void block_partial(double v, double *out, double *sh)
+constexpr int CST = 512;              // lanes of k_ccg_small
+constexpr int CCG_SMALL = 3 * CST;    // largest system it takes
+
+constexpr int RESW = 28;    // most entries per row (a hexahedral box has 27)
+
+// Sum over the workgroup in one fixed order, returned to every lane; one barrier.  Two
+// consecutive calls use different buffers, so a lane still reading one call's sums
+// cannot meet the next call's writes.
+__device__ __forceinline__ double small_sum(double v, double *sh)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    v = wave_sum(v);
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        double s = 0.0;
+    double s = sh[0];
 #pragma unroll
-        for (int q = 0; q < VT / 64; ++q) s += sh[q];
-        *out = s;
+    for (int q = 1; q < CST / 64; ++q) s += sh[q];
+    return s;
+}
+
+// Whole coarse solve in one workgroup: lane t owns rows t, t + 512, ... (RPT of them)
+// with x, r and p in registers and p shared through LDS for the matrix product.  The
+// matrix stays on the compute unit for all steps: columns packed two to a register,
+// values in registers, and with three rows per lane the last LW entries of each row in
+// LDS (the 256 registers a lane has with two waves per SIMD do not hold them; spilled to
+// memory, a step took 7 us).
+template <int RPT>
+__global__ __launch_bounds__(CST) void k_ccg_small(CoarseArgs A, int iters)
+{
+    constexpr int LW = RPT > 2 ? 10 : 0, RW = RESW - LW;
+    __shared__ double ps[CST * RPT];
+    __shared__ double sh[2][CST / 64];
+    __shared__ double al[LW > 0 ? LW * RPT * CST : 1];
+    double x[RPT], r[RPT], p[RPT], d[RPT], q[RPT], a[RPT][RW];
+    unsigned c2[RPT][RESW / 2];
+    double acc = 0.0;
+#pragma unroll
+    for (int h = 0; h < RPT; ++h) {
+        const int64_t v = threadIdx.x + h * CST;
+        const bool in = v < A.nv;
+#pragma unroll
+        for (int w = 0; w < RESW; ++w) {
+            const int64_t k = (w < A.width ? w : 0) * A.nv + (in ? v : 0);
+            const double av = in && w < A.width ? A.val[k] : 0.0;
+            if (w < RW) a[h][w] = av;
+            else al[((w - RW) * RPT + h) * CST + threadIdx.x] = av;  // read back by this lane only
+            const unsigned c = (unsigned)A.ci[k];
+            c2[h][w / 2] = (w & 1) ? (c2[h][w / 2] | c << 16) : c;
+        }
+        r[h] = in ? coarse_rhs(A, v) : 0.0;
+        d[h] = in ? A.dinv[v] : 0.0;
+        x[h] = 0.0;
+        p[h] = d[h] * r[h];
+        acc = fma(r[h], p[h], acc);
+    }
+    double rz = small_sum(acc, sh[0]);
+    for (int it = 0; it < iters; ++it) {
+#pragma unroll
+        for (int h = 0; h < RPT; ++h) ps[threadIdx.x + h * CST] = p[h];
+        __syncthreads();
+        acc = 0.0;
+#pragma unroll
+        for (int h = 0; h < RPT; ++h) {
+            double s = 0.0;
+#pragma unroll
+            for (int w = 0; w < RESW; ++w) {
+                const double av = w < RW ? a[h][w] : al[((w - RW) * RPT + h) * CST + threadIdx.x];
+                s = fma(av, ps[(w & 1) ? c2[h][w / 2] >> 16 : c2[h][w / 2] & 0xffffu], s);
+                // bound the LDS reads in flight (their results would spill)
+                if constexpr (RPT > 2) {
+                    if (w % 7 == 6) __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            q[h] = s;
+            acc = fma(p[h], s, acc);
+        }
+        const double pq = small_sum(acc, sh[1]);
+        const double alpha = (pq > 0.0 && isfinite(pq)) ? rz / pq : 0.0;
+        acc = 0.0;
+#pragma unroll
+        for (int h = 0; h < RPT; ++h) {
+            x[h] = fma(alpha, p[h], x[h]);
+            r[h] = fma(-alpha, q[h], r[h]);
+            acc = fma(r[h], d[h] * r[h], acc);
+        }
+        const double rzn = small_sum(acc, sh[0]);
+        const double beta = (rz != 0.0) ? rzn / rz : 0.0;
+        rz = rzn;
+#pragma unroll
+        for (int h = 0; h < RPT; ++h) p[h] = fma(beta, p[h], d[h] * r[h]);
+    }
+#pragma unroll
+    for (int h = 0; h < RPT; ++h) {
+        const int64_t v = threadIdx.x + h * CST;
+        if (v < A.nv) A.x[v] = x[h];
     }
 }
 
-// Coarse Jacobi-CG, start: b gathered from the restriction sums; x = 0, r = b,
-// z = D r; partial of (r, z) into slot 0.
+// Start of the launch-per-step form: r = b, w = s = 0, p = x = 0.
 __global__ __launch_bounds__(VT) void k_ccg_start(CoarseArgs A)
 {
-    __shared__ double sh[VT / 64];
     const int64_t v = (int64_t)blockIdx.x * VT + threadIdx.x;
-    double rz = 0.0;
-    if (v < A.nv) {
-        double b = 0.0;
-        if (!A.vdir[v])
-            for (int64_t q = A.vptr[v]; q < A.vptr[v + 1]; ++q) b += A.part[A.vidx[q]];
-        const double zv = A.dinv[v] * b;
-        A.x[v] = 0.0;
-        A.r[v] = b;
-        A.z[v] = zv;
-        rz = b * zv;
-    }
-    block_partial(rz, A.partial + blockIdx.x, sh);
+    if (v >= A.nv) return;
+    A.rec0[v] = CoarseRec{coarse_rhs(A, v), 0.0, 0.0, A.dinv[v]};
+    A.x[v] = 0.0;
+    A.p[v] = 0.0;
 }
 
-// Step it, first half: beta from the two latest (r, z) sums (it > 0), the new
-// direction p = z + beta p_old formed for the own row and, on the fly, for every
-// column the row touches; q = A p; partial of (p, q) into slot 2.  p alternates
-// between p0 (even steps) and p1 (odd steps).  SPL lanes share a row (entries
-// w = part, part + SPL, ...; summed across the lanes in a fixed order), so a row's
-// gathers are split over SPL lanes; the grid is SPL times that of the other kernels
-// (g, the row-per-lane grid, passed in).
+// One step of single-reduction Jacobi-CG (Chronopoulos-Gear) per launch.  With u = D r
+// (D the Jacobi inverse), w = A u, gamma = (r, u), delta = (u, w) of the current iterate
+// (reduced here from the previous launch's partials, by every workgroup in the same
+// fixed order):
+//   beta = gamma / gamma_old, alpha = gamma / (delta - beta gamma / alpha_old),
+//   p = u + beta p, s = w + beta s, x += alpha p, r -= alpha s,
+// then the new u, w, gamma, delta, with the new r of every column a row touches formed
+// on the fly from that column's record (r, w, s, D: one 32-byte gather).  Launch 0 has
+// alpha = beta = 0 and only forms w, gamma, delta; the last launch only updates x.
+// Records alternate between rec0 (read by even launches) and rec1.  SPL lanes share a
+// row (entries w = part, part + SPL, ...; summed across the lanes in a fixed order).
+// The records are requested before the partial sums are reduced, so the two round trips
+// overlap.
 #ifndef SEM_CCG_SPL
 #define SEM_CCG_SPL 4
 #endif
 constexpr int SPL = SEM_CCG_SPL;
-__global__ __launch_bounds__(VT) void k_ccg_spmv(CoarseArgs A, int it, int64_t g)
+constexpr int CCG_PRE = 28 / SPL;  // entries per lane requested ahead (27-point rows)
+__global__ __launch_bounds__(VT) void k_ccg_step(CoarseArgs A, int it, int last)
 {
-    __shared__ double sh[VT / 64];
-    double beta = 0.0;
-    if (it > 0) {
-        const double rz = all_sum(A.partial + (it & 1) * g, g, sh);
-        const double rz_old = all_sum(A.partial + ((it + 1) & 1) * g, g, sh);
-        beta = (rz_old != 0.0) ? rz / rz_old : 0.0;
-    }
-    double *pn = (it & 1) ? A.p1 : A.p0;
-    const double *po = (it & 1) ? A.p0 : A.p1;
-    const int part = threadIdx.x % SPL;
-    const int64_t v = ((int64_t)blockIdx.x * VT + threadIdx.x) / SPL;
-    double pq = 0.0;
-    if (v < A.nv) {
-        double s = 0.0;
-        for (int w = part; w < A.width; w += SPL) {
-            const int64_t k = (int64_t)w * A.nv + v;
-            const int32_t c = A.ci[k];
-            const double pc = (it > 0) ? fma(beta, po[c], A.z[c]) : A.z[c];
-            s = fma(A.val[k], pc, s);
-        }
-#pragma unroll
-        for (int off = 1; off < SPL; off <<= 1) s += __shfl_xor(s, off, 64);
-        if (part == 0) {
-            const double pv = (it > 0) ? fma(beta, po[v], A.z[v]) : A.z[v];
-            pn[v] = pv;
-            A.q[v] = s;
-            pq = pv * s;
-        }
-    }
-    block_partial(pq, A.partial + 2 * g + blockIdx.x, sh);
-}
-
-// Step it, second half: alpha = (r, z) / (p, q); x += alpha p, r -= alpha q,
-// z = D r; partial of the new (r, z) into the other slot.
-__global__ __launch_bounds__(VT) void k_ccg_update(CoarseArgs A, int it)
-{
-    __shared__ double sh[VT / 64];
+    __shared__ double sh[4][VT / 64];
+    const CoarseRec *ro = (it & 1) ? A.rec1 : A.rec0;
+    CoarseRec *rn = (it & 1) ? A.rec0 : A.rec1;
     const int64_t g = gridDim.x;
-    const double rz = all_sum(A.partial + (it & 1) * g, g, sh);
-    const double pq = all_sum(A.partial + 2 * g, SPL * g, sh);
-    const double alpha = (pq > 0.0 && isfinite(pq)) ? rz / pq : 0.0;
-    const double *pn = (it & 1) ? A.p1 : A.p0;
-    const int64_t v = (int64_t)blockIdx.x * VT + threadIdx.x;
-    double rzn = 0.0;
-    if (v < A.nv) {
-        A.x[v] = fma(alpha, pn[v], A.x[v]);
-        const double rv = fma(-alpha, A.q[v], A.r[v]);
-        A.r[v] = rv;
-        const double zv = A.dinv[v] * rv;
-        A.z[v] = zv;
-        rzn = rv * zv;
+    const int part = threadIdx.x % SPL, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t v = ((int64_t)blockIdx.x * VT + threadIdx.x) / SPL;
+    const bool in = v < A.nv;
+    const int64_t vc = in ? v : 0;
+    const CoarseRec own = ro[vc];
+    const double pv = A.p[vc], xv = A.x[vc];
+    CoarseRec c[CCG_PRE];
+    double a[CCG_PRE];
+    if (!last) {
+#pragma unroll
+        for (int q = 0; q < CCG_PRE; ++q) {
+            const int w = part + q * SPL;
+            const int64_t k = (int64_t)(w < A.width ? w : 0) * A.nv + vc;
+            a[q] = w < A.width ? A.val[k] : 0.0;
+            c[q] = ro[A.ci[k]];
+        }
     }
-    block_partial(rzn, A.partial + ((it + 1) & 1) * g + blockIdx.x, sh);
+    double alpha = 0.0, beta = 0.0;
+    if (it > 0) {
+        const double *pg = A.partial + (it & 1) * 2 * g;
+        double s0 = 0.0, s1 = 0.0;
+        for (int64_t q = threadIdx.x; q < g; q += VT) {
+            s0 += pg[q];
+            s1 += pg[g + q];
+        }
+        s0 = wave_sum(s0);
+        s1 = wave_sum(s1);
+        if (lane == 0) {
+            sh[0][wave] = s0;
+            sh[1][wave] = s1;
+        }
+        __syncthreads();
+        double gam = sh[0][0], del = sh[1][0];
+#pragma unroll
+        for (int q = 1; q < VT / 64; ++q) {
+            gam += sh[0][q];
+            del += sh[1][q];
+        }
+        // scal: (gamma, alpha) of the previous step, two slots in turn
+        const double *so = A.scal + 2 * ((it + 1) & 1);
+        if (it > 1) beta = (so[0] != 0.0) ? gam / so[0] : 0.0;
+        const double den = it > 1 ? del - beta * gam / so[1] : del;
+        alpha = (den > 0.0 && isfinite(den)) ? gam / den : 0.0;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            A.scal[2 * (it & 1)] = gam;
+            A.scal[2 * (it & 1) + 1] = alpha;
+        }
+    }
+    if (part == 0 && in && it > 0) {
+        const double pn = fma(beta, pv, own.d * own.r);
+        A.p[v] = pn;
+        A.x[v] = fma(alpha, pn, xv);
+    }
+    if (last) return;
+    const double so = fma(beta, own.s, own.w), rv = fma(-alpha, so, own.r), uv = own.d * rv;
+    double s = 0.0;
+#pragma unroll
+    for (int q = 0; q < CCG_PRE; ++q) {
+        const double rc = fma(-alpha, fma(beta, c[q].s, c[q].w), c[q].r);
+        s = fma(a[q], c[q].d * rc, s);
+    }
+    for (int w = part + CCG_PRE * SPL; w < A.width; w += SPL) {  // wider rows than a hexahedral box has
+        const int64_t k = (int64_t)w * A.nv + vc;
+        const CoarseRec e = ro[A.ci[k]];
+        s = fma(A.val[k], e.d * fma(-alpha, fma(beta, e.s, e.w), e.r), s);
+    }
+#pragma unroll
+    for (int off = 1; off < SPL; off <<= 1) s += __shfl_xor(s, off, 64);
+    double gn = 0.0, dn = 0.0;
+    if (part == 0 && in) {
+        rn[v] = CoarseRec{rv, s, so, own.d};
+        gn = rv * uv;
+        dn = uv * s;
+    }
+    gn = wave_sum(gn);
+    dn = wave_sum(dn);
+    if (lane == 0) {
+        sh[2][wave] = gn;
+        sh[3][wave] = dn;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        double t = 0.0;
+#pragma unroll
+        for (int q = 0; q < VT / 64; ++q) t += sh[2 + threadIdx.x][q];
+        A.partial[(((it + 1) & 1) * 2 + threadIdx.x) * g + blockIdx.x] = t;
+    }
 }
 
 // Per element, the sums over its points of G_dd / B for d = r, s, t (the local
@@ -1387,8 +1556,9 @@ static hipError_t launch_gs_t(const GsArgs<T> *A, hipStream_t st)
 static int64_t arn_chunk(int64_t n)
 {
     const int64_t rows = (n + VT - 1) / VT;
-    const int64_t per = (rows + 1023) / 1024;
-    return (per < 1 ? 1 : per) * VT;
+    const int64_t per = (rows + SEM_ARN_G - 1) / SEM_ARN_G;
+    const int64_t least = rows >= 256 * SEM_ARN_R ? SEM_ARN_R : 1;
+    return (per < least ? least : per) * VT;
 }
 static unsigned arn_grid(int64_t n)
 {
@@ -1536,8 +1706,11 @@ hipError_t sem_launch_dcgs(const DcgsArgs *A, int pass, hipStream_t st)
 {
     if (A->j < 0 || A->j >= ARN_MAXV || pass < 0 || pass > 1 || A->n < 1) return hipErrorInvalidValue;
     if (pass == 1 && !A->coef) return hipErrorInvalidValue;
-    if (A->j <= 8) launch_dcgs<8>(*A, pass, st);
+    if (A->j <= 4) launch_dcgs<4>(*A, pass, st);
+    else if (A->j <= 8) launch_dcgs<8>(*A, pass, st);
+    else if (A->j <= 12) launch_dcgs<12>(*A, pass, st);
     else if (A->j <= 16) launch_dcgs<16>(*A, pass, st);
+    else if (A->j <= 24) launch_dcgs<24>(*A, pass, st);
     else launch_dcgs<32>(*A, pass, st);
     return hipGetLastError();
 }
@@ -1552,8 +1725,11 @@ hipError_t sem_launch_arn(const ArnArgs *A, int mode, hipStream_t st)
     if (A->m < 1 || A->m > ARN_MAXV || mode < 0 || mode > 2 || A->n < 1) return hipErrorInvalidValue;
     if (mode != 0 && !A->coef) return hipErrorInvalidValue;
     if (mode == 2 && !A->scale) return hipErrorInvalidValue;
-    if (A->m <= 8) launch_arn<8>(*A, mode, st);
+    if (A->m <= 4) launch_arn<4>(*A, mode, st);
+    else if (A->m <= 8) launch_arn<8>(*A, mode, st);
+    else if (A->m <= 12) launch_arn<12>(*A, mode, st);
     else if (A->m <= 16) launch_arn<16>(*A, mode, st);
+    else if (A->m <= 24) launch_arn<24>(*A, mode, st);
     else launch_arn<32>(*A, mode, st);
     return hipGetLastError();
 }
@@ -1576,21 +1752,27 @@ hipError_t sem_launch_corner(const CornerArgs *A, hipStream_t st)
     hipLaunchKernelGGL(k_corner, dim3((unsigned)A->nelv), dim3(VT), 0, st, *A);
     return hipGetLastError();
 }
-// iters fixed-count Jacobi-CG steps on the coarse system from x = 0, two launches per
-// step and no host sync; partial must hold (2 + SPL) * ceil(nv / VT) values.
-// lanes per row of the coarse SpMV (the coarse partial buffer is sized by it)
-int sem_coarse_split() { return SPL; }
+// workgroups of k_ccg_step
+static int64_t ccg_grid(int64_t nv) { return (nv * SPL + VT - 1) / VT; }
+// doubles of the coarse solve's vectors (x, p, two record arrays) and of its partial
+// sums and scalars
+int64_t sem_coarse_words(int64_t nv) { return 10 * nv; }
+int64_t sem_coarse_partials(int64_t nv) { return 4 * ccg_grid(nv) + 4; }
 
+// iters fixed-count Jacobi-CG steps on the coarse system from x = 0, no host sync.
 hipError_t sem_launch_coarse_cg(const CoarseArgs *A, int iters, hipStream_t st)
 {
     if (A->nv == 0) return hipSuccess;
-    if (A->width < 1 || A->nv > 0x7fffffffLL * VT) return hipErrorInvalidValue;
-    const unsigned g = (unsigned)((A->nv + VT - 1) / VT);
-    hipLaunchKernelGGL(k_ccg_start, dim3(g), dim3(VT), 0, st, *A);
-    for (int it = 0; it < iters; ++it) {
-        hipLaunchKernelGGL(k_ccg_spmv, dim3(g * SPL), dim3(VT), 0, st, *A, it, (int64_t)g);
-        hipLaunchKernelGGL(k_ccg_update, dim3(g), dim3(VT), 0, st, *A, it);
+    if (A->width < 1 || A->nv > 0x7fffffffLL) return hipErrorInvalidValue;
+    if (A->nv <= CCG_SMALL && A->width <= RESW) {
+        if (A->nv <= CST) hipLaunchKernelGGL(k_ccg_small<1>, dim3(1), dim3(CST), 0, st, *A, iters);
+        else if (A->nv <= 2 * CST) hipLaunchKernelGGL(k_ccg_small<2>, dim3(1), dim3(CST), 0, st, *A, iters);
+        else hipLaunchKernelGGL(k_ccg_small<3>, dim3(1), dim3(CST), 0, st, *A, iters);
+        return hipGetLastError();
     }
+    hipLaunchKernelGGL(k_ccg_start, dim3((unsigned)((A->nv + VT - 1) / VT)), dim3(VT), 0, st, *A);
+    for (int it = 0; it <= iters && iters > 0; ++it)
+        hipLaunchKernelGGL(k_ccg_step, dim3((unsigned)ccg_grid(A->nv)), dim3(VT), 0, st, *A, it, it == iters ? 1 : 0);
     return hipGetLastError();
 }
 hipError_t sem_launch_elem_gb(const double *G, const double *B, double *out, int64_t nelv, int lx3,

@@ -590,6 +590,26 @@ def test_schwarz_overlap_apply_vs_oracle(shape, lx):
     O.set_coef(1.0, 0.0)
 
 
+@pytest.mark.parametrize("shape", [(7, 7, 7), (2, 8, 18), (7, 7, 15), (4, 4, 40), (7, 11, 15), (9, 10, 13)])
+def test_coarse_solve_sizes_vs_oracle(shape):
+    """The coarse solve at the edges of its forms: 512, 513, 1024, 1025, 1536 and 1540
+    vertices (one, two and three rows per lane of one workgroup, then a launch per
+    step), after an odd, an even and no number of steps.  FP64 sums of at most a few
+    thousand terms in another order, ten steps of a well-conditioned system: 1e-10."""
+    nx, ny, nz = shape
+    say(f"[coarse sizes] {nx}x{ny}x{nz}")
+    P, O = pair3(nx, ny, nz, 2)
+    O.schwarz_setup()
+    rl = workloads.uniform(P.n, 7)
+    ro = O.assemble_rhs(rl)
+    r = P.assemble(to_dev(rl))
+    for it in (0, 1, 7, 10):
+        z = sem.schwarz_apply(torch.empty_like(r), r, P.coef, P.msh, P.Xh, P.gs, coarse_iters=it)
+        d = rel_inf(host(z), O.schwarz_apply(ro, coarse_iters=it))
+        say(f"   coarse_iters={it}: rel diff {d:.2e}")
+        assert d <= 1e-10
+
+
 def _reorient(a, lx, perm, flip):
     """Per element, the local layout re-indexed so that new coordinate m is old
     coordinate perm[e][m], reversed where flip[e][m] (a: [..., nelv * lx^3])."""
