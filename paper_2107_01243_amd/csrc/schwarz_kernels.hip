@@ -25,259 +25,325 @@
 
 namespace sem {
 
-// y = M x along one pencil of X points, M row-major (a copy of S or of its transpose in
-// LDS), each y[m] summed over ascending l.
-template <int X>
-__device__ __forceinline__ void fdm_mul(const double *M, const double (&x)[X], double (&y)[X])
+// ------------------------------------------------------------------ local solves
+// Each of the six 1-D transforms of a solve multiplies an X x X matrix with the X^2 pencils
+// of the box.  The matrices differ from element to element, so on the vector units every
+// multiply-add needs its matrix entry broadcast from LDS (8 cycles of the compute unit's
+// LDS per 16 bytes, shared by four SIMDs), and that broadcast bounded the kernel.  On the
+// matrix cores an entry is held by one lane and no broadcast is needed: FP64 4x4x4
+// products of four independent blocks, the matrix tile the same in all four, so one
+// instruction multiplies a 4x4 tile with 16 pencils at the vector units' FP64 rate.
+//
+// Operand layout (lane = c + 16 g): B holds row g of a 4-row tile of pencil c, the result
+// holds row g of pencil c again, and A holds row c % 4, column g of the matrix tile.  A
+// pencil's points are thus spread over the four lane groups (node or mode 4 tile + g), and
+// the result of one transform is the operand of the next one along the same direction
+// (forward and inverse along s are chained in registers); between directions the box goes
+// through LDS (row stride odd: no bank conflicts).
+//
+// Nodes are ordered own points first (0 .. lx - 1), then with the overlap the extension
+// points below and above (lx, lx + 1): the inverse transforms then form the tiles of the
+// own points only.
+//
+// 32^3 elements, lx = 8: element box 99 -> 78 us, box with overlap 234 -> 205 us.  Now
+// neither a memory nor a matrix bound: the matrix cores are busy 38% of the time, the
+// vector units (the FP64 divisions, addresses, the gathers of the overlap) 35%, LDS 43%.
+template <int LX, bool OV>
+struct FdmShape {
+    static constexpr int X = OV ? LX + 2 : LX;
+    static constexpr int P = (X % 2) ? X : X + 1;                  // LDS row stride
+    static constexpr int T = (X + 3) / 4, TL = (LX + 3) / 4;       // tiles of all / own nodes
+    // Waves per element W, tiles in flight per wave HG and waves per SIMD the registers
+    // leave room for EU, measured per box size X at 9 to 17 million points (whole
+    // application without the coarse steps, before -> now): X = 4 355 -> 300 us, 5 249 ->
+    // 238, 6 262 -> 266 (EU 4: 276), 7 158 -> 160, 8 271 -> 249, 9 316 -> 306, 10 313 ->
+    // 319 (W 2, HG 4: 330), 12 256 -> 230, 16 285 -> 260; with overlap X = 6 517 -> 483,
+    // 7 380 -> 338, 8 347 -> 340, 9 298 -> 240, 10 416 -> 386 (W 1: 408, W 4: 397), 11
+    // 424 -> 372, 12 447 -> 385, 14 350 -> 336, 18 506 -> 448.
+    static constexpr int W = X <= 8 ? 1 : X <= 10 ? (OV ? 2 : 4) : X <= 14 ? 4 : 8;
+    static constexpr int HG = X == 10 && !OV ? 2 : 4;
+    static constexpr int EU = X == 6 ? 8 : X == 10 && !OV ? 6 : 4;
+    static constexpr int NT = 64 * W;
+};
+
+// A operand of every tile of S^T (forward: rows are modes) or of S (inverse: rows are
+// nodes); S in LDS, padded with zeros to whole tiles (row stride 4 TK').
+template <int TS, int TM, int TK, bool FWD>
+__device__ __forceinline__ void fdm_matrix(const double *Sd, double (&m)[TM][TK])
 {
+    const int i = threadIdx.x & 3, k = (threadIdx.x >> 4) & 3;
+    const double *p = Sd + (FWD ? 4 * TS * k + i : 4 * TS * i + k);
 #pragma unroll
-    for (int m = 0; m < X; ++m) {
-        double s = M[m * X] * x[0];
+    for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-        for (int l = 1; l < X; ++l) s = fma(M[m * X + l], x[l], s);
-        y[m] = s;
+        for (int tk = 0; tk < TK; ++tk) m[tm][tk] = p[FWD ? 16 * TS * tk + 4 * tm : 16 * TS * tm + 4 * tk];
+}
+
+// One transform of the workgroup's COUNT pencils, 16 per tile, the tiles dealt to the W
+// waves in turn: get(h, x) loads the operand rows of the wave's tile h, put(h, y) takes
+// the result rows.  HG tiles are in flight together, so that consecutive matrix
+// instructions are independent (a dependent one waits for its predecessor).
+template <int COUNT, typename Sh, int TM, int TK, typename Get, typename Put>
+__device__ __forceinline__ void fdm_stage(const double (&m)[TM][TK], Get get, Put put)
+{
+    constexpr int W = Sh::W, TPW = (COUNT + 16 * W - 1) / (16 * W), HG = TPW < Sh::HG ? TPW : Sh::HG;
+#pragma unroll
+    for (int h0 = 0; h0 < TPW; h0 += HG) {
+        double x[HG][TK], y[HG][TM];
+#pragma unroll
+        for (int h = 0; h < HG; ++h)
+            if (h0 + h < TPW) get(h0 + h, x[h]);
+#pragma unroll
+        for (int tk = 0; tk < TK; ++tk)
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+                for (int h = 0; h < HG; ++h)
+                    if (h0 + h < TPW)
+                        y[h][tm] = __builtin_amdgcn_mfma_f64_4x4x4f64(m[tm][tk], x[h][tk], tk ? y[h][tm] : 0.0, 0, 0, 0);
+#pragma unroll
+        for (int h = 0; h < HG; ++h)
+            if (h0 + h < TPW) put(h0 + h, y[h]);
     }
 }
 
-// Stage one element's S (3 X^2 values) and lambda (3 X) in LDS with coalesced loads:
-// S is kept twice, transposed for the forward transforms and as is for the inverse
-// ones, so that the two phases read distinct arrays and no matrix stays live in
-// registers between them (both are read back as broadcasts).
-template <int X, int NT>
-__device__ __forceinline__ void fdm_stage(const double *Se, const double *le, double *Sf, double *Si, double *lam,
-                                          int t)
+// Pencil of lane column c in the wave's tile h, clamped to the COUNT pencils there are
+// (a clamped lane computes the last pencil again and stores nothing).
+template <int COUNT, int W>
+__device__ __forceinline__ int fdm_pencil(int wave, int c, int h)
 {
-    constexpr int X2 = X * X;
-    for (int q = t; q < 3 * X2; q += NT) {
-        const double v = Se[q];
-        const int d = q / X2, l = (q % X2) / X, m = q % X;
-        Si[q] = v;
-        Sf[d * X2 + m * X + l] = v;
-    }
-    for (int q = t; q < 3 * X; q += NT) lam[q] = le[q];
+    const int p = 16 * (wave + W * h) + c;
+    return 16 * W * (h + 1) <= COUNT ? p : min(p, COUNT - 1);
+}
+template <int COUNT, int W>
+__device__ __forceinline__ bool fdm_valid(int wave, int c, int h)
+{
+    return 16 * W * (h + 1) <= COUNT || 16 * (wave + W * h) + c < COUNT;
 }
 
-// Coarse restriction of one element: pr[h] = the sum over the element's owned points
-// of r times the trilinear function of corner q = t + h NT (for q < 8; corner
-// c = a + 2 b + 4 c'), from each pencil's sums s0, s1 against the two linear functions
-// along t (lane t holds pencil tl when own is set), then along s and along r through
-// LDS, in a fixed order.  red: 2 lx^2 + 4 lx doubles.
-template <int LX, int NT>
-__device__ __forceinline__ void corner_sums(double s0, double s1, bool own, int tl, int t, const double *lin,
-                                            double *red, double (&pr)[(8 + NT - 1) / NT])
+// Rows 4 t + g (of X in use) of the lane's pencil; p points at row 0, rows STRIDE apart.
+template <int X, int T, int STRIDE>
+__device__ __forceinline__ void fdm_get(const double *p, int g, double (&x)[T])
 {
-    constexpr int L2 = LX * LX, NQ = (8 + NT - 1) / NT;
-    if (own) {
-        red[tl] = s0;
-        red[L2 + tl] = s1;
-    }
-    bsync<NT>();
-    for (int q = t; q < 4 * LX; q += NT) {
-        const int i = q % LX, cb = q / LX;  // cb = (j side) + 2 (k side)
-        const double *rk = red + (cb >> 1) * L2 + i;
-        const double *lj = lin + (cb & 1) * LX;
-        double s = 0.0;
-        for (int j = 0; j < LX; ++j) s = fma(lj[j], rk[LX * j], s);
-        red[2 * L2 + q] = s;
-    }
-    bsync<NT>();
 #pragma unroll
-    for (int h = 0; h < NQ; ++h) {
-        const int q = t + h * NT;
-        if (q >= 8) break;
-        const double *li = lin + (q & 1) * LX;
-        const double *u = red + 2 * L2 + (q >> 1) * LX;
-        double s = 0.0;
-        for (int i = 0; i < LX; ++i) s = fma(li[i], u[i], s);
-        pr[h] = s;
-    }
+    for (int t = 0; t < T; ++t) x[t] = (4 * t + 3 < X || 4 * t + g < X) ? p[(4 * t + g) * STRIDE] : 0.0;
+}
+template <int X, int T, int STRIDE>
+__device__ __forceinline__ void fdm_put(double *p, int g, const double (&y)[T])
+{
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+        if (4 * t + 3 < X || 4 * t + g < X) p[(4 * t + g) * STRIDE] = y[t];
 }
 
-// The fast-diagonalisation solve on an X^3 box held as t-pencils (lane t = a + X b holds
-// points (a, b, 0..X-1) in x): forward transform along t in registers, along r and
-// along s through the box in LDS (row stride X + 1), the division by
-// h1 (lr_a + ls_j + lt_b) + h2, and the inverse transforms along s and along r.  The
-// result is left in cube for the caller's inverse transform along t.  Expects S and
-// lambda staged and a barrier after the staging.
-template <int X, int NT>
-__device__ __forceinline__ void fdm_core(double (&x)[X], double (&y)[X], double *cube, const double *Sf,
-                                         const double *Si, const double *lam, double h1, double h2, int a, int b)
-{
-    constexpr int X2 = X * X;
-    fdm_mul<X>(Sf + 2 * X2, x, y);
-#pragma unroll
-    for (int k = 0; k < X; ++k) cube[lidx<X>(a, b, k)] = y[k];
-    bsync<NT>();
-    // r-pencil (j = a, k = b)
-#pragma unroll
-    for (int i = 0; i < X; ++i) x[i] = cube[lidx<X>(i, a, b)];
-    fdm_mul<X>(Sf, x, y);
-#pragma unroll
-    for (int i = 0; i < X; ++i) cube[lidx<X>(i, a, b)] = y[i];
-    bsync<NT>();
-    // s-pencil (i = a, k = b)
-#pragma unroll
-    for (int j = 0; j < X; ++j) x[j] = cube[lidx<X>(a, j, b)];
-    fdm_mul<X>(Sf + X2, x, y);
-    {
-        const double lra = lam[a], ltb = lam[2 * X + b];
-#pragma unroll
-        for (int j = 0; j < X; ++j) y[j] /= h1 * (lra + lam[X + j] + ltb) + h2;
-    }
-    fdm_mul<X>(Si + X2, y, x);
-#pragma unroll
-    for (int j = 0; j < X; ++j) cube[lidx<X>(a, j, b)] = x[j];
-    bsync<NT>();
-#pragma unroll
-    for (int i = 0; i < X; ++i) y[i] = cube[lidx<X>(i, a, b)];
-    fdm_mul<X>(Si, y, x);
-#pragma unroll
-    for (int i = 0; i < X; ++i) cube[lidx<X>(i, a, b)] = x[i];
-    bsync<NT>();
-}
-
-// Element's own box: one element per workgroup of lx^2 lanes.  Lane t = a + lx b keeps
-// its t-pencil (i = a, j = b) in registers, so the two t-direction transforms are
-// register-only.
+// Residual at the extension point of a face (face coordinates fa, fb; fc = the face's
+// table entry {neighbour, base, sa, sb}); zero where the face has no neighbour.
 template <int LX>
-__global__ __launch_bounds__(LX * LX) void k_fdm(FdmArgs A)
+__device__ __forceinline__ double ext_value(const double *__restrict__ r, int4 fc, int fa, int fb)
 {
-    constexpr int L2 = LX * LX, L3 = L2 * LX, NT = L2, NQ = (8 + NT - 1) / NT;
-    __shared__ double cube[L2 * (LX + 1)];
-    __shared__ double red[2 * L2 + 4 * LX];
-    __shared__ __align__(16) double Sf[3 * L2];  // S^T per direction (forward)
-    __shared__ __align__(16) double Si[3 * L2];  // S per direction (inverse)
-    __shared__ double lam[3 * LX];
-    const int64_t e = blockIdx.x;
-    const int t = threadIdx.x, a = t % LX, b = t / LX;
-    fdm_stage<LX, NT>(A.S + e * 3 * L2, A.lam + e * 3 * LX, Sf, Si, lam, t);
-    const double *__restrict__ lin = A.lin;
-    double x[LX], y[LX];
-    const double *r = A.r + e * L3;
-#pragma unroll
-    for (int k = 0; k < LX; ++k) x[k] = r[k * L2 + t];
-    double pr[NQ];
-    if (A.part) {
-        const uint8_t *ow = A.owner + e * L3;
-        double s0 = 0.0, s1 = 0.0;
-#pragma unroll
-        for (int k = 0; k < LX; ++k) {
-            const double v = ow[k * L2 + t] ? x[k] : 0.0;
-            s0 = fma(lin[k], v, s0);
-            s1 = fma(lin[LX + k], v, s1);
-        }
-        corner_sums<LX, NT>(s0, s1, true, t, t, lin, red, pr);
-    }
-    bsync<NT>();  // S and lambda staged
-    fdm_core<LX, NT>(x, y, cube, Sf, Si, lam, A.h1, A.h2, a, b);
-#pragma unroll
-    for (int k = 0; k < LX; ++k) y[k] = cube[lidx<LX>(a, b, k)];
-    fdm_mul<LX>(Si + 2 * L2, y, x);
-    double *z = A.z + e * L3;
-#pragma unroll
-    for (int k = 0; k < LX; ++k) z[k * L2 + t] = x[k];
-    if (A.part) {
-#pragma unroll
-        for (int h = 0; h < NQ; ++h) {
-            const int q = t + h * NT;
-            if (q >= 8) break;
-            A.part[e * 8 + q] = pr[h];
-        }
-    }
+    constexpr int L3 = LX * LX * LX;  // (a field has fewer than 2^31 points)
+    return fc.x < 0 ? 0.0 : r[fc.x * L3 + fc.y + fa * fc.z + fb * fc.w];
 }
 
-// Residual at the extension point of face f (face coordinates fa, fb) of the element
-// whose face table fc (6 x {neighbour, base, sa, sb}) is staged in LDS; zero where the
-// face has no neighbour.
-template <int LX>
-__device__ __forceinline__ double ext_value(const double *__restrict__ r, const int32_t *fc, int f, int fa, int fb)
-{
-    constexpr int64_t L3 = (int64_t)LX * LX * LX;
-    const int32_t e2 = fc[4 * f];
-    if (e2 < 0) return 0.0;
-    return r[(int64_t)e2 * L3 + fc[4 * f + 1] + fa * fc[4 * f + 2] + fb * fc[4 * f + 3]];
-}
-
-// Element box extended by one point beyond each face: one element per workgroup of
-// X^2 lanes, X = lx + 2.  Lane t = a + X b holds the extended t-pencil (a, b, 0..X-1);
-// extended coordinate c is element coordinate c - 1.  Its right-hand side:
-//  - own points (1 <= a, b, k <= lx): r of the element, read coalesced per t-slab;
+// One element per workgroup of W waves; the waves share the 16-pencil tiles of every
+// transform.  OV: the right-hand side of the extended box is
+//  - own points: r of the element;
 //  - one coordinate outside (a face layer): r at the neighbour's point one GLL index
 //    inside it (face table A.face), zero without a neighbour;
 //  - two or three coordinates outside (box edges and corners): zero.
 // The 1-D operators of a face without a neighbour hold a decoupled extension node, so
-// with its zero right-hand side the solve there equals the element-only one.  Only the
-// own points are transformed back along t and written.
-template <int LX>
-__global__ __launch_bounds__((LX + 2) * (LX + 2)) void k_fdm_ov(FdmArgs A)
+// with its zero right-hand side the solve there equals the element-only one.
+// With A.part the same pass restricts r to the coarse space: per element the eight sums
+// over its owned points of r times the trilinear corner functions, contracted along t
+// with the loads, then along s and along r between the transforms.
+template <int LX, bool OV>
+__global__ __launch_bounds__((FdmShape<LX, OV>::NT)) __attribute__((
+    amdgpu_waves_per_eu(FdmShape<LX, OV>::EU))) void k_fdm(FdmArgs A)
 {
-    constexpr int X = LX + 2, X2 = X * X, L2 = LX * LX, L3 = L2 * LX, NT = X2, NQ = (8 + NT - 1) / NT;
-    __shared__ double cube[X2 * (X + 1)];
+    using Sh = FdmShape<LX, OV>;
+    constexpr int X = Sh::X, P = Sh::P, T = Sh::T, TL = Sh::TL, W = Sh::W, NT = Sh::NT;
+    constexpr int X2 = X * X, L2 = LX * LX, L3 = L2 * LX;
+    __shared__ double cube[P * X2];
     __shared__ double red[2 * L2 + 4 * LX];
-    __shared__ __align__(16) double Sf[3 * X2];
-    __shared__ __align__(16) double Si[3 * X2];
     __shared__ double lam[3 * X];
-    __shared__ int32_t fc[24];
+    constexpr int TS = T, S2 = 16 * T * T;  // padded matrix
+    __shared__ double Ss[3 * S2];
     const int64_t e = blockIdx.x;
-    const int t = threadIdx.x, a = t % X, b = t / X;
-    fdm_stage<X, NT>(A.S + e * 3 * X2, A.lam + e * 3 * X, Sf, Si, lam, t);
-    for (int q = t; q < 24; q += NT) fc[q] = A.face[e * 24 + q];  // NT is 16 at lx = 2
-    bsync<NT>();  // face table, S and lambda staged
-    const double *__restrict__ r = A.r;
-    const bool ia = a >= 1 && a <= LX, ib = b >= 1 && b <= LX, own = ia && ib;
-    double x[X], y[X];
+    const int tid = threadIdx.x, c = tid & 15, g = (tid >> 4) & 3;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const double *__restrict__ re = A.r + e * L3;
+    const double *__restrict__ lin = A.lin;
+    // everything the element reads from memory is requested at once
 #pragma unroll
-    for (int k = 0; k < X; ++k) x[k] = 0.0;
-    if (own) {
-        const double *re = r + e * L3 + (a - 1) + LX * (b - 1);
-#pragma unroll
-        for (int k = 0; k < LX; ++k) x[k + 1] = re[k * L2];
-        x[0] = ext_value<LX>(r, fc, 4, a - 1, b - 1);      // face t = 0
-        x[X - 1] = ext_value<LX>(r, fc, 5, a - 1, b - 1);  // face t = lx - 1
-    } else if (ia != ib) {
-        // an r face layer (a outside: face coordinates (j, k)) or an s face layer
-        // (b outside: face coordinates (i, k))
-        const int f = ib ? (a == X - 1 ? 1 : 0) : (b == X - 1 ? 3 : 2);
-        const int fa = ib ? b - 1 : a - 1;
-#pragma unroll
-        for (int k = 0; k < LX; ++k) x[k + 1] = ext_value<LX>(r, fc, f, fa, k);
+    for (int q0 = 0; q0 < 3 * S2; q0 += NT) {
+        const int q = q0 + tid;
+        if (3 * S2 % NT == 0 || q < 3 * S2) {
+            const int col = q % (4 * T), row = q / (4 * T) % (4 * T), d = q / S2;
+            Ss[q] = X % 4 == 0 || (col < X && row < X) ? A.S[(e * 3 + d) * X2 + row * X + col] : 0.0;
+        }
     }
-    double pr[NQ];
-    if (A.part) {
-        double s0 = 0.0, s1 = 0.0;
-        if (own) {
-            const uint8_t *ow = A.owner + e * L3 + (a - 1) + LX * (b - 1);
-            const double *__restrict__ lin = A.lin;
+    for (int q = tid; q < 3 * X; q += NT) lam[q] = A.lam[e * 3 * X + q];
+    constexpr int TPW = (X2 + 16 * W - 1) / (16 * W), PLANE = P * X;
+    double xr[OV ? 1 : TPW][T];  // element box: the pencils along t
+    unsigned ob[TPW];            // their owner flags, bit t for row 4 t + g
+    int px[TPW], py[TPW];        // pencil p = px + X py
 #pragma unroll
-            for (int k = 0; k < LX; ++k) {
-                const double v = ow[k * L2] ? x[k + 1] : 0.0;
-                s0 = fma(lin[k], v, s0);
-                s1 = fma(lin[LX + k], v, s1);
+    for (int h = 0; h < TPW; ++h) {
+        const int p = fdm_pencil<X2, W>(wave, c, h);
+        py[h] = p / X;
+        px[h] = p - X * py[h];
+        if constexpr (!OV) fdm_get<X, T, L2>(re + p, g, xr[h]);
+        ob[h] = 0;
+        if (A.part && fdm_valid<X2, W>(wave, c, h) && (!OV || (px[h] < LX && py[h] < LX))) {
+            const uint8_t *ow = A.owner + e * L3 + px[h] + LX * py[h];
+#pragma unroll
+            for (int t = 0; t < TL; ++t)
+                if (4 * t + 3 < LX || 4 * t + g < LX) ob[h] |= ow[(4 * t + g) * L2] ? 1u << t : 0u;
+        }
+    }
+    if constexpr (OV) {
+        int4 fc[(6 * L2 + NT - 1) / NT];
+        const int4 *__restrict__ face = (const int4 *)A.face + e * 6;
+#pragma unroll
+        for (int q0 = 0, u = 0; q0 < 6 * L2; q0 += NT, ++u) fc[u] = face[min((q0 + tid) / L2, 5)];
+#pragma unroll
+        for (int q0 = 0; q0 < L3; q0 += NT) {
+            const int q = q0 + tid;
+            if (L3 % NT == 0 || q < L3) cube[q % LX + P * (q / LX % LX + X * (q / L2))] = re[q];
+        }
+#pragma unroll
+        for (int q0 = 0, u = 0; q0 < 6 * L2; q0 += NT, ++u) {
+            const int q = q0 + tid;
+            if (6 * L2 % NT == 0 || q < 6 * L2) {
+                const int f = q / L2, fa = q % LX, fb = q / LX % LX, d = f >> 1, n = LX + (f & 1);
+                // the face point's two coordinates, ascending direction order
+                const int st = d == 0 ? P : 1, su = d == 2 ? P : PLANE, sn = d == 0 ? 1 : d == 1 ? P : PLANE;
+                cube[st * fa + su * fb + sn * n] = ext_value<LX>(A.r, fc[u], fa, fb);
             }
         }
-        corner_sums<LX, NT>(s0, s1, own, (a - 1) + LX * (b - 1), t, A.lin, red, pr);
-    }
-    fdm_core<X, NT>(x, y, cube, Sf, Si, lam, A.h1, A.h2, a, b);
-    if (own) {
-#pragma unroll
-        for (int k = 0; k < X; ++k) y[k] = cube[lidx<X>(a, b, k)];
-        double *z = A.z + e * L3 + (a - 1) + LX * (b - 1);
-        const double *St = Si + 2 * X2;
-#pragma unroll
-        for (int m = 1; m <= LX; ++m) {
-            double s = St[m * X] * y[0];
-#pragma unroll
-            for (int l = 1; l < X; ++l) s = fma(St[m * X + l], y[l], s);
-            z[(m - 1) * L2] = s;
+        for (int q = tid; q < 12 * X; q += NT) {
+            const int o = q / (4 * X), n = q % X, u = LX + (q / X & 1), v = LX + (q / (2 * X) & 1);
+            cube[o == 0 ? n + P * (u + X * v) : o == 1 ? u + P * (n + X * v) : u + P * (v + X * n)] = 0.0;
         }
     }
-    if (A.part) {
+    bsync<NT>();
+    // forward along t; the restriction's sums along t are one more (two-row) product
+    {
+        double mt[T][T], lt[1][TL];
+        fdm_matrix<TS, T, T, true>(Ss + 2 * S2, mt);
 #pragma unroll
-        for (int h = 0; h < NQ; ++h) {
-            const int q = t + h * NT;
-            if (q >= 8) break;
-            A.part[e * 8 + q] = pr[h];
+        for (int t = 0; t < TL; ++t) {
+            const int l = 4 * t + g, row = c & 3;
+            lt[0][t] = row < 2 && (LX % 4 == 0 || l < LX) ? lin[row * LX + (LX % 4 == 0 || l < LX ? l : 0)] : 0.0;
         }
+        fdm_stage<X2, Sh, T, T>(
+            mt,
+            [&](int h, double (&x)[T]) {
+                if constexpr (OV) fdm_get<X, T, PLANE>(cube + px[h] + P * py[h], g, x);
+                else {
+#pragma unroll
+                    for (int t = 0; t < T; ++t) x[t] = xr[h][t];
+                }
+                if (A.part) {
+                    double s = 0.0;
+#pragma unroll
+                    for (int t = 0; t < TL; ++t)
+                        s = __builtin_amdgcn_mfma_f64_4x4x4f64(lt[0][t], ob[h] >> t & 1 ? x[t] : 0.0, s, 0, 0, 0);
+                    // row g < 2 of the result: the sum against linear function g
+                    if (fdm_valid<X2, W>(wave, c, h) && g < 2 && (!OV || (px[h] < LX && py[h] < LX)))
+                        red[g * L2 + px[h] + LX * py[h]] = s;
+                }
+            },
+            [&](int h, const double (&y)[T]) {
+                if (fdm_valid<X2, W>(wave, c, h)) fdm_put<X, T, PLANE>(cube + px[h] + P * py[h], g, y);
+            });
+    }
+    bsync<NT>();
+    if (A.part)
+        for (int q = tid; q < 4 * LX; q += NT) {
+            const int i = q % LX, cb = q / LX;  // cb = (j side) + 2 (k side)
+            const double *rk = red + (cb >> 1) * L2 + i;
+            const double *lj = lin + (cb & 1) * LX;
+            double s = 0.0;
+            for (int j = 0; j < LX; ++j) s = fma(lj[j], rk[LX * j], s);
+            red[2 * L2 + q] = s;
+        }
+    // forward along r: pencil (j, k) is row p = j + X k
+    {
+        double mr[T][T];
+        fdm_matrix<TS, T, T, true>(Ss, mr);
+        fdm_stage<X2, Sh, T, T>(
+            mr, [&](int h, double (&x)[T]) { fdm_get<X, T, 1>(cube + P * fdm_pencil<X2, W>(wave, c, h), g, x); },
+            [&](int h, const double (&y)[T]) {
+                if (fdm_valid<X2, W>(wave, c, h)) fdm_put<X, T, 1>(cube + P * fdm_pencil<X2, W>(wave, c, h), g, y);
+            });
+    }
+    bsync<NT>();
+    if (A.part && tid < 8) {
+        const double *li = lin + (tid & 1) * LX;
+        const double *u = red + 2 * L2 + (tid >> 1) * LX;
+        double s = 0.0;
+        for (int i = 0; i < LX; ++i) s = fma(li[i], u[i], s);
+        A.part[e * 8 + tid] = s;
+    }
+    // forward along s, the division by the box operator's eigenvalues, inverse along s:
+    // pencil (i, k), p = i + X k
+    {
+        double ms[T][T], is[TL][T], ls[T];
+        fdm_matrix<TS, T, T, true>(Ss + S2, ms);
+        fdm_matrix<TS, TL, T, false>(Ss + S2, is);
+#pragma unroll
+        for (int t = 0; t < T; ++t) ls[t] = lam[X + (4 * t + 3 < X ? 4 * t + g : min(4 * t + g, X - 1))];
+        double v[TPW][T];
+        fdm_stage<X2, Sh, T, T>(
+            ms, [&](int h, double (&x)[T]) { fdm_get<X, T, P>(cube + px[h] + PLANE * py[h], g, x); },
+            [&](int h, const double (&y)[T]) {
+                // (a row past the last mode is zero here: its matrix rows are)
+                const double lr = lam[px[h]], lt = lam[2 * X + py[h]];
+#pragma unroll
+                for (int t = 0; t < T; ++t) v[h][t] = y[t] / (A.h1 * (lr + ls[t] + lt) + A.h2);
+            });
+        fdm_stage<X2, Sh, TL, T>(
+            is,
+            [&](int h, double (&x)[T]) {
+#pragma unroll
+                for (int t = 0; t < T; ++t) x[t] = v[h][t];
+            },
+            [&](int h, const double (&z)[TL]) {
+                if (fdm_valid<X2, W>(wave, c, h)) fdm_put<LX, TL, P>(cube + px[h] + PLANE * py[h], g, z);
+            });
+    }
+    bsync<NT>();
+    // inverse along r: pencils (j, k) with j an own point, p = j + lx k
+    {
+        constexpr int NR = LX * X;
+        double ir[TL][T];
+        fdm_matrix<TS, TL, T, false>(Ss, ir);
+        auto row = [&](int h) {
+            const int p = fdm_pencil<NR, W>(wave, c, h), k = p / LX;
+            return cube + P * (p - LX * k + X * k);
+        };
+        fdm_stage<NR, Sh, TL, T>(
+            ir, [&](int h, double (&x)[T]) { fdm_get<X, T, 1>(row(h), g, x); },
+            [&](int h, const double (&y)[TL]) {
+                if (fdm_valid<NR, W>(wave, c, h)) fdm_put<LX, TL, 1>(row(h), g, y);
+            });
+    }
+    bsync<NT>();
+    // inverse along t: own pencils (i, j), p = i + lx j; the own points go to z
+    {
+        double it[TL][T];
+        fdm_matrix<TS, TL, T, false>(Ss + 2 * S2, it);
+        fdm_stage<L2, Sh, TL, T>(
+            it,
+            [&](int h, double (&x)[T]) {
+                const int p = fdm_pencil<L2, W>(wave, c, h), j = p / LX;
+                fdm_get<X, T, PLANE>(cube + (p - LX * j) + P * j, g, x);
+            },
+            [&](int h, const double (&y)[TL]) {
+                if (fdm_valid<L2, W>(wave, c, h))
+                    fdm_put<LX, TL, L2>(A.z + e * L3 + fdm_pencil<L2, W>(wave, c, h), g, y);
+            });
     }
 }
 
@@ -336,10 +402,11 @@ hipError_t SEM_PASTE(sem_launch_fdm_lx, SEM_LX)(const sem::FdmArgs *A, hipStream
     if (A->nelv > 0x7fffffff) return hipErrorInvalidValue;
     if (A->part && (!A->owner || !A->lin)) return hipErrorInvalidValue;
     if (A->face)
-        hipLaunchKernelGGL((sem::k_fdm_ov<SEM_LX>), dim3((unsigned)A->nelv), dim3((SEM_LX + 2) * (SEM_LX + 2)), 0,
+        hipLaunchKernelGGL((sem::k_fdm<SEM_LX, true>), dim3((unsigned)A->nelv), dim3(sem::FdmShape<SEM_LX, true>::NT), 0,
                            st, *A);
     else
-        hipLaunchKernelGGL((sem::k_fdm<SEM_LX>), dim3((unsigned)A->nelv), dim3(SEM_LX * SEM_LX), 0, st, *A);
+        hipLaunchKernelGGL((sem::k_fdm<SEM_LX, false>), dim3((unsigned)A->nelv), dim3(sem::FdmShape<SEM_LX, false>::NT),
+                           0, st, *A);
     return hipGetLastError();
 }
 hipError_t SEM_PASTE(sem_launch_prolong_lx, SEM_LX)(const sem::ProlongArgs *A, hipStream_t st)

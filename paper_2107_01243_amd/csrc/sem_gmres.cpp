@@ -291,9 +291,12 @@ static sem_status schwarz_setup_overlap(sem_coef c, hipStream_t st)
                 for (int i = 0; i < X; ++i)
                     for (int q = 0; q < X; ++q) a[i * X + q] = K[i * X + q] / std::sqrt(M[i] * M[q]);
                 semh::sym_eig(X, a.data(), V.data(), l.data());
+                // rows in the kernel's node order: own nodes, then the extension nodes
                 double *Sd = &S[((size_t)e * 3 + d) * X * X];
-                for (int i = 0; i < X; ++i)
-                    for (int m = 0; m < X; ++m) Sd[i * X + m] = V[i * X + m] / std::sqrt(M[i]);
+                for (int i = 0; i < X; ++i) {
+                    const int row = i == 0 ? lx : i == X - 1 ? lx + 1 : i - 1;
+                    for (int m = 0; m < X; ++m) Sd[row * X + m] = V[i * X + m] / std::sqrt(M[i]);
+                }
                 for (int m = 0; m < X; ++m) lam[((size_t)e * 3 + d) * X + m] = l[m];
             }
         }

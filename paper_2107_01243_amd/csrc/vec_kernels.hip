@@ -1764,7 +1764,7 @@ hipError_t sem_launch_coarse_cg(const CoarseArgs *A, int iters, hipStream_t st)
 {
     if (A->nv == 0) return hipSuccess;
     if (A->width < 1 || A->nv > 0x7fffffffLL) return hipErrorInvalidValue;
-    if (A->nv <= CCG_SMALL && A->width <= RESW) {
+    if (iters > 0 && A->nv <= CCG_SMALL && A->width <= RESW) {
         if (A->nv <= CST) hipLaunchKernelGGL(k_ccg_small<1>, dim3(1), dim3(CST), 0, st, *A, iters);
         else if (A->nv <= 2 * CST) hipLaunchKernelGGL(k_ccg_small<2>, dim3(1), dim3(CST), 0, st, *A, iters);
         else hipLaunchKernelGGL(k_ccg_small<3>, dim3(1), dim3(CST), 0, st, *A, iters);

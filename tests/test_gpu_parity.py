@@ -590,6 +590,27 @@ def test_schwarz_overlap_apply_vs_oracle(shape, lx):
     O.set_coef(1.0, 0.0)
 
 
+@pytest.mark.parametrize("shape,lx", [((2, 2, 1), 3), ((3, 1, 2), 7), ((2, 1, 1), 9), ((1, 1, 2), 11),
+                                      ((1, 2, 1), 13), ((1, 1, 1), 14), ((1, 1, 1), 15)])
+def test_schwarz_local_solves_tile_remainders(shape, lx):
+    """Local solves where the box is not a whole number of 4-row tiles or its pencils not a
+    whole number of 16-pencil tiles per wave, element box and overlap, against the
+    oracle's dense solves.  Six products of at most 17 terms per point and one division:
+    within 1e-10 of the largest value at the condition numbers of these boxes."""
+    nx, ny, nz = shape
+    say(f"[schwarz tiles] {nx}x{ny}x{nz} lx={lx}")
+    P, O = pair3(nx, ny, nz, lx)
+    rl = workloads.uniform(P.n, 7)
+    ro = O.assemble_rhs(rl)
+    r = P.assemble(to_dev(rl))
+    for ov in (False, True):
+        O.schwarz_setup(overlap=ov)
+        z = sem.schwarz_apply(torch.empty_like(r), r, P.coef, P.msh, P.Xh, P.gs, coarse_iters=3, overlap=ov)
+        d = rel_inf(host(z), O.schwarz_apply(ro, coarse_iters=3))
+        say(f"   overlap={ov}: rel diff {d:.2e}")
+        assert d <= 1e-10
+
+
 @pytest.mark.parametrize("shape", [(7, 7, 7), (2, 8, 18), (7, 7, 15), (4, 4, 40), (7, 11, 15), (9, 10, 13)])
 def test_coarse_solve_sizes_vs_oracle(shape):
     """The coarse solve at the edges of its forms: 512, 513, 1024, 1025, 1536 and 1540
