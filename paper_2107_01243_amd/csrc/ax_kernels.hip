@@ -25,6 +25,8 @@
 #include <stdint.h>
 #include <string.h>
 
+#include <type_traits>
+
 #include "sem_kernels.h"
 #include "sem_pencil.h"
 
@@ -721,17 +723,20 @@ __device__ __forceinline__ void spencil(T *__restrict__ eb, unsigned t, const T 
 }
 
 // Coefficient forms of the lean kernels, fixed at compile time so that no pointer test
-// or branch sits between the loads and the arithmetic that uses them.
-enum LeanKind : int {
-    KPOISSON = 0,  // h1 scalar, no mass term
-    KHELM = 1,     // h1 scalar, h2 scalar != 0 (velocity Helmholtz)
-    KH1F = 2,      // h1 field, h2 scalar != 0
-    KGEN = 3       // anything else: h1 and h2 scalars or fields, tested at run time
-};
+// or branch sits between the loads and the arithmetic that uses them (a form tested at
+// run time spilled up to 159 registers at lx = 12): bit 0, h1 is a field; bits 1-2, the
+// mass term: none, h2 a scalar, h2 a field.
+constexpr int KPOISSON = 0, KINDS = 6;
+constexpr bool kind_h1f(int kind) { return kind & 1; }
+constexpr int kind_mass(int kind) { return kind >> 1; }
 
+// h (a x + b y + c z), the order of the products fixed so that every kernel that applies
+// G (G in registers or in chunks, one field or three) rounds alike.
 template <typename T>
-__device__ __forceinline__ const T *ebase(const T *p, int64_t off) { return p ? p + off : nullptr; }
-
+__device__ __forceinline__ T row_G(T h, T a, T x, T b, T y, T c, T z)
+{
+    return h * fma(c, z, fma(b, y, a * x));
+}
 
 // (ur, us, ut) <- h1 G (ur, us, ut) with G (and the h1 field) read in chunks of C
 // points, Ge = G + element base (plane stride n).  NTL: non-temporal loads (G used by
@@ -751,8 +756,7 @@ __device__ __forceinline__ void apply_G_lean(const T *__restrict__ Ge, const T *
                 const unsigned o = (k0 + kk) * (LX * LX) + t;
 #pragma unroll
                 for (int f = 0; f < 6; ++f) g[f][kk] = ldx<NTL>(Ge + f * n + o);
-                if constexpr (KIND == KH1F) h[kk] = h1e[o];
-                else if constexpr (KIND == KGEN) h[kk] = h1e ? h1e[o] : h1s;
+                if constexpr (kind_h1f(KIND)) h[kk] = h1e[o];
                 else h[kk] = h1s;
             }
         }
@@ -761,19 +765,19 @@ __device__ __forceinline__ void apply_G_lean(const T *__restrict__ Ge, const T *
             const int k = k0 + kk;
             if (k < LX) {
                 const T r = ur[k], s = us[k], q = ut[k];
-                ur[k] = h[kk] * (g[0][kk] * r + g[3][kk] * s + g[4][kk] * q);
-                us[k] = h[kk] * (g[3][kk] * r + g[1][kk] * s + g[5][kk] * q);
-                ut[k] = h[kk] * (g[4][kk] * r + g[5][kk] * s + g[2][kk] * q);
+                ur[k] = row_G(h[kk], g[0][kk], r, g[3][kk], s, g[4][kk], q);
+                us[k] = row_G(h[kk], g[3][kk], r, g[1][kk], s, g[5][kk], q);
+                ut[k] = row_G(h[kk], g[4][kk], r, g[5][kk], s, g[2][kk], q);
             }
         }
     }
 }
 
-// h2 B at the lane's points (zero for KPOISSON), B and the h2 field read here.
+// h2 B at the lane's points (forms with a mass term), B and the h2 field read here.
 template <int LX, typename T, int KIND>
 __device__ __forceinline__ T mass_coef(const T *__restrict__ Be, const T *__restrict__ h2e, T h2s, unsigned o)
 {
-    if constexpr (KIND == KGEN) return h2e ? h2e[o] * Be[o] : h2s * Be[o];
+    if constexpr (kind_mass(KIND) == 2) return h2e[o] * Be[o];
     else return h2s * Be[o];
 }
 
@@ -782,12 +786,10 @@ template <int LX, typename T, int KIND>
 __device__ __forceinline__ void add_mass_lean(const T *__restrict__ Be, const T *__restrict__ h2e, T h2s, unsigned t,
                                               const T (&u)[LX], T (&w)[LX])
 {
-    if constexpr (KIND != KPOISSON) {
-        if (KIND != KGEN || h2e || h2s != T(0)) {
-            __builtin_amdgcn_sched_barrier(0);
+    if constexpr (kind_mass(KIND) != 0) {
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int k = 0; k < LX; ++k) w[k] = fma(mass_coef<LX, T, KIND>(Be, h2e, h2s, k * (LX * LX) + t), u[k], w[k]);
-        }
+        for (int k = 0; k < LX; ++k) w[k] = fma(mass_coef<LX, T, KIND>(Be, h2e, h2s, k * (LX * LX) + t), u[k], w[k]);
     }
 }
 
@@ -796,33 +798,31 @@ template <int LX, typename T, int KIND>
 __device__ __forceinline__ void add_mass_reload(const T *__restrict__ Be, const T *__restrict__ h2e, T h2s, unsigned t,
                                                 const T *__restrict__ ue, T (&w)[LX])
 {
-    if constexpr (KIND != KPOISSON) {
-        if (KIND != KGEN || h2e || h2s != T(0)) {
-            __builtin_amdgcn_sched_barrier(0);
+    if constexpr (kind_mass(KIND) != 0) {
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int k = 0; k < LX; ++k) {
-                const unsigned o = k * (LX * LX) + t;
-                w[k] = fma(mass_coef<LX, T, KIND>(Be, h2e, h2s, o), ue[o], w[k]);
-            }
+        for (int k = 0; k < LX; ++k) {
+            const unsigned o = k * (LX * LX) + t;
+            w[k] = fma(mass_coef<LX, T, KIND>(Be, h2e, h2s, o), ue[o], w[k]);
         }
     }
 }
 
-// (ur, us, ut) <- h1 G (ur, us, ut) from G pencils held in registers.
+// (ur, us, ut) <- h1 G (ur, us, ut) from G pencils held in registers; an h1 field's values
+// at hp[k * lx^2] (the lane's own column).
 template <int LX, typename T, int KIND>
-__device__ __forceinline__ void apply_G_regs(const T (&g)[6][LX], const T *__restrict__ h1e, T h1s, unsigned t,
-                                             T (&ur)[LX], T (&us)[LX], T (&ut)[LX])
+__device__ __forceinline__ void apply_G_regs(const T (&g)[6][LX], const T *hp, T h1s, T (&ur)[LX], T (&us)[LX],
+                                             T (&ut)[LX])
 {
 #pragma unroll
     for (int k = 0; k < LX; ++k) {
         T h;
-        if constexpr (KIND == KH1F) h = h1e[k * (LX * LX) + t];
-        else if constexpr (KIND == KGEN) h = h1e ? h1e[k * (LX * LX) + t] : h1s;
+        if constexpr (kind_h1f(KIND)) h = hp[k * (LX * LX)];
         else h = h1s;
         const T r = ur[k], s = us[k], q = ut[k];
-        ur[k] = h * (g[0][k] * r + g[3][k] * s + g[4][k] * q);
-        us[k] = h * (g[3][k] * r + g[1][k] * s + g[5][k] * q);
-        ut[k] = h * (g[4][k] * r + g[5][k] * s + g[2][k] * q);
+        ur[k] = row_G(h, g[0][k], r, g[3][k], s, g[4][k], q);
+        us[k] = row_G(h, g[3][k], r, g[1][k], s, g[5][k], q);
+        ut[k] = row_G(h, g[4][k], r, g[5][k], s, g[2][k], q);
     }
 }
 
@@ -846,36 +846,24 @@ __device__ __forceinline__ void div_nb(const DS &D, const T (&wr)[LX], const T (
 // Launch configuration of the lean kernels, per precision, field count and kernel
 // (CG: the fused CG matvec, which also keeps p for its dot product).
 //  * HOLD: with three fields sharing one G, hold G's six pencils in registers (loaded
-//    once, non-temporal) instead of reading them in chunks for every field; pays for the
-//    FP32 operator up to lx = 12 (in FP64 the held pencils would cost the second wave
-//    per SIMD; the FP32 CG matvec, which also holds p, is faster reading chunks at
-//    three waves per SIMD: 4.6 -> 3.7 ms at 48^3 x lx = 12).
+//    once, non-temporal) instead of reading them in chunks for every field: the L2 does
+//    not keep them, so they are read from memory three times otherwise.  It pays where
+//    they fit: the FP32 operator up to lx = 12, the FP64 operator at lx = 10 and 11 at two
+//    waves per SIMD (three Helmholtz fields, 20 million points: 635 -> 467 us and 676 ->
+//    492 us; with h1 and h2 fields 1690 -> 508 and 2000 -> 649 us; FP32 at lx = 12 with
+//    h1 and h2 fields 389 -> 294 us).  The FP32 CG matvec,
+//    which also holds p, is faster reading chunks at three waves per SIMD (4.6 -> 3.7 ms at
+//    48^3 x lx = 12).
 //  * NB: LDS element buffers, 4 (grad4 / div4: four barriers per field pass) or 2
 //    (grad_lean / div_lean: eight); in FP64 four would halve the workgroups a compute
 //    unit holds.
 //  * MINW: waves per SIMD the register allocation is held to.
-#ifndef SEM_AX_HOLD
-#define SEM_AX_HOLD 1
-#endif
-#ifndef SEM_CG_HOLD
-#define SEM_CG_HOLD 0
-#endif
-#ifndef SEM_AX_NB32
-#define SEM_AX_NB32 4
-#endif
-#ifndef SEM_CG_NB32
-#define SEM_CG_NB32 4
-#endif
-#ifndef SEM_CG_W32H
-#define SEM_CG_W32H 3
-#endif
 template <int LX, typename T, int NF, bool CG>
 struct LeanCfg {
     static constexpr bool F32 = sizeof(T) == 4;
-    static constexpr bool HOLD = NF > 1 && F32 && LX <= 12 && (CG ? SEM_CG_HOLD : SEM_AX_HOLD);
-    static constexpr int NB = F32 ? (CG ? SEM_CG_NB32 : SEM_AX_NB32) : 2;
-    static constexpr int MINW = HOLD ? (CG ? SEM_CG_W32H : 3)
-                                     : ((!CG && NF > 1 && !F32 && LX <= 12) ? 3 : Shape<LX, T>::MINW);
+    static constexpr bool HOLD = NF > 1 && !CG && LX <= (F32 ? 12 : 11);
+    static constexpr int NB = F32 ? 4 : 2;
+    static constexpr int MINW = HOLD ? (F32 ? 3 : 2) : Shape<LX, T>::MINW;
 };
 
 template <int LX, typename T, int NB>
@@ -896,12 +884,30 @@ __device__ __forceinline__ void ax_lean_body(const DS &D, const AxArgs<T> &A)
     const unsigned t = threadIdx.x;
     const int a = t % LX, b = t / LX;
     const int64_t e0 = (int64_t)blockIdx.x * (LX * LX * LX);
-    const T *Ge = A.G + e0;
-    const T *h1e = KIND >= KH1F ? ebase(A.h1, e0) : nullptr;
+    const T *Ge = A.G + e0, *Be = A.B + e0;
+    const T *h1e = kind_h1f(KIND) ? A.h1 + e0 : nullptr, *h2e = kind_mass(KIND) == 2 ? A.h2 + e0 : nullptr;
     T g[HOLD ? 6 : 1][LX];
+    // HOLD: with G in registers, h1 and h2 B of the lane's column wait in LDS (read back by
+    // the same lane); read again for every field they would come from memory
+    constexpr bool H1F = kind_h1f(KIND), MASS = kind_mass(KIND) != 0;
+    __shared__ T park[HOLD && H1F + MASS ? (H1F + MASS) * LX * LX * LX : 1];
+    T *hp = park + t, *mp = park + (H1F ? LX * LX * LX : 0) + t;
     if constexpr (HOLD) {
 #pragma unroll
         for (int q = 0; q < 6; ++q) lpencil<LX, T, true>(g[q], Ge + q * A.n, t);
+        T v[LX];
+        if constexpr (H1F) {
+            lpencil<LX, T, true>(v, h1e, t);
+#pragma unroll
+            for (int k = 0; k < LX; ++k) hp[k * (LX * LX)] = v[k];
+        }
+        if constexpr (MASS) {
+            lpencil<LX, T, true>(v, Be, t);
+            T v2[LX];
+            if constexpr (kind_mass(KIND) == 2) lpencil<LX, T, true>(v2, h2e, t);
+#pragma unroll
+            for (int k = 0; k < LX; ++k) mp[k * (LX * LX)] = (kind_mass(KIND) == 2 ? v2[k] : A.h2s) * v[k];
+        }
     }
 #pragma unroll 1
     for (int f = 0; f < NF; ++f) {
@@ -914,11 +920,21 @@ __device__ __forceinline__ void ax_lean_body(const DS &D, const AxArgs<T> &A)
                 lpencil<LX, T, false>(u, A.u + fe, t);
                 grad_nb<LX, T, NB>(D, u, lds.buf, a, b, ur, us, ut);
             }
-            if constexpr (HOLD) apply_G_regs<LX, T, KIND>(g, h1e ? fresh(h1e) : h1e, A.h1s, t, ur, us, ut);
-            else apply_G_lean<LX, T, KIND, NF == 1>(fresh(Ge), h1e ? fresh(h1e) : h1e, A.h1s, A.n, t, ur, us, ut);
+            if constexpr (HOLD) apply_G_regs<LX, T, KIND>(g, hp, A.h1s, ur, us, ut);
+            else apply_G_lean<LX, T, KIND, NF == 1>(fresh(Ge), H1F ? fresh(h1e) : h1e, A.h1s, A.n, t, ur, us, ut);
             div_nb<LX, T, NB>(D, ur, us, ut, lds.buf, a, b, w);
         }
-        add_mass_reload<LX, T, KIND>(A.B + e0, KIND == KGEN ? ebase(A.h2, e0) : nullptr, A.h2s, t, A.u + fe, w);
+        if constexpr (HOLD && MASS) {
+            const T *ue = A.u + fe;
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = 0; k < LX; ++k) w[k] = fma(mp[k * (LX * LX)], ue[k * (LX * LX) + t], w[k]);
+        } else {
+            // B and h2 are the same for every field: in FP64, held over the loop they would spill
+            constexpr bool AGAIN = NF > 1 && sizeof(T) == 8;
+            add_mass_reload<LX, T, KIND>(AGAIN ? fresh(Be) : Be, AGAIN && kind_mass(KIND) == 2 ? fresh(h2e) : h2e, A.h2s,
+                                         t, A.u + fe, w);
+        }
         spencil<LX, T>(A.w + fe, t, w);
     }
 }
@@ -937,7 +953,6 @@ __device__ __forceinline__ void cg_lean_body(const DS &D, const CgMatvecArgs<T> 
 {
     using S = Shape<LX, T>;
     using C = LeanCfg<LX, T, NF, true>;
-    constexpr bool HOLD = C::HOLD;
     static_assert(S::EPB == 1 && S::NT >= 64, "one element per workgroup of at least one wave");
     constexpr int NB = C::NB;
     __shared__ LeanBufs<LX, T, NB> lds;
@@ -950,12 +965,7 @@ __device__ __forceinline__ void cg_lean_body(const DS &D, const CgMatvecArgs<T> 
     for (int f = 0; f < NF; ++f) live = live || !A.scal[f].stop;
     if (!live) return;
     const T *Ge = A.G + e0;
-    const T *h1e = KIND >= KH1F ? ebase(A.h1, e0) : nullptr;
-    T g[HOLD ? 6 : 1][LX];
-    if constexpr (HOLD) {
-#pragma unroll
-        for (int q = 0; q < 6; ++q) lpencil<LX, T, true>(g[q], Ge + q * A.n, t);
-    }
+    const T *h1e = kind_h1f(KIND) ? A.h1 + e0 : nullptr;
     double part[NF];
 #pragma unroll 1
     for (int f = 0; f < NF; ++f) {
@@ -984,11 +994,13 @@ __device__ __forceinline__ void cg_lean_body(const DS &D, const CgMatvecArgs<T> 
         {
             T ur[LX], us[LX], ut[LX];
             grad_nb<LX, T, NB>(D, p, lds.buf, a, b, ur, us, ut);
-            if constexpr (HOLD) apply_G_regs<LX, T, KIND>(g, h1e ? fresh(h1e) : h1e, A.h1s, t, ur, us, ut);
-            else apply_G_lean<LX, T, KIND, NF == 1>(fresh(Ge), h1e ? fresh(h1e) : h1e, A.h1s, A.n, t, ur, us, ut);
+            apply_G_lean<LX, T, KIND, NF == 1>(fresh(Ge), kind_h1f(KIND) ? fresh(h1e) : h1e, A.h1s, A.n, t, ur, us, ut);
             div_nb<LX, T, NB>(D, ur, us, ut, lds.buf, a, b, w);
         }
-        add_mass_lean<LX, T, KIND>(A.B + e0, KIND == KGEN ? ebase(A.h2, e0) : nullptr, A.h2s, t, p, w);
+        const T *Be = A.B + e0, *h2e = kind_mass(KIND) == 2 ? A.h2 + e0 : nullptr;
+        constexpr bool REUSE = NF > 1 && sizeof(T) == 8;  // as in ax_lean_body
+        add_mass_lean<LX, T, KIND>(REUSE ? fresh(Be) : Be, REUSE && kind_mass(KIND) == 2 ? fresh(h2e) : h2e, A.h2s, t,
+                                   p, w);
         spencil<LX, T>(A.w + fe, t, w);
         double sum = 0.0;
 #pragma unroll
@@ -1016,6 +1028,389 @@ __global__ SEM_BOUNDS2((Shape<LX, T>::NT), (LeanCfg<LX, T, NF, true>::MINW)) voi
 {
     if constexpr (sizeof(T) == 8) cg_lean_body<LX, T, NF, KIND, CG1>(DMem<LX, T>{Dg}, A);
     else cg_lean_body<LX, T, NF, KIND, CG1>(DArg<LX, T>{D}, A);
+}
+
+// ------------------------------------------------------------------ matrix-core variants
+// One element per workgroup, its points spread over W waves in tiles of 16 pencils: lane
+// c + 16 g of a wave holds rows 4 t + g (t = 0 .. ceil(lx/4) - 1) of pencil c of each of
+// its tiles, and a derivative along the pencils is a matrix product D x on the matrix
+// cores whose result has the operand's layout (see Mat).  A lane holds lx^3 / (64 W)
+// points instead of a whole pencil, so the six geometric factors of all of them fit
+// its registers next to a field's derivatives, and with three fields G is read from
+// memory once.
+//
+// Field pass (three LDS element buffers, four barriers): u in the t layout goes to A;
+// A's r and s pencils are differentiated into B and C; every lane reads the r and s
+// derivatives of its own points back from B and C, applies h1 G and writes w_r, w_s to the
+// same places; B's r pencils and C's s pencils are multiplied with D^T in place (a tile's
+// pencils belong to one wave), and every lane adds the two at its points to D^T w_t.  A
+// buffer is written again only after a barrier that follows its last read.
+//
+// Matrix operand of D or D^T for the tile product.  FP64: 4x4x4 products of four
+// blocks with the same matrix tile (A: row lane % 4, column g; B, C: row g, pencil c).
+// FP32: 16x16x4 products (A: row lane % 16, column g; B: row g; C register r: row
+// 4 g + r); with the matrix rows permuted so that A's row q holds row 4 (q % 4) + q / 4,
+// C register r is row 4 r + g, the operand layout.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+template <int LX, typename T>
+struct Mat;
+
+template <int LX>
+struct Mat<LX, double> {
+    static constexpr int N = (LX + 3) / 4;
+    double m[N][N];
+    // D row-major in memory; tr: the transpose
+    __device__ __forceinline__ void load(const double *__restrict__ D, bool tr)
+    {
+        const int i = threadIdx.x & 3, k = (threadIdx.x >> 4) & 3;
+#pragma unroll
+        for (int a = 0; a < N; ++a)
+#pragma unroll
+            for (int b = 0; b < N; ++b) {
+                const int row = 4 * a + i, col = 4 * b + k;
+                const bool in = (4 * a + 3 < LX || row < LX) && (4 * b + 3 < LX || col < LX);
+                m[a][b] = in ? D[tr ? col * LX + row : row * LX + col] : 0.0;
+            }
+    }
+    __device__ __forceinline__ void mul(const double (&x)[N], double (&y)[N]) const
+    {
+#pragma unroll
+        for (int b = 0; b < N; ++b)
+#pragma unroll
+            for (int a = 0; a < N; ++a)
+                y[a] = __builtin_amdgcn_mfma_f64_4x4x4f64(m[a][b], x[b], b ? y[a] : 0.0, 0, 0, 0);
+    }
+};
+
+template <int LX>
+struct Mat<LX, float> {
+    static constexpr int N = (LX + 3) / 4;
+    float m[N];
+    __device__ __forceinline__ void load(const float *__restrict__ D, bool tr)
+    {
+        const int q = threadIdx.x & 15, k = (threadIdx.x >> 4) & 3, row = 4 * (q & 3) + (q >> 2);
+#pragma unroll
+        for (int b = 0; b < N; ++b) {
+            const int col = 4 * b + k;
+            m[b] = row < LX && col < LX ? D[tr ? col * LX + row : row * LX + col] : 0.0f;
+        }
+    }
+    __device__ __forceinline__ void mul(const float (&x)[N], float (&y)[N]) const
+    {
+        f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int b = 0; b < N; ++b) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(m[b], x[b], acc, 0, 0, 0);
+#pragma unroll
+        for (int a = 0; a < N; ++a) y[a] = acc[a];
+    }
+};
+
+template <int LX, typename T, int W>
+struct Tiles {
+    static constexpr int L2 = LX * LX, NTILE = (L2 + 15) / 16;
+    static constexpr int H = (NTILE + W - 1) / W;       // tiles per wave
+    static constexpr int R = (LX + 3) / 4;              // rows per lane and tile
+    static constexpr int P = (LX % 2) ? LX : LX + 1;    // LDS row stride
+    static constexpr int ESZ = L2 * P;
+    int wave, c, g;
+    int p[H], pi[H], pj[H];  // pencil of tile h (clamped) and its two coordinates, p = pi + lx pj
+    __device__ __forceinline__ Tiles()
+    {
+        wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        c = threadIdx.x & 15;
+        g = (threadIdx.x >> 4) & 3;
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+            const int q = 16 * (wave + W * h) + c;
+            p[h] = 16 * W * (h + 1) <= L2 ? q : (q < L2 ? q : L2 - 1);
+            pj[h] = p[h] / LX;
+            pi[h] = p[h] - LX * pj[h];
+        }
+    }
+    // tile h of this lane is a pencil of the element (a clamped lane is not)
+    __device__ __forceinline__ bool own(int h) const
+    {
+        return 16 * W * (h + 1) <= L2 || 16 * (wave + W * h) + c < L2;
+    }
+    __device__ __forceinline__ bool row(int t) const { return 4 * t + 3 < LX || 4 * t + g < LX; }
+    // LDS places of row 0 of the lane's t, r and s pencils and the strides of the rows
+    __device__ __forceinline__ int at_t(int h) const { return pi[h] + P * pj[h]; }
+    __device__ __forceinline__ int at_r(int h) const { return P * p[h]; }
+    __device__ __forceinline__ int at_s(int h) const { return pi[h] + P * LX * pj[h]; }
+    static constexpr int ST = P * LX, SR = 1, SS = P;
+    template <int STRIDE>
+    __device__ __forceinline__ void get(const T *b, T (&x)[R]) const
+    {
+#pragma unroll
+        for (int t = 0; t < R; ++t) x[t] = row(t) ? b[(4 * t + g) * STRIDE] : T(0);
+    }
+    template <int STRIDE>
+    __device__ __forceinline__ void put(T *b, int h, const T (&x)[R]) const
+    {
+        if (!own(h)) return;
+#pragma unroll
+        for (int t = 0; t < R; ++t)
+            if (row(t)) b[(4 * t + g) * STRIDE] = x[t];
+    }
+    // the lane's points of one field or plane; eb: element base (wave-uniform)
+    template <bool NTL>
+    __device__ __forceinline__ void load(const T *__restrict__ eb, T (&x)[H][R]) const
+    {
+#pragma unroll
+        for (int h = 0; h < H; ++h)
+#pragma unroll
+            for (int t = 0; t < R; ++t) x[h][t] = row(t) ? ldx<NTL>(eb + ((4 * t + g) * L2 + p[h])) : T(0);
+    }
+    template <bool NTS>
+    __device__ __forceinline__ void store(T *__restrict__ eb, const T (&x)[H][R]) const
+    {
+#pragma unroll
+        for (int h = 0; h < H; ++h)
+            if (own(h)) {
+#pragma unroll
+                for (int t = 0; t < R; ++t)
+                    if (row(t)) {
+                        T *q = eb + ((4 * t + g) * L2 + p[h]);
+                        if constexpr (NTS) __builtin_nontemporal_store(x[h][t], q);
+                        else *q = x[h][t];
+                    }
+            }
+    }
+};
+
+// The wave's pencils along r or s (at(h): row 0 of the lane's pencil of tile h) from buffer
+// X through D into buffer Y; X may be Y.
+template <int STRIDE, int LX, typename T, int W, typename TL, typename At>
+__device__ __forceinline__ void tile_pass(const TL &L, const Mat<LX, T> &D, const T *X, T *Y, At at)
+{
+    T x[TL::H][TL::R];
+#pragma unroll
+    for (int h = 0; h < TL::H; ++h) L.template get<STRIDE>(X + at(h), x[h]);
+#pragma unroll
+    for (int h = 0; h < TL::H; ++h) {
+        T v[TL::R];
+        D.mul(x[h], v);
+        L.template put<STRIDE>(Y + at(h), h, v);
+    }
+}
+
+// (ur, us, ut) <- gradient of u at the lane's points; buffers A, B, C.
+template <int LX, typename T, int W, typename TL>
+__device__ __forceinline__ void tile_grad(const TL &L, const Mat<LX, T> &D, const T (&u)[TL::H][TL::R], T *A, T *B, T *C,
+                                          T (&ur)[TL::H][TL::R], T (&us)[TL::H][TL::R], T (&ut)[TL::H][TL::R])
+{
+    constexpr int H = TL::H, R = TL::R;
+#pragma unroll
+    for (int h = 0; h < H; ++h) L.template put<TL::ST>(A + L.at_t(h), h, u[h]);
+#pragma unroll
+    for (int h = 0; h < H; ++h) D.mul(u[h], ut[h]);
+    __syncthreads();
+    tile_pass<TL::SR, LX, T, W>(L, D, A, B, [&](int h) { return L.at_r(h); });
+    __builtin_amdgcn_sched_barrier(0);
+    tile_pass<TL::SS, LX, T, W>(L, D, A, C, [&](int h) { return L.at_s(h); });
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+        L.template get<TL::ST>(B + L.at_t(h), ur[h]);
+        L.template get<TL::ST>(C + L.at_t(h), us[h]);
+    }
+}
+
+// w = D_r^T wr + D_s^T ws + D_t^T wt; wr and ws go through B and C in place.
+template <int LX, typename T, int W, typename TL>
+__device__ __forceinline__ void tile_div(const TL &L, const Mat<LX, T> &Dt, const T (&wr)[TL::H][TL::R],
+                                         const T (&ws)[TL::H][TL::R], const T (&wt)[TL::H][TL::R], T *B, T *C,
+                                         T (&w)[TL::H][TL::R])
+{
+    constexpr int H = TL::H, R = TL::R;
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+        L.template put<TL::ST>(B + L.at_t(h), h, wr[h]);
+        L.template put<TL::ST>(C + L.at_t(h), h, ws[h]);
+    }
+#pragma unroll
+    for (int h = 0; h < H; ++h) Dt.mul(wt[h], w[h]);
+    __syncthreads();
+    tile_pass<TL::SR, LX, T, W>(L, Dt, B, B, [&](int h) { return L.at_r(h); });
+    __builtin_amdgcn_sched_barrier(0);
+    tile_pass<TL::SS, LX, T, W>(L, Dt, C, C, [&](int h) { return L.at_s(h); });
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+        T a[R], b[R];
+        L.template get<TL::ST>(B + L.at_t(h), a);
+        L.template get<TL::ST>(C + L.at_t(h), b);
+#pragma unroll
+        for (int t = 0; t < R; ++t) w[h][t] += a[t] + b[t];
+    }
+}
+
+// Where the matrix-core kernels are used, waves per element W and waves per SIMD EU.
+//  * FP64, lx = 12: 12^2 pencils are nine whole tiles of three whole rows, three tiles to a
+//    wave, and a lane's 9 points of G are 108 of its 256 registers.  48^3-type elements at
+//    21 million points, us before -> now: one field Poisson 260 -> 252, Helmholtz 297 ->
+//    272, h1 field 321 -> 299, h1 and h2 fields 544 -> 335; three fields Helmholtz 714 ->
+//    524 (G was read from memory three times, at 6.8 TB/s), h1 and h2 fields 2600 -> 553.
+//  * FP32, lx = 16, three fields: sixteen whole tiles of four rows; 558 -> 262 us.
+// Elsewhere the pencil kernels are faster: the padding of a tile (lx = 10: 16 pencils by 12
+// rows for 14.3 by 10) costs up to half of the lanes (467 against 690 us for three fields
+// at lx = 10, 330 against 250 us for one), FP64 G at lx = 16 does not fit (670 us either
+// way), and in FP32 at lx = 12 the pencil kernels hold G too (243 against 266 us).
+template <int LX, typename T, int NF, bool CG>
+struct TileCfg {
+    static constexpr bool F64 = sizeof(T) == 8;
+    static constexpr bool USE = F64 ? LX == 12 : LX == 16 && NF == 3 && !CG;
+    static constexpr int W = F64 ? 3 : 8;
+    static constexpr int EU = 2;
+};
+
+// w = A_L u for NF fields (args AxArgs), or with CG the fused matvecs of k_cg_matvec
+// (CgMatvecArgs): p = dinv r + beta p stored, w = A_L p, partial sums of p.w; CG1: the
+// same of u = dinv r.
+template <int LX, typename T, int NF, int KIND, bool CG, bool CG1, typename Args>
+__device__ __forceinline__ void tile_body(const Args &A, const T *__restrict__ Dm)
+{
+    constexpr int W = TileCfg<LX, T, NF, CG>::W;
+    using TL = Tiles<LX, T, W>;
+    constexpr int H = TL::H, R = TL::R;
+    __shared__ T buf[3][TL::ESZ];
+    __shared__ double red[CG ? NF : 1][W];
+    if constexpr (CG) {
+        bool live = false;
+#pragma unroll
+        for (int f = 0; f < NF; ++f) live = live || !A.scal[f].stop;
+        if (!live) return;
+    }
+    const TL L;
+    const int64_t e0 = (int64_t)blockIdx.x * (LX * LX * LX);
+    T u[H][R];
+    if constexpr (!CG) L.template load<false>(A.u + e0, u);
+    T G[6][H][R];
+#pragma unroll
+    for (int q = 0; q < 6; ++q) L.template load<true>(A.G + q * A.n + e0, G[q]);
+    // h1 and h2 B at the lane's points: with several fields in LDS (each lane reads back
+    // its own values), since next to G they do not fit the registers
+    constexpr bool H1F = kind_h1f(KIND), MASS = kind_mass(KIND) != 0, PARK = NF > 1;
+    __shared__ T park[PARK && H1F + MASS ? H1F + MASS : 1][PARK ? H * R : 1][PARK && H1F + MASS ? 64 * W : 1];
+    T h1[H1F && !PARK ? H : 1][R], mb[MASS && !PARK ? H : 1][R];
+    if constexpr (H1F) {
+        T v[H][R];
+        L.template load<PARK>(A.h1 + e0, v);
+#pragma unroll
+        for (int h = 0; h < H; ++h)
+#pragma unroll
+            for (int t = 0; t < R; ++t) {
+                if constexpr (PARK) park[0][h * R + t][threadIdx.x] = v[h][t];
+                else h1[h][t] = v[h][t];
+            }
+    }
+    if constexpr (MASS) {
+        T v[H][R], m2[H][R];
+        L.template load<PARK>(A.B + e0, v);
+        if constexpr (kind_mass(KIND) == 2) L.template load<PARK>(A.h2 + e0, m2);
+#pragma unroll
+        for (int h = 0; h < H; ++h)
+#pragma unroll
+            for (int t = 0; t < R; ++t) {
+                const T m = v[h][t] * (kind_mass(KIND) == 2 ? m2[h][t] : A.h2s);
+                if constexpr (PARK) park[H1F][h * R + t][threadIdx.x] = m;
+                else mb[h][t] = m;
+            }
+    }
+#pragma unroll 1
+    for (int f = 0; f < NF; ++f) {
+        const int64_t fe = f * A.n + e0;
+        if constexpr (CG) {
+            if (L.c + 16 * L.g == 0) red[f][L.wave] = 0.0;
+            if (A.scal[f].stop) continue;  // uniform: every lane reads the same flag
+            T r[H][R], dv[H][R];
+            L.template load<true>(A.r + fe, r);
+            L.template load<NF == 1>(A.dinv + e0, dv);
+            if constexpr (CG1) {
+#pragma unroll
+                for (int h = 0; h < H; ++h)
+#pragma unroll
+                    for (int t = 0; t < R; ++t) u[h][t] = dv[h][t] * r[h][t];
+            } else {
+                const T beta = (T)A.scal[f].beta;
+                L.template load<true>(A.p + fe, u);
+#pragma unroll
+                for (int h = 0; h < H; ++h)
+#pragma unroll
+                    for (int t = 0; t < R; ++t) u[h][t] = fma(beta, u[h][t], dv[h][t] * r[h][t]);
+                L.template store<true>(A.p + fe, u);
+            }
+        }
+        T ur[H][R], us[H][R], ut[H][R], w[H][R];
+        Mat<LX, T> D;
+        D.load(fresh(Dm), false);
+        tile_grad<LX, T, W>(L, D, u, buf[0], buf[1], buf[2], ur, us, ut);
+#pragma unroll
+        for (int h = 0; h < H; ++h)
+#pragma unroll
+            for (int t = 0; t < R; ++t) {
+                T hv;
+                if constexpr (H1F && PARK) hv = park[0][h * R + t][threadIdx.x];
+                else if constexpr (H1F) hv = h1[h][t];
+                else hv = A.h1s;
+                const T r = ur[h][t], s = us[h][t], q = ut[h][t];
+                ur[h][t] = row_G(hv, G[0][h][t], r, G[3][h][t], s, G[4][h][t], q);
+                us[h][t] = row_G(hv, G[3][h][t], r, G[1][h][t], s, G[5][h][t], q);
+                ut[h][t] = row_G(hv, G[4][h][t], r, G[5][h][t], s, G[2][h][t], q);
+            }
+        Mat<LX, T> Dt;
+        Dt.load(fresh(Dm), true);
+        tile_div<LX, T, W>(L, Dt, ur, us, ut, buf[1], buf[2], w);
+        double dot = 0.0;
+        if constexpr (MASS || CG) {
+#pragma unroll
+            for (int h = 0; h < H; ++h) {
+                // (u again from A, where it lies until the next field is written)
+                T v[R];
+                L.template get<TL::ST>(buf[0] + L.at_t(h), v);
+#pragma unroll
+                for (int t = 0; t < R; ++t) {
+                    if constexpr (MASS && PARK) w[h][t] = fma(park[H1F][h * R + t][threadIdx.x], v[t], w[h][t]);
+                    else if constexpr (MASS) w[h][t] = fma(mb[h][t], v[t], w[h][t]);
+                    if constexpr (CG)
+                        if (L.own(h) && L.row(t)) dot += (double)v[t] * (double)w[h][t];
+                }
+            }
+        }
+        if constexpr (!CG)
+            if (f + 1 < NF) L.template load<false>(A.u + fe + A.n, u);
+        L.template store<false>(A.w + fe, w);
+        if constexpr (CG) {
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) dot += __shfl_xor(dot, off, 64);
+            if (L.c + 16 * L.g == 0) red[f][L.wave] = dot;
+        }
+    }
+    if constexpr (CG) {
+        // workgroup sums, the waves in order (a stopped field's slots are zero)
+        __syncthreads();
+        if (threadIdx.x < NF) {
+            double v = 0.0;
+#pragma unroll
+            for (int q = 0; q < W; ++q) v += red[threadIdx.x][q];
+            A.partial[(int64_t)threadIdx.x * gridDim.x + blockIdx.x] = v;
+        }
+    }
+}
+
+template <int LX, typename T, int NF, int KIND>
+__global__ __launch_bounds__((64 * TileCfg<LX, T, NF, false>::W)) __attribute__((amdgpu_waves_per_eu(
+    TileCfg<LX, T, NF, false>::EU))) void k_ax_helm_tile(AxArgs<T> A, const T *__restrict__ Dm)
+{
+    tile_body<LX, T, NF, KIND, false, false>(A, Dm);
+}
+
+template <int LX, typename T, int NF, int KIND, bool CG1>
+__global__ __launch_bounds__((64 * TileCfg<LX, T, NF, true>::W)) __attribute__((amdgpu_waves_per_eu(
+    TileCfg<LX, T, NF, true>::EU))) void k_cg_matvec_tile(CgMatvecArgs<T> A, const T *__restrict__ Dm)
+{
+    tile_body<LX, T, NF, KIND, true, CG1>(A, Dm);
 }
 
 // g = (D v)^T G (D u) per point, lean form: G (D u) is formed first (G read in
@@ -1216,13 +1611,54 @@ sem::DEo<LX, T> make_deo(const double *D)
     return m;
 }
 
-// Coefficient form of a lean launch (see LeanKind).
+// Coefficient form of a lean launch (see KINDS).
 template <typename T>
 int lean_kind(const T *h1, const T *h2, T h2s)
 {
-    if (h2) return sem::KGEN;
-    if (h2s == T(0)) return h1 ? sem::KGEN : sem::KPOISSON;
-    return h1 ? sem::KH1F : sem::KHELM;
+    return (h1 ? 1 : 0) + 2 * (h2 ? 2 : h2s != T(0) ? 1 : 0);
+}
+
+// f(integral_constant<int, kind>) for the coefficient form kind.
+template <typename F>
+void with_kind(int kind, F f)
+{
+    switch (kind) {
+    case 0: f(std::integral_constant<int, 0>()); break;
+    case 1: f(std::integral_constant<int, 1>()); break;
+    case 2: f(std::integral_constant<int, 2>()); break;
+    case 3: f(std::integral_constant<int, 3>()); break;
+    case 4: f(std::integral_constant<int, 4>()); break;
+    default: f(std::integral_constant<int, 5>()); break;
+    }
+}
+
+// D row-major of this lx and precision, behind the even-odd form in the device copy.
+template <typename T>
+const T *dense_d(const void *deo)
+{
+    return (const T *)((const char *)deo + sizeof(sem::DEo<SEM_LX, T>));
+}
+
+template <typename T, int NF>
+void launch_ax_nf(const sem::AxArgs<T> &A, const sem::DEo<SEM_LX, T> &Dm, unsigned grid, hipStream_t st)
+{
+    using S = sem::Shape<SEM_LX, T>;
+    using C = sem::TileCfg<SEM_LX, T, NF, false>;
+    if constexpr (C::USE) {
+        with_kind(lean_kind(A.h1, A.h2, A.h2s), [&](auto k) {
+            hipLaunchKernelGGL((sem::k_ax_helm_tile<SEM_LX, T, NF, decltype(k)::value>), dim3(grid), dim3(64 * C::W), 0,
+                               st, A, dense_d<T>(A.deo));
+        });
+    } else if constexpr (S::LEAN) {
+        with_kind(lean_kind(A.h1, A.h2, A.h2s), [&](auto k) {
+            hipLaunchKernelGGL((sem::k_ax_helm_lean<SEM_LX, T, NF, decltype(k)::value>), dim3(grid), dim3(S::NT), 0, st,
+                               A, Dm, (const sem::DEo<SEM_LX, T> *)A.deo);
+        });
+    } else {
+        const bool gen = A.h1 || A.h2 || A.h2s != T(0);
+        if (gen) hipLaunchKernelGGL((sem::k_ax_helm<SEM_LX, T, NF, true>), dim3(grid), dim3(S::NT), 0, st, A, Dm);
+        else hipLaunchKernelGGL((sem::k_ax_helm<SEM_LX, T, NF, false>), dim3(grid), dim3(S::NT), 0, st, A, Dm);
+    }
 }
 
 template <typename T>
@@ -1231,40 +1667,33 @@ hipError_t launch_ax(const sem::AxArgs<T> &A, const double *D, int nfields, hipS
     using S = sem::Shape<SEM_LX, T>;
     const unsigned grid = (unsigned)((A.nelv + S::EPB - 1) / S::EPB);
     if (grid == 0) return hipSuccess;
+    if (S::LEAN && !A.deo) return hipErrorInvalidValue;
     const auto Dm = make_deo<SEM_LX, T>(D);
-    if constexpr (S::LEAN) {
-        if (sizeof(T) == 8 && !A.deo) return hipErrorInvalidValue;
-        const int kind = lean_kind(A.h1, A.h2, A.h2s);
-#define SEM_LEAN_AX(NF_, K_)                                                                               \
-    hipLaunchKernelGGL((sem::k_ax_helm_lean<SEM_LX, T, NF_, K_>), dim3(grid), dim3(S::NT), 0, st, A, Dm, \
-                       (const sem::DEo<SEM_LX, T> *)A.deo)
-        if (nfields == 3) {
-            switch (kind) {
-            case sem::KPOISSON: SEM_LEAN_AX(3, sem::KPOISSON); break;
-            case sem::KHELM: SEM_LEAN_AX(3, sem::KHELM); break;
-            case sem::KH1F: SEM_LEAN_AX(3, sem::KH1F); break;
-            default: SEM_LEAN_AX(3, sem::KGEN); break;
-            }
-        } else {
-            switch (kind) {
-            case sem::KPOISSON: SEM_LEAN_AX(1, sem::KPOISSON); break;
-            case sem::KHELM: SEM_LEAN_AX(1, sem::KHELM); break;
-            case sem::KH1F: SEM_LEAN_AX(1, sem::KH1F); break;
-            default: SEM_LEAN_AX(1, sem::KGEN); break;
-            }
-        }
-#undef SEM_LEAN_AX
+    if (nfields == 3) launch_ax_nf<T, 3>(A, Dm, grid, st);
+    else launch_ax_nf<T, 1>(A, Dm, grid, st);
+    return hipGetLastError();
+}
+
+template <typename T, int NF, bool CG1>
+void launch_cg_nf(const sem::CgMatvecArgs<T> &A, const sem::DEo<SEM_LX, T> &Dm, unsigned grid, hipStream_t st)
+{
+    using S = sem::Shape<SEM_LX, T>;
+    using C = sem::TileCfg<SEM_LX, T, NF, true>;
+    if constexpr (C::USE) {
+        with_kind(lean_kind(A.h1, A.h2, A.h2s), [&](auto k) {
+            hipLaunchKernelGGL((sem::k_cg_matvec_tile<SEM_LX, T, NF, decltype(k)::value, CG1>), dim3(grid),
+                               dim3(64 * C::W), 0, st, A, dense_d<T>(A.deo));
+        });
+    } else if constexpr (S::LEAN) {
+        with_kind(lean_kind(A.h1, A.h2, A.h2s), [&](auto k) {
+            hipLaunchKernelGGL((sem::k_cg_matvec_lean<SEM_LX, T, NF, decltype(k)::value, CG1>), dim3(grid), dim3(S::NT),
+                               0, st, A, Dm, (const sem::DEo<SEM_LX, T> *)A.deo);
+        });
     } else {
         const bool gen = A.h1 || A.h2 || A.h2s != T(0);
-        if (nfields == 3) {
-            if (gen) hipLaunchKernelGGL((sem::k_ax_helm<SEM_LX, T, 3, true>), dim3(grid), dim3(S::NT), 0, st, A, Dm);
-            else hipLaunchKernelGGL((sem::k_ax_helm<SEM_LX, T, 3, false>), dim3(grid), dim3(S::NT), 0, st, A, Dm);
-        } else {
-            if (gen) hipLaunchKernelGGL((sem::k_ax_helm<SEM_LX, T, 1, true>), dim3(grid), dim3(S::NT), 0, st, A, Dm);
-            else hipLaunchKernelGGL((sem::k_ax_helm<SEM_LX, T, 1, false>), dim3(grid), dim3(S::NT), 0, st, A, Dm);
-        }
+        if (gen) hipLaunchKernelGGL((sem::k_cg_matvec<SEM_LX, T, NF, true, CG1>), dim3(grid), dim3(S::NT), 0, st, A, Dm);
+        else hipLaunchKernelGGL((sem::k_cg_matvec<SEM_LX, T, NF, false, CG1>), dim3(grid), dim3(S::NT), 0, st, A, Dm);
     }
-    return hipGetLastError();
 }
 
 template <typename T, bool CG1>
@@ -1273,39 +1702,10 @@ hipError_t launch_cg(const sem::CgMatvecArgs<T> &A, const double *D, int nfields
     using S = sem::Shape<SEM_LX, T>;
     const unsigned grid = (unsigned)((A.nelv + S::EPB - 1) / S::EPB);
     if (grid == 0) return hipSuccess;
+    if (S::LEAN && !A.deo) return hipErrorInvalidValue;
     const auto Dm = make_deo<SEM_LX, T>(D);
-    if constexpr (S::LEAN) {
-        if (sizeof(T) == 8 && !A.deo) return hipErrorInvalidValue;
-        const int kind = lean_kind(A.h1, A.h2, A.h2s);
-#define SEM_LEAN_CG(NF_, K_)                                                                               \
-    hipLaunchKernelGGL((sem::k_cg_matvec_lean<SEM_LX, T, NF_, K_, CG1>), dim3(grid), dim3(S::NT), 0, st, A, Dm, \
-                       (const sem::DEo<SEM_LX, T> *)A.deo)
-        if (nfields == 3) {
-            switch (kind) {
-            case sem::KPOISSON: SEM_LEAN_CG(3, sem::KPOISSON); break;
-            case sem::KHELM: SEM_LEAN_CG(3, sem::KHELM); break;
-            case sem::KH1F: SEM_LEAN_CG(3, sem::KH1F); break;
-            default: SEM_LEAN_CG(3, sem::KGEN); break;
-            }
-        } else {
-            switch (kind) {
-            case sem::KPOISSON: SEM_LEAN_CG(1, sem::KPOISSON); break;
-            case sem::KHELM: SEM_LEAN_CG(1, sem::KHELM); break;
-            case sem::KH1F: SEM_LEAN_CG(1, sem::KH1F); break;
-            default: SEM_LEAN_CG(1, sem::KGEN); break;
-            }
-        }
-#undef SEM_LEAN_CG
-    } else {
-        const bool gen = A.h1 || A.h2 || A.h2s != T(0);
-        if (nfields == 3) {
-            if (gen) hipLaunchKernelGGL((sem::k_cg_matvec<SEM_LX, T, 3, true, CG1>), dim3(grid), dim3(S::NT), 0, st, A, Dm);
-            else hipLaunchKernelGGL((sem::k_cg_matvec<SEM_LX, T, 3, false, CG1>), dim3(grid), dim3(S::NT), 0, st, A, Dm);
-        } else {
-            if (gen) hipLaunchKernelGGL((sem::k_cg_matvec<SEM_LX, T, 1, true, CG1>), dim3(grid), dim3(S::NT), 0, st, A, Dm);
-            else hipLaunchKernelGGL((sem::k_cg_matvec<SEM_LX, T, 1, false, CG1>), dim3(grid), dim3(S::NT), 0, st, A, Dm);
-        }
-    }
+    if (nfields == 3) launch_cg_nf<T, 3, CG1>(A, Dm, grid, st);
+    else launch_cg_nf<T, 1, CG1>(A, Dm, grid, st);
     return hipGetLastError();
 }
 
@@ -1392,6 +1792,10 @@ void SEM_PASTE(sem_deo_fill_lx, SEM_LX)(const double *D, void *out64, void *out3
     const auto m32 = make_deo<SEM_LX, float>(D);
     memcpy(out64, &m64, sizeof(m64));
     memcpy(out32, &m32, sizeof(m32));
+    const auto d64 = make_dmat<SEM_LX, double>(D);
+    const auto d32 = make_dmat<SEM_LX, float>(D);
+    memcpy((char *)out64 + sizeof(m64), &d64, sizeof(d64));
+    memcpy((char *)out32 + sizeof(m32), &d32, sizeof(d32));
 }
 // number of per-workgroup partials the CG matvec writes per field
 int64_t SEM_PASTE(sem_cg_nblocks_f64_lx, SEM_LX)(int64_t nelv)

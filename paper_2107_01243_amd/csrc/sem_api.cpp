@@ -460,7 +460,8 @@ static sem_status coef_alloc(sem_space Xh, sem_mesh msh, unsigned flags, sem_coe
     }
     {
         // the even-odd D of this lx in device memory (read by the kernels for lx >= 10)
-        constexpr size_t b64 = sizeof(DEo<SEM_LX_MAX, double>), b32 = sizeof(DEo<SEM_LX_MAX, float>);
+        constexpr size_t b64 = sizeof(DEo<SEM_LX_MAX, double>) + sizeof(DMat<SEM_LX_MAX, double>);
+        constexpr size_t b32 = sizeof(DEo<SEM_LX_MAX, float>) + sizeof(DMat<SEM_LX_MAX, float>);
         unsigned char h64[b64] = {}, h32[b32] = {};
         fns(c->lx).deo(Xh->D, h64, h32);
         hipError_t e = hipSuccess;

@@ -119,6 +119,60 @@ def test_ax_fp32_and_batched(nx, lx):
     P.coef.set_helmholtz(1.0, 0.0)
 
 
+@pytest.mark.parametrize("lx", [10, 11, 12, 14, 16])
+def test_ax_coefficient_forms_high_order(lx):
+    """The six coefficient forms (h1 scalar or field; no mass term, h2 scalar or field) at the
+    orders whose kernels fix them at compile time, one and three fields: FP64 <= 1e-12 and
+    three fields bit-identical to three single calls, FP32 <= 2e-6 (the bounds of the
+    operator tests above; contractions of at most 16 terms)."""
+    nx = 2
+    say(f"[ax forms] nx={nx} lx={lx}")
+    P, O = pair(nx, lx)
+    h1v = np.exp(0.5 * workloads.uniform(P.n, 5))
+    h2v = 3.0 + workloads.uniform(P.n, 6)
+    us = [workloads.uniform(P.n, s) for s in workloads.SEED_RHS_FIELDS]
+    U = np.concatenate(us)
+    for h1 in (0.7, h1v):
+        for h2 in (0.0, 7.0, h2v):
+            P.coef.set_helmholtz(*[to_dev(h) if isinstance(h, np.ndarray) else h for h in (h1, h2)])
+            O.set_coef(h1, h2)
+            W = host(P.ax(to_dev(U), nfields=3)).reshape(3, -1)
+            W32 = host(P.ax(to_dev(U, torch.float32), nfields=3)).reshape(3, -1)
+            for f in range(3):
+                ref = O.ax_local(us[f])
+                np.testing.assert_array_equal(W[f], host(P.ax(to_dev(us[f]))))
+                assert rel_inf(W[f], ref) <= 1e-12
+                assert rel_inf(W32[f], ref) <= 2e-6
+                assert rel_inf(host(P.ax(to_dev(us[f], torch.float32))), ref) <= 2e-6
+    P.coef.set_helmholtz(1.0, 0.0)
+    O.set_coef(1.0, 0.0)
+
+
+@pytest.mark.parametrize("nf,single_reduction", [(1, False), (1, True), (3, False), (3, True)])
+def test_pcg_matvec_forms_lx12(nf, single_reduction):
+    """The fused CG matvec at lx = 12 in every coefficient form: 20 fixed iterations against
+    the oracle's PCG.  The iterates of two exact recurrences that round differently: within
+    1e-11 after 20 steps (50 steps of the verification case agree to 1e-12)."""
+    nx, lx = 2, 12
+    say(f"[pcg forms] nx={nx} lx={lx} nf={nf} single_reduction={single_reduction}")
+    P, O = pair(nx, lx)
+    h1v = np.exp(0.5 * workloads.uniform(P.n, 5))
+    h2v = 300.0 + workloads.uniform(P.n, 6)
+    bl = [workloads.uniform(P.n, s) for s in workloads.SEED_RHS_FIELDS[:nf]]
+    b = P.assemble(to_dev(np.concatenate(bl)), nf)
+    for h1 in (0.7, h1v):
+        for h2 in (0.0, 70.0, h2v):
+            P.coef.set_helmholtz(*[to_dev(h) if isinstance(h, np.ndarray) else h for h in (h1, h2)])
+            O.set_coef(h1, h2)
+            x, _ = P.solve(b, nfields=nf, rtol=0.0, max_iter=20, single_reduction=single_reduction)
+            X = host(x).reshape(nf, -1)
+            for f in range(nf):
+                xo, _ = O.pcg(O.assemble_rhs(bl[f]), rtol=0.0, max_iter=20)
+                assert rel_inf(X[f], xo) <= 1e-11
+    P.coef.set_helmholtz(1.0, 0.0)
+    O.set_coef(1.0, 0.0)
+
+
 def test_ax_full_size_32cubed_lx8_sampled():
     """32^3 curved elements, lx = 8, in the benchmark's launch shape: sampled elements
     recomputed by the oracle from its own coordinates and geometry."""
