@@ -12,6 +12,56 @@ template <typename T>
 sem_status cg_iterate(sem_coef c, Work &W, sem_gs g, int nf, T *x, T *r, T *p, T *w, const T *dinv, int max_iter,
                       int check_every, double *hist, int hist_len, hipStream_t st);
 
+// Whether the CG update gathers w itself (k_cg_update_gather) or a gather-scatter launch
+// assembles w before it.  Gathering saves a launch and w's second trip; it costs an index
+// per point and dependent loads, the more the larger the share of points with copies (0.70
+// at lx = 6, 0.58 at 8, 0.42 at 12).  Measured, us per iteration of one field, gathering
+// against assembling: FP64 lx = 6 at 13.8K points 16.8 / 19.8, lx = 8 at 0.26M 18.8 / 23.9,
+// 0.88M 35.4 / 41.1, 2.1M 63.9 / 69.0, 7.1M 186 / 185 and 16.8M 435 / 432 (three fields 440 /
+// 446 and 1076 / 1118), lx = 12 at 13.8M 345 / 364 (three 901 / 980); lx = 6 at 1.7M
+// 65.7 / 65.6, at 13.8M 386 / 369, lx = 4 at 0.88M with three fields 87.5 / 82.3, lx = 2 at
+// 1M 52.8 / 48.5, lx = 3 at 0.22M 22.0 / 24.9.  FP32 lx = 8 at 0.88M 25.2 / 25.7 (three
+// 50.2 / 55.2), at 2.1M 44.4 / 44.7 (three 93.5 / 88.0).
+template <typename T>
+static bool cg_gathers(sem_coef c, int nf)
+{
+    if (c->n <= (c->lx >= 5 ? 1 << 20 : 1 << 18)) return true;
+    if (sizeof(T) == 4) return false;
+    return c->lx >= 9 || (c->lx == 8 && (nf == 3 || c->n <= (1 << 22)));
+}
+
+template <typename T>
+static int64_t matvec_blocks(sem_coef c)
+{
+    return sizeof(T) == 8 ? fns(c->lx).nblk64(c->nelv) : fns(c->lx).nblk32(c->nelv);
+}
+
+// The gathering form of U where it is used.  Up to sem_gather_fold_max() partial sums of
+// the matvec it also computes the step length; its own sums then go past the matvec's.
+template <typename T>
+static void gather_in_update(CgUpdateArgs<T> &U, sem_coef c, Work &W, sem_gs g)
+{
+    const int32_t *pmap = g->d_pmap.load(std::memory_order_acquire);
+    if (!pmap || !cg_gathers<T>(c, U.nfields)) return;
+    U.pmap = pmap;
+    U.grp = (const int4 *)g->d_grp;
+    if (matvec_blocks<T>(c) > sem_gather_fold_max()) return;
+    U.mpart = W.partial;
+    U.nm = matvec_blocks<T>(c);
+    U.partial = W.partial + 3 * W.nb;
+}
+
+// Between matvec and update: the gather-scatter of w with the step length in it, the step
+// length alone (the update gathers) or nothing (the update does both).
+template <typename T>
+static sem_status assemble_or_alpha(const CgUpdateArgs<T> &U, sem_coef c, Work &W, sem_gs g, hipStream_t st)
+{
+    if (!U.pmap)
+        return launch_gs<T>(const_cast<T *>(U.w), U.nfields, g, W.scal, sizeof(T) == 8 ? W.job64 : W.job32, st);
+    if (!U.nm) HIP_TRY(sem_launch_cg_alpha(W.partial, matvec_blocks<T>(c), W.scal, U.nfields, st));
+    return SEM_OK;
+}
+
 // Jacobi-PCG in precision T on nf fields.  x is the iterate (zeroed unless use_x0),
 // b the assembled, masked right-hand side.  Per-field results land in W.h_scal.
 template <typename T>
@@ -61,8 +111,6 @@ sem_status cg_iterate(sem_coef c, Work &W, sem_gs g, int nf, T *x, T *r, T *p, T
 {
     const int64_t n = c->n;
     const bool f64 = sizeof(T) == 8;
-    const unsigned ug = sem_update_grid(n, f64 ? 0 : 1);
-    const AlphaJob *job = f64 ? W.job64 : W.job32;
     CgMatvecArgs<T> M;
     M.p = p;
     M.w = w;
@@ -80,7 +128,9 @@ sem_status cg_iterate(sem_coef c, Work &W, sem_gs g, int nf, T *x, T *r, T *p, T
     M.partial = W.partial;
     M.deo = sizeof(T) == 8 ? c->deo64 : c->deo32;
     CgUpdateArgs<T> U{x, r, p, w, dinv, g->d_owner, W.scal, W.partial, n, nf};
-    CgFinishArgs F{W.partial, (int64_t)ug, W.scal, hist, hist_len, nf};
+    gather_in_update(U, c, W, g);
+    const unsigned ug = sem_update_grid(n, f64 ? 0 : 1, U.pmap != nullptr);
+    CgFinishArgs F{U.partial, (int64_t)ug, W.scal, hist, hist_len, nf};
     if (check_every < 1) check_every = 1;
     const int64_t max_batches = (int64_t)(max_iter + check_every - 1) / check_every + 2;
     // first poll right after initialisation (b = 0 or an exact initial guess)
@@ -96,7 +146,7 @@ sem_status cg_iterate(sem_coef c, Work &W, sem_gs g, int nf, T *x, T *r, T *p, T
         for (int it = 0; it < todo; ++it) {
             if constexpr (sizeof(T) == 8) HIP_TRY(fns(c->lx).cg64(&M, c->Xh->D, nf, st));
             else HIP_TRY(fns(c->lx).cg32(&M, c->Xh->D, nf, st));
-            SEM_TRY(launch_gs<T>(w, nf, g, W.scal, job, st));
+            SEM_TRY(assemble_or_alpha(U, c, W, g, st));
             if constexpr (sizeof(T) == 8) HIP_TRY(sem_launch_cg_update_f64(&U, ug, st));
             else HIP_TRY(sem_launch_cg_update_f32(&U, ug, st));
             HIP_TRY(sem_launch_cg_finish(&F, st));
@@ -392,8 +442,9 @@ static sem_status pcg_mixed_reliable(double *x, const double *b, int nf, sem_coe
     M.partial = W.partial;
     M.deo = c->deo32;
     CgUpdateArgs<float> U{W.y32, W.r32, W.p32, W.w32, c->dinv32, g->d_owner, W.scal, W.partial, n, nf};
-    const unsigned ug = sem_update_grid(n, 1);
-    CgFinishArgs F{W.partial, (int64_t)ug, W.scal, nullptr, 0, nf};
+    gather_in_update(U, c, W, g);
+    const unsigned ug = sem_update_grid(n, 1, U.pmap != nullptr);
+    CgFinishArgs F{U.partial, (int64_t)ug, W.scal, nullptr, 0, nf};
     const int check_every = std::max(1, P->check_every);
     const int64_t max_polls = (int64_t)P->max_iter + 64 * 64;  // every poll runs >= 1 iteration or ends a segment
     // Launches queued between polls after a segment has ended do no work but still
@@ -435,7 +486,7 @@ static sem_status pcg_mixed_reliable(double *x, const double *b, int nf, sem_coe
         }
         for (int it = 0; it < todo; ++it) {
             HIP_TRY(fns(c->lx).cg32(&M, c->Xh->D, nf, st));
-            SEM_TRY(launch_gs<float>(W.w32, nf, g, W.scal, W.job32, st));
+            SEM_TRY(assemble_or_alpha(U, c, W, g, st));
             HIP_TRY(sem_launch_cg_update_f32(&U, ug, st));
             HIP_TRY(sem_launch_cg_finish(&F, st));
         }
@@ -606,6 +657,8 @@ sem_status sem_pcg_solve(double *x, const double *b, int nfields, sem_coef coef,
     if ((size_t)coef->n * nfields == 0) return SEM_OK;
     hipStream_t st = S(stream);
     SEM_TRY(gs_upload(gs));
+    if (P.mixed ? cg_gathers<float>(coef, nfields) : P.variant == 0 && cg_gathers<double>(coef, nfields))
+        SEM_TRY(gs_gather_lists(gs));
     SEM_TRY(ensure_dinv(coef, gs, st));
     SEM_TRY(ensure_work(coef, nfields, P.mixed != 0));
     // every stopping test below works on the target SEM_RTOL_MARGIN * rtol

@@ -13,6 +13,8 @@
 #include <cstdio>
 #include <cstring>
 #include <string>
+#include <atomic>
+#include <mutex>
 #include <vector>
 
 #include "sem.h"
@@ -56,7 +58,8 @@ SEM_LX_LIST(SEM_DECL)
 
 extern "C" {
 unsigned sem_vec_grid(int64_t n);
-unsigned sem_update_grid(int64_t n, int f32);
+unsigned sem_update_grid(int64_t n, int f32, int gather);
+int64_t sem_gather_fold_max();
 hipError_t sem_launch_gs_f64(const GsArgs<double> *, hipStream_t);
 hipError_t sem_launch_gs_f32(const GsArgs<float> *, hipStream_t);
 hipError_t sem_launch_mask(void *, int, const int32_t *, int64_t, int64_t, int, hipStream_t);
@@ -70,6 +73,7 @@ hipError_t sem_launch_cg_init_f32(const CgInitArgs<float> *, unsigned, hipStream
 hipError_t sem_launch_cg_start(const CgFinishArgs *, hipStream_t);
 hipError_t sem_launch_cg_update_f64(const CgUpdateArgs<double> *, unsigned, hipStream_t);
 hipError_t sem_launch_cg_update_f32(const CgUpdateArgs<float> *, unsigned, hipStream_t);
+hipError_t sem_launch_cg_alpha(const double *, int64_t, CgScalars *, int, hipStream_t);
 hipError_t sem_launch_cg_finish(const CgFinishArgs *, hipStream_t);
 hipError_t sem_launch_cg1_update(const Cg1UpdateArgs *, hipStream_t);
 hipError_t sem_launch_dots(const DotArgs *, unsigned, hipStream_t);
@@ -200,6 +204,12 @@ struct sem_gs_s {
     int32_t *d_blk_idx = nullptr;
     uint8_t *d_owner = nullptr;
     uint32_t *d_ent_word = nullptr;  // entry-parallel list, one packed word per entry
+    // per-point lists of the update that gathers (see CgUpdateArgs), built by the first
+    // solve that uses them; d_pmap is published last and stays nullptr without them
+    std::mutex lists_mu;
+    bool lists_tried = false;
+    std::atomic<int32_t *> d_pmap{nullptr};
+    int32_t *d_grp = nullptr;
     bool entries = false;  // entry-parallel execution (groups > 64 copies via d_blk_*)
     int64_t npairs() const { return (int64_t)m.pairs.size() / 2; }
     int64_t nblocks() const { return (int64_t)m.blk_ptr.size() - 1; }
@@ -328,6 +338,7 @@ namespace __attribute__((visibility("hidden"))) semi {
 sem_status check_device(int want);
 sem_status mesh_upload(sem_mesh m);
 sem_status gs_upload(sem_gs g);
+sem_status gs_gather_lists(sem_gs g);
 sem_status check_coef(sem_coef c, sem_mesh msh, sem_space Xh);
 
 template <typename T>

@@ -80,10 +80,20 @@ struct CgUpdateArgs {
     const T *w;
     const T *dinv;
     const uint8_t *owner;
-    const CgScalars *scal;
+    CgScalars *scal;
     double *partial;  // [2][field][grid]
     int64_t n;
     int nfields;
+    // nullptr: w is assembled.  Otherwise w holds element contributions and every point
+    // sums its copies itself: per point -1 (one copy), the other copy (two copies), or
+    // -2 - (32 a + 2 (c - 1) + o) for c copies listed in ascending order from grp[a]
+    // (padded to whole int4), o set on the copy that owns the point
+    const int32_t *pmap = nullptr;
+    const int4 *grp = nullptr;
+    // with pmap: the matvec's partial sums of p.w, nm of them per field, for the step
+    // length (nm = 0: it is in scal)
+    const double *mpart = nullptr;
+    int64_t nm = 0;
 };
 
 struct CgFinishArgs {

@@ -55,8 +55,9 @@ constexpr int GEPL = SEM_GS_EPL;  // 64-entry segments per wave of the entry-par
 // the bytes of an FP64 one, so it takes more points to amortise the workgroup's
 // reduction epilogue (and it halves the partials the finish kernel sums).
 template <typename T> struct UpdChunk;
-template <> struct UpdChunk<double> { static constexpr int UV = SEM_UPD64; };
-template <> struct UpdChunk<float> { static constexpr int UV = SEM_UPD32; };
+// GV: the same for the update that gathers, which holds four more values per point.
+template <> struct UpdChunk<double> { static constexpr int UV = SEM_UPD64, GV = 2; };
+template <> struct UpdChunk<float> { static constexpr int UV = SEM_UPD32, GV = 4; };
 
 // Sum `nblk` partials in a fixed order inside one workgroup of NTH lanes: lane t
 // accumulates entries t, t+NTH, ... into four interleaved accumulators (loads in
@@ -127,6 +128,19 @@ __device__ inline void cg1_fold(CgScalars &s, double gamma, double delta, double
     s.primed = 1;
 }
 
+// Step length of one field, alpha = rz / (p, A p); stops it on a breakdown.
+__device__ inline void cg_set_alpha(CgScalars &sc, double pw)
+{
+    if (sc.stop) return;
+    if (!(pw > 0.0) || !isfinite(pw) || !isfinite(sc.rz)) {
+        sc.stop = 1;
+        sc.status = 2;
+        sc.alpha = 0.0;
+    } else {
+        sc.alpha = sc.rz / pw;
+    }
+}
+
 // Fold of the CG scalars for every field by workgroup 0 of a gather-scatter launch
 // (the matvec whose partials it reads ended before this launch began).
 template <int NTH>
@@ -135,18 +149,7 @@ __device__ void fold_job(const AlphaJob &J, int nfields, double *sh)
     for (int f = 0; f < nfields; ++f) {
         if (J.mode == 0) {
             const double pw = block_sum_fixed<NTH>(J.partial + f * J.nblk, J.nblk, sh);
-            if (threadIdx.x == 0) {
-                CgScalars &sc = J.scal[f];
-                if (!sc.stop) {
-                    if (!(pw > 0.0) || !isfinite(pw) || !isfinite(sc.rz)) {
-                        sc.stop = 1;
-                        sc.status = 2;
-                        sc.alpha = 0.0;
-                    } else {
-                        sc.alpha = sc.rz / pw;
-                    }
-                }
-            }
+            if (threadIdx.x == 0) cg_set_alpha(J.scal[f], pw);
         } else {
             const double d = block_sum_fixed<NTH>(J.partial + f * J.nblk, J.nblk, sh);
             CgScalars &sc = J.scal[f];
@@ -1104,6 +1107,184 @@ __global__ __launch_bounds__(VT) void k_cg_update(CgUpdateArgs<T> A)
     }
 }
 
+// The same update with the gather-scatter of w inside it (A.pmap): every point sums the
+// copies of its own value in the gather-scatter's order (the results are the same to the
+// bit), so w is read once and never written back.  With NM > 0 every workgroup also sums the
+// matvec's partials for the step length, NM a lane, while its operands are on their way: the
+// iteration is then matvec, this, finish.  Small problems are bound by the latency of each
+// launch's chain of loads, and this form takes out the gather-scatter's chain (6^3 points in
+// 64 elements: 20.3 -> 16.8 us per iteration; 8^3 in 512: 25 -> 18.8).  On large ones it is
+// bound by that chain too, scalars and index -> list -> copies -> stores, not by bandwidth
+// (8^3 in 32768 elements: 5.1 TB/s in 207 us, against 145 + 66 us for update and
+// gather-scatter).  All loads of one level are issued together for the GV points of a lane;
+// lists are read four entries at a time, since a fifth copy is rare.  Measured slower:
+// one wave per chunk with the next index prefetched, GV = 1 and 4, index loads non-temporal,
+// runs of 1, 64 and 256 chunks, one contiguous range per XCD.
+constexpr int GATHER_NM = 1024;  // most partial sums of the matvec that it folds
+template <typename T, int NM>
+__global__ __launch_bounds__(VT) void k_cg_update_gather(CgUpdateArgs<T> A, unsigned nblk, int run)
+{
+    constexpr int UV = UpdChunk<T>::GV;
+    __shared__ double sh[2][VT / 64], sp[NM > 0 ? VT : 1];
+    const int f = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // XCD x takes runs of 1 << run chunks, so that most copies of a point are in its own L2
+    const unsigned i = blockIdx.x / 8, lb = (((i >> run) * 8 + blockIdx.x % 8) << run) + (i & ((1u << run) - 1));
+    if (lb >= nblk) return;
+    const int64_t off = f * A.n, t0 = (int64_t)lb * (UV * VT) + threadIdx.x;
+    int32_t m[UV];
+#pragma unroll
+    for (int u = 0; u < UV; ++u) m[u] = A.pmap[min(t0 + (int64_t)u * VT, A.n - 1)];
+    double pw = 0.0;
+    if constexpr (NM > 0) {
+        const double *mp = A.mpart + f * A.nm;
+        double a[NM];
+#pragma unroll
+        for (int q = 0; q < NM; ++q) {
+            const int64_t k = threadIdx.x + q * VT;
+            a[q] = k < A.nm ? mp[k] : 0.0;
+        }
+        // (the order of block_sum_fixed<VT>, as in the gather-scatter's fold)
+        const bool full = threadIdx.x + 3 * VT < A.nm;
+        pw = full ? (a[0] + a[1]) + (a[2] + a[3]) : (a[0] + a[1]) + a[2];
+        sp[threadIdx.x] = pw;
+    }
+    CgScalars &sc = A.scal[f];
+    double rz = 0.0, rr = 0.0;
+    if (!sc.stop) {
+        T *x = A.x + off, *r = A.r + off;
+        const T *p = A.p + off, *w = A.w + off;
+        T di[UV], xv[UV], pv[UV], rv[UV], v[UV][4];
+        int4 g[UV];
+#pragma unroll
+        for (int u = 0; u < UV; ++u) {
+            const int64_t t = min(t0 + (int64_t)u * VT, A.n - 1);
+            v[u][0] = w[t];
+            di[u] = __builtin_nontemporal_load(A.dinv + t);
+            xv[u] = __builtin_nontemporal_load(x + t);
+            pv[u] = __builtin_nontemporal_load(p + t);
+            rv[u] = __builtin_nontemporal_load(r + t);
+        }
+#pragma unroll
+        for (int u = 0; u < UV; ++u) {
+            if (m[u] < -1) g[u] = A.grp[(-2 - m[u]) >> 5];
+        }
+#pragma unroll
+        for (int u = 0; u < UV; ++u) {
+            v[u][1] = T(0);
+            if (m[u] >= 0) v[u][1] = w[m[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < UV; ++u) {
+            v[u][2] = v[u][3] = T(0);
+            if (m[u] < -1) {
+                v[u][0] = w[g[u].x];
+                v[u][1] = w[g[u].y];
+                v[u][2] = w[g[u].z];
+                v[u][3] = w[g[u].w];
+            }
+        }
+        T alpha;
+        bool ok = true;
+        if constexpr (NM > 0) {
+            __syncthreads();
+            pw = (sp[lane] + sp[lane + 128]) + (sp[lane + 64] + sp[lane + 192]);
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) pw += __shfl_xor(pw, o, 64);
+            const double rz0 = sc.rz;
+            // every workgroup finds the same; on a breakdown none updates anything, and the
+            // stop flag that the first one sets makes no difference to one that reads it
+            ok = pw > 0.0 && isfinite(pw) && isfinite(rz0);
+            alpha = ok ? (T)(rz0 / pw) : T(0);
+            if (!ok && lb == 0 && threadIdx.x == 0) cg_set_alpha(sc, pw);
+        } else {
+            alpha = (T)sc.alpha;
+        }
+        if (ok) {
+#pragma unroll
+            for (int u = 0; u < UV; ++u) {
+                const int64_t t = t0 + (int64_t)u * VT;
+                if (t >= A.n) break;
+                T wi = v[u][0];
+                bool own = true;
+                if (m[u] >= 0) {
+                    wi = (T(0) + wi) + v[u][1];  // (a sum of two is the same in either order)
+                    own = t < m[u];
+                } else if (m[u] < -1) {
+                    const int32_t o = -2 - m[u], cnt = ((o >> 1) & 15) + 1;
+                    own = o & 1;
+                    wi = ((T(0) + wi) + v[u][1]) + v[u][2];
+                    if (cnt > 3) wi += v[u][3];
+                    for (int c = 4; c < cnt; c += 4) {
+                        const int4 h = A.grp[(o >> 5) + c / 4];
+                        const T a = w[h.x], b = w[h.y], d = w[h.z], e = w[h.w];
+                        wi += a;
+                        if (c + 1 < cnt) wi += b;
+                        if (c + 2 < cnt) wi += d;
+                        if (c + 3 < cnt) wi += e;
+                    }
+                }
+                __builtin_nontemporal_store(fma(alpha, pv[u], xv[u]), x + t);
+                T ri = rv[u];
+                if (di[u] != T(0)) {
+                    ri = fma(-alpha, wi, ri);
+                    __builtin_nontemporal_store(ri, r + t);
+                }
+                if (own) {
+                    rz += (double)ri * (double)(di[u] * ri);
+                    rr += (double)ri * (double)ri;
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        rz += __shfl_xor(rz, o, 64);
+        rr += __shfl_xor(rr, o, 64);
+    }
+    if (lane == 0) {
+        sh[0][wave] = rz;
+        sh[1][wave] = rr;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        double a = 0.0;
+#pragma unroll
+        for (int q = 0; q < VT / 64; ++q) a += sh[threadIdx.x][q];
+        A.partial[((int64_t)threadIdx.x * A.nfields + f) * nblk + lb] = a;
+    }
+}
+
+// Step lengths from the matvec's partial sums where they are too many for every workgroup
+// of the update to add them up again, one workgroup per field: the additions of
+// block_sum_fixed<VT> in the same order, with a lane for each of its four accumulators.
+__global__ __launch_bounds__(RT) void k_cg_alpha(const double *part, int64_t nblk, CgScalars *scal)
+{
+    static_assert(RT == 4 * VT, "a lane per accumulator");
+    __shared__ double sh[RT];
+    const int tid = threadIdx.x, f = blockIdx.x, t = tid & (VT - 1);
+    part += f * nblk;
+    double a = 0.0;
+    int64_t q = t;  // the first of this step's four entries
+#pragma unroll 4
+    for (; q + 3 * VT < nblk; q += RT) a += part[q + (tid - t)];
+    if (tid < VT)
+        for (; q < nblk; q += VT) a += part[q];
+    sh[tid] = a;
+    __syncthreads();
+    if (tid < 64) {
+        double s[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const double *v = sh + tid + 64 * k;
+            s[k] = (v[0] + v[VT]) + (v[2 * VT] + v[3 * VT]);
+        }
+        double pw = (s[0] + s[2]) + (s[1] + s[3]);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) pw += __shfl_xor(pw, o, 64);
+        if (tid == 0) cg_set_alpha(scal[f], pw);
+    }
+}
+
 // Single-reduction CG update (Chronopoulos-Gear): with u = dinv r recomputed on the
 // fly, p = u + beta p, s = w + beta s (s = A p carried as a vector), x += alpha p,
 // r -= alpha s on non-Dirichlet points, and the partial sums of the new (r, dinv r)
@@ -1525,12 +1706,14 @@ extern "C" {
 
 unsigned sem_vec_grid(int64_t n) { return stream_grid(n); }
 // workgroups of the CG update in precision f32 ? FP32 : FP64
-unsigned sem_update_grid(int64_t n, int f32)
+unsigned sem_update_grid(int64_t n, int f32, int gather)
 {
-    const int64_t c = (int64_t)VT * (f32 ? UpdChunk<float>::UV : UpdChunk<double>::UV);
+    const int64_t c = (int64_t)VT * (f32 ? (gather ? UpdChunk<float>::GV : UpdChunk<float>::UV)
+                                         : (gather ? UpdChunk<double>::GV : UpdChunk<double>::UV));
     const int64_t g = (n + c - 1) / c;
     return (unsigned)(g < 1 ? 1 : g);
 }
+int64_t sem_gather_fold_max() { return GATHER_NM; }
 
 }  // extern "C"
 
@@ -1565,6 +1748,17 @@ static unsigned arn_grid(int64_t n)
     const int64_t c = arn_chunk(n);
     const int64_t g = (n + c - 1) / c;
     return (unsigned)(g < 1 ? 1 : g);
+}
+template <typename T>
+static hipError_t launch_gather(const CgUpdateArgs<T> *A, unsigned grid, hipStream_t st)
+{
+    if (A->nm > GATHER_NM || (A->nm > 0 && !A->mpart)) return hipErrorInvalidValue;
+    const int run = grid > 4096 ? 4 : 2;
+    const unsigned per = 8u << run;
+    const dim3 g((grid + per - 1) / per * per, A->nfields);
+    if (A->nm == 0) hipLaunchKernelGGL((k_cg_update_gather<T, 0>), g, dim3(VT), 0, st, *A, grid, run);
+    else hipLaunchKernelGGL((k_cg_update_gather<T, GATHER_NM / VT>), g, dim3(VT), 0, st, *A, grid, run);
+    return hipGetLastError();
 }
 template <int MV>
 static void launch_dcgs(const DcgsArgs &A, int pass, hipStream_t st)
@@ -1645,13 +1839,26 @@ hipError_t sem_launch_cg_start(const CgFinishArgs *A, hipStream_t st)
 hipError_t sem_launch_cg_update_f64(const CgUpdateArgs<double> *A, unsigned grid, hipStream_t st)
 {
     if ((int64_t)grid * VT * UpdChunk<double>::UV < A->n) return hipErrorInvalidValue;
+    if (A->pmap) {
+launch_gather<double>(A, grid, st);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_cg_update<double>, dim3(grid, A->nfields), dim3(VT), 0, st, *A);
     return hipGetLastError();
 }
 hipError_t sem_launch_cg_update_f32(const CgUpdateArgs<float> *A, unsigned grid, hipStream_t st)
 {
     if ((int64_t)grid * VT * UpdChunk<float>::UV < A->n) return hipErrorInvalidValue;
+    if (A->pmap) {
+launch_gather<float>(A, grid, st);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_cg_update<float>, dim3(grid, A->nfields), dim3(VT), 0, st, *A);
+    return hipGetLastError();
+}
+hipError_t sem_launch_cg_alpha(const double *partial, int64_t nblk, CgScalars *scal, int nfields, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_cg_alpha, dim3(nfields), dim3(RT), 0, st, partial, nblk, scal);
     return hipGetLastError();
 }
 hipError_t sem_launch_cg1_update(const Cg1UpdateArgs *A, hipStream_t st)

@@ -1063,3 +1063,59 @@ def test_side_stream_matches_default_stream():
     side.synchronize()
     for name, r, o in zip(("ax+gs", "pcg", "mixed", "gmres"), ref, out):
         assert torch.equal(r, o), name
+
+
+def _glued(P, seed, copies):
+    """The box of P with its points glued at random in groups of the given sizes."""
+    rng = np.random.default_rng(seed)
+    glb = np.arange(P.n, dtype=np.int64)
+    left, q = rng.permutation(P.n), 0
+    while q + sum(copies) <= (3 * P.n) // 4:
+        for c in copies:
+            glb[left[q:q + c]] = left[q]
+            q += c
+    msh = sem.Mesh(P.msh.nelv, P.lx, glb)
+    return msh, sem.GS(msh), sem.Coef(P.Xh, msh, xyz=P.xyz, fp32=True)
+
+
+@pytest.mark.parametrize("nx,lx,nf,copies", [
+    (1, 8, 1, None),             # no point has a copy
+    (3, 5, 1, None),             # 3375 points: a ragged last chunk, groups of 2, 4 and 8
+    (2, 12, 3, None),
+    (7, 7, 1, None),
+    (16, 3, 3, None),
+    (11, 9, 1, None),            # the step length in its own launch
+    (20, 5, 1, None),            # the largest of the small range
+    (4, 6, 1, (2, 3, 4, 5, 8, 9)),
+    (4, 6, 3, (2, 13, 16)),      # the most copies the lists take
+    (4, 6, 1, (2, 3, 17)),       # one more: the gather-scatter runs
+])
+def test_pcg_gathering_update_is_the_assembled_one(nx, lx, nf, copies):
+    """The FP64 solve whose update gathers w sums every point's copies in the order of the
+    gather-scatter: solution, iteration count and residual equal, to the bit, those of the
+    solve that assembles w first (the allocation-free one on a handle without the lists);
+    after the lists exist it uses them too, with the same result.  The FP32 iteration, where
+    it gathers, must meet the tolerance on the FP64 residual."""
+    say(f"[gathering update] nx={nx} lx={lx} nf={nf} copies={copies}")
+    P = sem.BoxProblem.build(nx, lx, 0.05, fp32=True)
+    if copies is not None:
+        msh, gs, coef = _glued(P, 7, copies)
+        P = sem.BoxProblem(P.Xh, msh, gs, coef, P.xyz, None, None, nx, lx)
+    P.coef.set_helmholtz(1.0, 1.0)
+    f = to_dev(workloads.uniform(P.n * nf, workloads.SEED_RHS))
+    b = P.assemble(f, nf)
+    args = (P.coef, P.msh, P.Xh, P.gs)
+    kw = dict(nfields=nf, rtol=1e-10, check_every=7)
+    xa, xg, xn = (torch.full_like(b, float("nan")) for _ in range(3))
+    ia = sem.pcg_solve_noalloc(xa, b, *args, **kw)
+    ig = sem.pcg_solve(xg, b, *args, **kw)
+    im = sem.pcg_solve_noalloc(xn, b, *args, **kw)
+    assert torch.equal(xa, xg) and torch.equal(xa, xn)
+    assert ia == ig == im
+    xm = torch.zeros_like(b)
+    info = sem.pcg_solve(xm, b, *args, nfields=nf, rtol=1e-10, mixed="reliable")
+    assert all(i["converged"] and i["true_rel_res"] <= 1e-10 for i in info)
+    r = b - P.apply(xm, nf)
+    for k in range(nf):
+        rk, bk = r[k * P.n:(k + 1) * P.n], b[k * P.n:(k + 1) * P.n]
+        assert float((rk * rk / P.mult).sum().sqrt() / (bk * bk / P.mult).sum().sqrt()) <= 1.05e-10
