@@ -97,7 +97,7 @@ sem_status gs_upload(sem_gs g)
         for (size_t q = 0; q < word.size(); ++q)
             word[q] = m.ent_idx[q] < 0 ? 0xffffffffu
                                        : ((uint32_t)m.ent_idx[q] | ((m.ent_meta[q] & 0xffu) == 0 ? 0x80000000u : 0u));
-        SEM_TRY(dalloc(&g->d_ent_word, word.size()));
+        SEM_TRY(dalloc(&g->d_ent_word, word.size() + 4));  // a list is read four entries at a time
         if (!word.empty())
             HIP_TRY(hipMemcpy(g->d_ent_word, word.data(), word.size() * 4, hipMemcpyHostToDevice));
     }
@@ -124,49 +124,28 @@ sem_status gs_upload(sem_gs g)
     return SEM_OK;
 }
 
-// Per-point lists of the CG update that gathers (see CgUpdateArgs).  Not built (the solver
-// then runs the gather-scatter) when a point has more than 16 copies or the list offsets
-// would not fit their word, or when memory is short.  On a mesh of 2.1M points this takes
-// about 9 ms, once per handle.
-sem_status gs_gather_lists(sem_gs g)
+// Per-point map of the kernels that gather (see CgUpdateArgs).  Not built (the solver then
+// runs the gather-scatter) when a point has more than 16 copies, when an entry's position
+// does not fit its word, or when memory is short.
+sem_status gs_gather_map(sem_gs g, hipStream_t st)
 {
     const auto &m = g->m;
-    std::lock_guard<std::mutex> lock(g->lists_mu);
-    if (g->lists_tried || m.n == 0) return SEM_OK;
-    g->lists_tried = true;
-    int64_t most = 2, lists = 0;
-    for (size_t b = 0; b + 1 < m.blk_ptr.size(); ++b) {
-        most = std::max(most, m.blk_ptr[b + 1] - m.blk_ptr[b]);
-        lists += (m.blk_ptr[b + 1] - m.blk_ptr[b] + 3) / 4;
+    std::lock_guard<std::mutex> lock(g->pmap_mu);
+    if (g->pmap_tried || m.n == 0) return SEM_OK;
+    const int64_t nent = (int64_t)m.ent_idx.size();
+    int32_t *pmap = nullptr;
+    if (g->entries && m.big_idx.empty() && m.max_group <= 16 && nent < (1 << 26) - 64 &&
+        hipMalloc((void **)&pmap, m.n * sizeof(int32_t)) == hipSuccess) {
+        hipError_t e = sem_launch_gather_map(g->d_ent_word, nent, g->d_owner, pmap, m.n, st);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);  // (other streams may use it next)
+        if (e != hipSuccess) {
+            dfree(pmap);
+            HIP_TRY(e);
+        }
+        g->d_pmap.store(pmap, std::memory_order_release);
     }
-    if (most > 16 || lists >= (1 << 26)) return SEM_OK;
-    std::vector<int32_t> pmap(m.n, -1), grp;
-    for (size_t q = 0; q + 1 < m.pairs.size(); q += 2) {
-        pmap[m.pairs[q]] = m.pairs[q + 1];
-        pmap[m.pairs[q + 1]] = m.pairs[q];
-    }
-    grp.reserve(4 * lists);
-    for (size_t b = 0; b + 1 < m.blk_ptr.size(); ++b) {
-        const int32_t *idx = &m.blk_idx[m.blk_ptr[b]];
-        const int32_t at = (int32_t)(grp.size() / 4), cnt = (int32_t)(m.blk_ptr[b + 1] - m.blk_ptr[b]);
-        for (int32_t q = 0; q < (cnt + 3) / 4 * 4; ++q) grp.push_back(idx[q < cnt ? q : 0]);
-        for (int32_t q = 0; q < cnt; ++q) pmap[idx[q]] = -2 - (32 * at + 2 * (cnt - 1) + (m.owner[idx[q]] ? 1 : 0));
-    }
-    int32_t *dp = nullptr, *dg = nullptr;
-    if (dalloc(&dp, pmap.size()) != SEM_OK || dalloc(&dg, std::max<size_t>(grp.size(), 4)) != SEM_OK) {
-        dfree(dp);  // no room for them: the solver runs without
-        (void)hipGetLastError();
-        return SEM_OK;
-    }
-    hipError_t e = hipMemcpy(dp, pmap.data(), pmap.size() * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess && !grp.empty()) e = hipMemcpy(dg, grp.data(), grp.size() * 4, hipMemcpyHostToDevice);
-    if (e != hipSuccess) {
-        dfree(dp);
-        dfree(dg);
-        return fail(SEM_ERR_HIP, "upload of the gather lists failed: %s", hipGetErrorString(e));
-    }
-    g->d_grp = dg;
-    g->d_pmap.store(dp, std::memory_order_release);
+    (void)hipGetLastError();  // of a failed allocation
+    g->pmap_tried = true;
     return SEM_OK;
 }
 
@@ -457,7 +436,6 @@ void sem_gs_destroy(sem_gs gs)
     dfree(gs->d_owner);
     dfree(gs->d_ent_word);
     if (int32_t *dp = gs->d_pmap.exchange(nullptr)) dfree(dp);
-    dfree(gs->d_grp);
     delete gs;
 }
 

@@ -44,7 +44,7 @@ static void gather_in_update(CgUpdateArgs<T> &U, sem_coef c, Work &W, sem_gs g)
     const int32_t *pmap = g->d_pmap.load(std::memory_order_acquire);
     if (!pmap || !cg_gathers<T>(c, U.nfields)) return;
     U.pmap = pmap;
-    U.grp = (const int4 *)g->d_grp;
+    U.ent_word = g->d_ent_word;
     if (matvec_blocks<T>(c) > sem_gather_fold_max()) return;
     U.mpart = W.partial;
     U.nm = matvec_blocks<T>(c);
@@ -399,20 +399,16 @@ static sem_status pcg_mixed_reliable(double *x, const double *b, int nf, sem_coe
     Work &W = c->ws;
     const int64_t n = c->n;
     const int64_t nn = n * nf;
-    const unsigned vg = sem_vec_grid(n);
-    // FP64 residual of the initial guess
+    // whether A x is assembled by a gather-scatter or where it is read
+    const int32_t *pmap = cg_gathers<double>(c, nf) ? g->d_pmap.load(std::memory_order_acquire) : nullptr;
+    double bb[3] = {0.0, 0.0, 0.0};  // for x = 0 the first residual's
     if (P->use_x0) {
         SEM_TRY(launch_ax<double>(c, W.w, x, nf, st));
-        SEM_TRY(launch_gs<double>(W.w, nf, g, nullptr, nullptr, st));
-        HIP_TRY(sem_launch_residual(W.r, b, W.w, c->dinv, n, nf, st));
-    } else {
-        HIP_TRY(sem_launch_fill_f64(x, 0.0, nn, st));
-        HIP_TRY(hipMemcpyAsync(W.r, b, sizeof(double) * nn, hipMemcpyDeviceToDevice, st));
-    }
-    double bb[3];
-    {
+        if (!pmap) SEM_TRY(launch_gs<double>(W.w, nf, g, nullptr, nullptr, st));
         const double *a[1] = {b};
         SEM_TRY(dots(c, g, nf, 1, a, a, bb, st));
+    } else {
+        HIP_TRY(sem_launch_fill_f64(x, 0.0, nn, st));
     }
     const double delta = (P->delta > 0.0 && P->delta < 1.0) ? P->delta : 0.5;
     for (int f = 0; f < nf; ++f) {
@@ -423,10 +419,12 @@ static sem_status pcg_mixed_reliable(double *x, const double *b, int nf, sem_coe
     }
     HIP_TRY(hipMemcpyAsync(W.rel, W.h_rel, sizeof(RelState) * nf, hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(W.scal, W.h_scal, sizeof(CgScalars) * nf, hipMemcpyHostToDevice, st));
-    RelRestartArgs RA{W.r, W.r32, W.y32, W.p32, c->dinv32, g->d_owner, W.rel, W.partial, n, nf};
-    CgFinishArgs RF{W.partial, (int64_t)vg, W.scal, nullptr, 0, nf};
-    HIP_TRY(sem_launch_rel_restart(&RA, vg, st));
-    HIP_TRY(sem_launch_rel_resume(&RF, W.rel, 1, st));
+    RelRestartArgs RA{b, P->use_x0 ? W.w : nullptr, W.r32, W.y32, W.p32, c->dinv, g->d_owner, W.rel, W.partial, n, nf,
+                      pmap, g->d_ent_word};
+    CgFinishArgs RF{W.partial, (int64_t)sem_rel_grid(n), W.scal, nullptr, 0, nf};
+    HIP_TRY(sem_launch_rel_restart(&RA, st));
+    HIP_TRY(sem_launch_rel_resume(&RF, W.rel, 1, P->use_x0 ? 0 : 1, st));
+    RA.w = W.w;
     RA.p32 = nullptr;  // later segments keep the search direction
 
     CgMatvecArgs<float> M;
@@ -472,10 +470,9 @@ static sem_status pcg_mixed_reliable(double *x, const double *b, int nf, sem_coe
             HIP_TRY(hipMemcpyAsync(W.done, W.h_done, sizeof(int) * nf, hipMemcpyHostToDevice, st));
             HIP_TRY(sem_launch_add_f32(x, W.y32, W.done, n, nf, st));
             SEM_TRY(launch_ax<double>(c, W.w, x, nf, st));
-            SEM_TRY(launch_gs<double>(W.w, nf, g, nullptr, nullptr, st));
-            HIP_TRY(sem_launch_residual(W.r, b, W.w, c->dinv, n, nf, st));
-            HIP_TRY(sem_launch_rel_restart(&RA, vg, st));
-            HIP_TRY(sem_launch_rel_resume(&RF, W.rel, 0, st));
+            if (!pmap) SEM_TRY(launch_gs<double>(W.w, nf, g, nullptr, nullptr, st));
+            HIP_TRY(sem_launch_rel_restart(&RA, st));
+            HIP_TRY(sem_launch_rel_resume(&RF, W.rel, 0, 0, st));
             continue;
         }
         int todo = check_every;
@@ -657,8 +654,8 @@ sem_status sem_pcg_solve(double *x, const double *b, int nfields, sem_coef coef,
     if ((size_t)coef->n * nfields == 0) return SEM_OK;
     hipStream_t st = S(stream);
     SEM_TRY(gs_upload(gs));
-    if (P.mixed ? cg_gathers<float>(coef, nfields) : P.variant == 0 && cg_gathers<double>(coef, nfields))
-        SEM_TRY(gs_gather_lists(gs));
+    if (P.variant == 0 && (cg_gathers<float>(coef, nfields) || cg_gathers<double>(coef, nfields)))
+        SEM_TRY(gs_gather_map(gs, st));
     SEM_TRY(ensure_dinv(coef, gs, st));
     SEM_TRY(ensure_work(coef, nfields, P.mixed != 0));
     // every stopping test below works on the target SEM_RTOL_MARGIN * rtol

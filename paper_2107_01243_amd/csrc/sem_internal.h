@@ -73,15 +73,17 @@ hipError_t sem_launch_cg_init_f32(const CgInitArgs<float> *, unsigned, hipStream
 hipError_t sem_launch_cg_start(const CgFinishArgs *, hipStream_t);
 hipError_t sem_launch_cg_update_f64(const CgUpdateArgs<double> *, unsigned, hipStream_t);
 hipError_t sem_launch_cg_update_f32(const CgUpdateArgs<float> *, unsigned, hipStream_t);
+hipError_t sem_launch_gather_map(const uint32_t *, int64_t, const uint8_t *, int32_t *, int64_t, hipStream_t);
 hipError_t sem_launch_cg_alpha(const double *, int64_t, CgScalars *, int, hipStream_t);
 hipError_t sem_launch_cg_finish(const CgFinishArgs *, hipStream_t);
 hipError_t sem_launch_cg1_update(const Cg1UpdateArgs *, hipStream_t);
 hipError_t sem_launch_dots(const DotArgs *, unsigned, hipStream_t);
-hipError_t sem_launch_rel_restart(const RelRestartArgs *, unsigned, hipStream_t);
+unsigned sem_rel_grid(int64_t n);
+hipError_t sem_launch_rel_restart(const RelRestartArgs *, hipStream_t);
 hipError_t sem_launch_cg_replace_f64(const double *, const double *, const uint8_t *, const int *, double *, int64_t,
                                      int, hipStream_t);
 hipError_t sem_launch_cg_resume(const CgFinishArgs *, const int *, hipStream_t);
-hipError_t sem_launch_rel_resume(const CgFinishArgs *, RelState *, int, hipStream_t);
+hipError_t sem_launch_rel_resume(const CgFinishArgs *, RelState *, int, int, hipStream_t);
 hipError_t sem_launch_add_f32(double *, const float *, const int *, int64_t, int, hipStream_t);
 hipError_t sem_launch_dots_finish(const double *, int64_t, int, double *, hipStream_t);
 hipError_t sem_launch_comb(const CombArgs *, hipStream_t);
@@ -204,12 +206,11 @@ struct sem_gs_s {
     int32_t *d_blk_idx = nullptr;
     uint8_t *d_owner = nullptr;
     uint32_t *d_ent_word = nullptr;  // entry-parallel list, one packed word per entry
-    // per-point lists of the update that gathers (see CgUpdateArgs), built by the first
-    // solve that uses them; d_pmap is published last and stays nullptr without them
-    std::mutex lists_mu;
-    bool lists_tried = false;
+    // per-point map of the kernels that gather (see CgUpdateArgs), built by the first solve
+    // that uses it; stays nullptr where it cannot be built
+    std::mutex pmap_mu;
+    bool pmap_tried = false;
     std::atomic<int32_t *> d_pmap{nullptr};
-    int32_t *d_grp = nullptr;
     bool entries = false;  // entry-parallel execution (groups > 64 copies via d_blk_*)
     int64_t npairs() const { return (int64_t)m.pairs.size() / 2; }
     int64_t nblocks() const { return (int64_t)m.blk_ptr.size() - 1; }
@@ -338,7 +339,7 @@ namespace __attribute__((visibility("hidden"))) semi {
 sem_status check_device(int want);
 sem_status mesh_upload(sem_mesh m);
 sem_status gs_upload(sem_gs g);
-sem_status gs_gather_lists(sem_gs g);
+sem_status gs_gather_map(sem_gs g, hipStream_t st);
 sem_status check_coef(sem_coef c, sem_mesh msh, sem_space Xh);
 
 template <typename T>

@@ -86,10 +86,10 @@ struct CgUpdateArgs {
     int nfields;
     // nullptr: w is assembled.  Otherwise w holds element contributions and every point
     // sums its copies itself: per point -1 (one copy), the other copy (two copies), or
-    // -2 - (32 a + 2 (c - 1) + o) for c copies listed in ascending order from grp[a]
-    // (padded to whole int4), o set on the copy that owns the point
+    // -2 - (32 a + 2 (c - 1) + o) for c copies whose entries start at ent_word[a] (ascending
+    // local index), o set on the copy that owns the point
     const int32_t *pmap = nullptr;
-    const int4 *grp = nullptr;
+    const uint32_t *ent_word = nullptr;
     // with pmap: the matvec's partial sums of p.w, nm of them per field, for the step
     // length (nm = 0: it is in scal)
     const double *mpart = nullptr;
@@ -119,16 +119,20 @@ struct RelState {
 // r32 = (float) r64, x32 = 0 (optionally p32 = 0), partials of (r32, dinv r32),
 // (r32, r32) and (r64, r64) over owned points, for fields not done.
 struct RelRestartArgs {
-    const double *r64;
+    const double *b;
+    const double *w;   // A x, or nullptr for x = 0
     float *r32;
     float *x32;
     float *p32;        // zeroed when non-null (first segment)
-    const float *dinv32;
+    const double *dinv;
     const uint8_t *owner;
     const RelState *rel;
     double *partial;   // [3][field][grid]
     int64_t n;
     int nfields;
+    // as in CgUpdateArgs: nullptr, or w holds element contributions
+    const int32_t *pmap;
+    const uint32_t *ent_word;
 };
 
 struct DotArgs {

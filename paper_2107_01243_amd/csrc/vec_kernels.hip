@@ -270,6 +270,25 @@ __global__ __launch_bounds__(VT) void k_gs_entries(GsArgs<T> A)
     }
 }
 
+// pmap of the updates that gather (see CgUpdateArgs) from the entry list, on a pmap of -1.
+__global__ __launch_bounds__(VT) void k_gather_map(const uint32_t *ent_word, int64_t nent, const uint8_t *owner,
+                                                   int32_t *pmap)
+{
+    const int64_t t = (int64_t)blockIdx.x * VT + threadIdx.x;  // (64 | VT: a wave is a segment)
+    const int lane = threadIdx.x & 63;
+    const uint32_t wd = t < nent ? ent_word[t] : 0xffffffffu;
+    const bool pad = wd == 0xffffffffu;
+    const uint64_t M = __ballot(pad || (wd >> 31) != 0), upto = lane == 63 ? ~0ull : ((2ull << lane) - 1);
+    if (pad) return;
+    const int lead = 63 - __clzll((long long)(M & upto));
+    const uint64_t above = M & ~upto;
+    const int cnt = (above ? __ffsll((long long)above) - 1 : 64) - lead;
+    const int64_t first = t - lane + lead;
+    const int32_t e = (int32_t)(wd & 0x7fffffffu);
+    if (cnt == 2) pmap[e] = (int32_t)(ent_word[2 * first + 1 - t] & 0x7fffffffu);
+    else pmap[e] = (int32_t)(-2 - (32 * first + 2 * (cnt - 1) + (owner[e] ? 1 : 0)));
+}
+
 // ------------------------------------------------------------------ basis combinations
 // Linear combination of up to PB basis vectors (coefficients by value).
 __global__ __launch_bounds__(VT) void k_comb(CombArgs A)
@@ -1117,9 +1136,11 @@ __global__ __launch_bounds__(VT) void k_cg_update(CgUpdateArgs<T> A)
 // bound by that chain too, scalars and index -> list -> copies -> stores, not by bandwidth
 // (8^3 in 32768 elements: 5.1 TB/s in 207 us, against 145 + 66 us for update and
 // gather-scatter).  All loads of one level are issued together for the GV points of a lane;
-// lists are read four entries at a time, since a fifth copy is rare.  Measured slower:
+// lists are the gather-scatter's own entries, read four at a time: a fifth copy is rare.  Measured slower:
 // one wave per chunk with the next index prefetched, GV = 1 and 4, index loads non-temporal,
 // runs of 1, 64 and 256 chunks, one contiguous range per XCD.
+// four consecutive entries of the gather-scatter's list, at any of them
+struct __attribute__((packed, aligned(4))) List4 { uint32_t e[4]; };
 constexpr int GATHER_NM = 1024;  // most partial sums of the matvec that it folds
 template <typename T, int NM>
 __global__ __launch_bounds__(VT) void k_cg_update_gather(CgUpdateArgs<T> A, unsigned nblk, int run)
@@ -1154,7 +1175,7 @@ __global__ __launch_bounds__(VT) void k_cg_update_gather(CgUpdateArgs<T> A, unsi
         T *x = A.x + off, *r = A.r + off;
         const T *p = A.p + off, *w = A.w + off;
         T di[UV], xv[UV], pv[UV], rv[UV], v[UV][4];
-        int4 g[UV];
+        List4 g[UV];
 #pragma unroll
         for (int u = 0; u < UV; ++u) {
             const int64_t t = min(t0 + (int64_t)u * VT, A.n - 1);
@@ -1166,7 +1187,7 @@ __global__ __launch_bounds__(VT) void k_cg_update_gather(CgUpdateArgs<T> A, unsi
         }
 #pragma unroll
         for (int u = 0; u < UV; ++u) {
-            if (m[u] < -1) g[u] = A.grp[(-2 - m[u]) >> 5];
+            if (m[u] < -1) g[u] = *(const List4 *)(A.ent_word + ((-2 - m[u]) >> 5));
         }
 #pragma unroll
         for (int u = 0; u < UV; ++u) {
@@ -1177,10 +1198,11 @@ __global__ __launch_bounds__(VT) void k_cg_update_gather(CgUpdateArgs<T> A, unsi
         for (int u = 0; u < UV; ++u) {
             v[u][2] = v[u][3] = T(0);
             if (m[u] < -1) {
-                v[u][0] = w[g[u].x];
-                v[u][1] = w[g[u].y];
-                v[u][2] = w[g[u].z];
-                v[u][3] = w[g[u].w];
+                const int32_t o = -2 - m[u];
+                v[u][0] = w[g[u].e[0] & 0x7fffffffu];
+                v[u][1] = w[g[u].e[1] & 0x7fffffffu];
+                v[u][2] = w[g[u].e[2] & 0x7fffffffu];
+                if ((o & 31) >= 6) v[u][3] = w[g[u].e[3] & 0x7fffffffu];
             }
         }
         T alpha;
@@ -1215,12 +1237,13 @@ __global__ __launch_bounds__(VT) void k_cg_update_gather(CgUpdateArgs<T> A, unsi
                     wi = ((T(0) + wi) + v[u][1]) + v[u][2];
                     if (cnt > 3) wi += v[u][3];
                     for (int c = 4; c < cnt; c += 4) {
-                        const int4 h = A.grp[(o >> 5) + c / 4];
-                        const T a = w[h.x], b = w[h.y], d = w[h.z], e = w[h.w];
-                        wi += a;
-                        if (c + 1 < cnt) wi += b;
-                        if (c + 2 < cnt) wi += d;
-                        if (c + 3 < cnt) wi += e;
+                        const List4 h = *(const List4 *)(A.ent_word + (o >> 5) + c);
+                        T a[4];
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) a[k] = w[c + k < cnt ? h.e[k] & 0x7fffffffu : (uint32_t)t];
+#pragma unroll
+                        for (int k = 0; k < 4; ++k)
+                            if (c + k < cnt) wi += a[k];
                     }
                 }
                 __builtin_nontemporal_store(fma(alpha, pv[u], xv[u]), x + t);
@@ -1391,130 +1414,199 @@ __device__ void block_sum2_fixed(const double *pa, const double *pb, int64_t nbl
     __syncthreads();
 }
 
+// One workgroup per field; a stopped field's sums are not read.
 __global__ __launch_bounds__(RT) void k_cg_finish(CgFinishArgs A)
 {
     __shared__ double sh[2 * (RT / 64)];
-    for (int f = 0; f < A.nfields; ++f) {
-        double rz, rr;
-        block_sum2_fixed<RT>(A.partial + (0 * A.nfields + f) * A.nblk, A.partial + (1 * A.nfields + f) * A.nblk,
-                             A.nblk, sh, rz, rr);
-        if (threadIdx.x == 0) {
-            CgScalars &s = A.scal[f];
-            if (!s.stop) {
-                s.iter += 1;
-                s.rr = rr;
-                const double rel = sqrt(rr / s.bb);
-                if (A.hist && s.iter < A.hist_len) A.hist[(int64_t)f * A.hist_len + s.iter] = rel;
-                s.beta = rz / s.rz;
-                s.rz = rz;
-                if (s.rtol > 0.0 && rel <= s.rtol) s.stop = 1;
-                else if (!isfinite(rr) || !isfinite(rz)) { s.stop = 1; s.status = 2; }
-                else if (rz == 0.0) s.stop = 1;
-                else if (s.iter >= s.max_iter) { s.stop = 1; s.status = (s.rtol > 0.0) ? 1 : 0; }
-            }
-        }
+    const int f = blockIdx.x;
+    CgScalars &s = A.scal[f];
+    if (s.stop) return;
+    double rz, rr;
+    block_sum2_fixed<RT>(A.partial + (0 * A.nfields + f) * A.nblk, A.partial + (1 * A.nfields + f) * A.nblk, A.nblk, sh,
+                         rz, rr);
+    if (threadIdx.x == 0) {
+        s.iter += 1;
+        s.rr = rr;
+        const double rel = sqrt(rr / s.bb);
+        if (A.hist && s.iter < A.hist_len) A.hist[(int64_t)f * A.hist_len + s.iter] = rel;
+        s.beta = rz / s.rz;
+        s.rz = rz;
+        if (s.rtol > 0.0 && rel <= s.rtol) s.stop = 1;
+        else if (!isfinite(rr) || !isfinite(rz)) { s.stop = 1; s.status = 2; }
+        else if (rz == 0.0) s.stop = 1;
+        else if (s.iter >= s.max_iter) { s.stop = 1; s.status = (s.rtol > 0.0) ? 1 : 0; }
     }
 }
 
 // ------------------------------------------------------------------ reliable-update mixed CG
-// Restart data for a new FP32 segment from the FP64 true residual r64.
-__global__ __launch_bounds__(VT) void k_rel_restart(RelRestartArgs A)
+// Restart data for a new FP32 segment: the FP64 true residual b - w (0 on Dirichlet points;
+// b itself for x = 0), rounded to FP32, the segment's zero iterate, and the partial sums of
+// (r32, dinv r32), (r32, r32) and (r, r).  One pass: the FP64 residual is not stored, and w
+// is gathered here (pmap) instead of by a gather-scatter before.  A workgroup takes REL_R
+// rounds of VT points and all fields, which share the point's index, dinv and owner, so that
+// few partial sums are left.  Three fields of 13.8M points at lx = 12: 281 us (4.1 TB/s of
+// what it must move: the chain index -> entries -> copies bounds it, as in the gathering
+// update), against 143 for the gather-scatter, 209 for the residual and 231 for the restart
+// as passes of their own.  Chunks of 512 to 2048 points, runs of 4 or 16, the indices of all
+// rounds loaded first: 275 to 306 us.
+constexpr int REL_R = 8, REL_RUN = 4;
+template <int NF, bool GA>
+__global__ __launch_bounds__(VT) void k_rel_restart(RelRestartArgs A, unsigned nblk)
 {
-    __shared__ double sh[3][VT];
-    const int f = blockIdx.y;
-    double rz = 0.0, rr = 0.0, r64 = 0.0;
-    if (!A.rel[f].done) {
-        const double *rs = A.r64 + f * A.n;
-        float *r = A.r32 + f * A.n;
-        float *x = A.x32 + f * A.n;
-        float *p = A.p32 ? A.p32 + f * A.n : nullptr;
-        for (int64_t t = (int64_t)blockIdx.x * CHUNK + threadIdx.x, t_end = min(A.n, (int64_t)(blockIdx.x + 1) * CHUNK);
-             t < t_end; t += VT) {
-            const double rd = rs[t];
-            const float ri = (float)rd;
-            r[t] = ri;
-            x[t] = 0.0f;
-            if (p) p[t] = 0.0f;
-            if (A.owner[t]) {
-                rz += (double)ri * (double)(A.dinv32[t] * ri);
-                rr += (double)ri * (double)ri;
-                r64 += rd * rd;
+    __shared__ double sh[3 * NF][VT / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // XCD x takes runs of REL_RUN chunks, so that most copies of a point are in its own L2
+    const unsigned i = blockIdx.x / 8, lb = (i / REL_RUN * 8 + blockIdx.x % 8) * REL_RUN + i % REL_RUN;
+    if (lb >= nblk) return;
+    const int64_t n = A.n, t0 = (int64_t)lb * (REL_R * VT) + threadIdx.x;
+    bool live[NF];
+    double acc[3 * NF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+        live[f] = !A.rel[f].done;
+        acc[3 * f] = acc[3 * f + 1] = acc[3 * f + 2] = 0.0;
+    }
+#pragma unroll 1
+    for (int q = 0; q < REL_R; ++q) {
+        const int64_t t = t0 + q * VT;
+        if (t >= n) break;
+        const double di = __builtin_nontemporal_load(A.dinv + t);
+        int32_t m = -1;
+        if constexpr (GA) m = A.pmap[t];
+        double rd[NF], wv[NF][4];
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            rd[f] = live[f] ? __builtin_nontemporal_load(A.b + f * n + t) : 0.0;
+            wv[f][0] = live[f] && A.w ? A.w[f * n + t] : 0.0;
+        }
+        bool own = true;
+        if constexpr (GA) {
+            if (m >= 0) {
+                own = t < m;
+#pragma unroll
+                for (int f = 0; f < NF; ++f)
+                    if (live[f] && A.w) wv[f][0] = (0.0 + wv[f][0]) + A.w[f * n + m];
+            } else if (m < -1) {
+                const int32_t o = -2 - m, cnt = ((o >> 1) & 15) + 1;
+                own = o & 1;
+                double s[NF];
+#pragma unroll
+                for (int f = 0; f < NF; ++f) s[f] = 0.0;
+                for (int c = 0; c < cnt && A.w; c += 4) {
+                    const List4 h = *(const List4 *)(A.ent_word + (o >> 5) + c);
+                    int64_t e[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) e[k] = c + k < cnt ? (int64_t)(h.e[k] & 0x7fffffffu) : t;
+#pragma unroll
+                    for (int f = 0; f < NF; ++f) {
+                        if (!live[f]) continue;
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) wv[f][k] = A.w[f * n + e[k]];
+                    }
+#pragma unroll
+                    for (int f = 0; f < NF; ++f) {
+                        if (!live[f]) continue;
+#pragma unroll
+                        for (int k = 0; k < 4; ++k)
+                            if (c + k < cnt) s[f] += wv[f][k];
+                    }
+                }
+#pragma unroll
+                for (int f = 0; f < NF; ++f) wv[f][0] = s[f];
+            }
+        } else {
+            own = A.owner[t] != 0;
+        }
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            if (!live[f]) continue;
+            const double r = A.w ? (di != 0.0 ? rd[f] - wv[f][0] : 0.0) : rd[f];
+            const float ri = (float)r;
+            __builtin_nontemporal_store(ri, A.r32 + f * n + t);
+            __builtin_nontemporal_store(0.0f, A.x32 + f * n + t);
+            if (A.p32) __builtin_nontemporal_store(0.0f, A.p32 + f * n + t);
+            if (own) {
+                acc[3 * f] += (double)ri * (double)((float)di * ri);
+                acc[3 * f + 1] += (double)ri * (double)ri;
+                acc[3 * f + 2] += r * r;
             }
         }
     }
-    sh[0][threadIdx.x] = rz;
-    sh[1][threadIdx.x] = rr;
-    sh[2][threadIdx.x] = r64;
-    __syncthreads();
-    for (int s = VT / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s)
-            for (int q = 0; q < 3; ++q) sh[q][threadIdx.x] += sh[q][threadIdx.x + s];
-        __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 3 * NF; ++k) {
+        const double v = wave_sum(acc[k]);
+        if (lane == 0) sh[k][wave] = v;
     }
-    if (threadIdx.x == 0)
-        for (int q = 0; q < 3; ++q) A.partial[((int64_t)q * A.nfields + f) * gridDim.x + blockIdx.x] = sh[q][0];
+    __syncthreads();
+    if (threadIdx.x < 3 * NF) {
+        double a = 0.0;
+#pragma unroll
+        for (int q = 0; q < VT / 64; ++q) a += sh[threadIdx.x][q];
+        const int f = threadIdx.x / 3, k = threadIdx.x % 3;
+        A.partial[((int64_t)k * NF + f) * nblk + lb] = a;
+    }
 }
 
-// Start (first = 1) or resume an FP32 segment after a residual replacement.  The
+// One workgroup per field: start (first = 1; with zero_x0 the residual is b) or resume an FP32 segment after a residual replacement.  The
 // FP64 true residual decides convergence.  Resuming keeps the search direction p:
 // beta is rescaled to the replaced residual, beta = (r_new, z_new) / (r_old, z_old).
 // The segment stops once its residual has dropped by max(delta, half of the
 // reduction still needed), at most 0.5.
-__global__ __launch_bounds__(RT) void k_rel_resume(CgFinishArgs F, RelState *rel, int first)
+__global__ __launch_bounds__(RT) void k_rel_resume(CgFinishArgs F, RelState *rel, int first, int zero_x0)
 {
     __shared__ double sh[RT];
-    for (int f = 0; f < F.nfields; ++f) {
-        const double rz = block_sum_fixed<RT>(F.partial + (0 * F.nfields + f) * F.nblk, F.nblk, sh);
-        const double rr = block_sum_fixed<RT>(F.partial + (1 * F.nfields + f) * F.nblk, F.nblk, sh);
-        const double r64 = block_sum_fixed<RT>(F.partial + (2 * F.nfields + f) * F.nblk, F.nblk, sh);
-        if (threadIdx.x == 0) {
-            RelState &R = rel[f];
-            CgScalars &s = F.scal[f];
-            if (R.done) continue;
-            R.rr64 = r64;
-            R.outer += first ? 0 : 1;
-            // the segment that just ended failed (breakdown) or used up the iterations
-            if (!first && s.status != 0) {
-                R.done = 1;
-                s.stop = 1;
-                continue;
-            }
-            const double rel64 = R.bb64 > 0.0 ? sqrt(r64 / R.bb64) : 0.0;
-            if (!isfinite(r64) || !isfinite(rz)) {
-                R.done = 1;
-                s.stop = 1;
-                s.status = 2;
-                continue;
-            }
-            if (R.bb64 == 0.0 || rel64 <= R.tol) {
-                R.done = 1;
-                s.stop = 1;
-                s.status = 0;
-                continue;
-            }
-            if (first) {
-                s.beta = 0.0;
-                s.iter = 0;
-            } else {
-                s.beta = (s.rz != 0.0) ? s.beta * (rz / s.rz) : 0.0;
-                // a fast-converging system reaches delta within a few iterations:
-                // ask for more reduction per segment so replacements stay rare
-                if (s.iter - R.last_iter < 8) R.delta = fmax(R.delta * R.delta, 1e-3);
-            }
-            R.last_iter = s.iter;
-            s.rz = rz;
-            s.rr = rr;
-            s.bb = rr;  // the segment's reference residual
-            const double need = R.tol / rel64;
-            s.rtol = fmin(0.5, fmax(R.delta, 0.5 * need));
-            s.alpha = 0.0;
+    const int f = blockIdx.x;
+    const double rz = block_sum_fixed<RT>(F.partial + (0 * F.nfields + f) * F.nblk, F.nblk, sh);
+    const double rr = block_sum_fixed<RT>(F.partial + (1 * F.nfields + f) * F.nblk, F.nblk, sh);
+    const double r64 = block_sum_fixed<RT>(F.partial + (2 * F.nfields + f) * F.nblk, F.nblk, sh);
+    if (threadIdx.x == 0) {
+        RelState &R = rel[f];
+        CgScalars &s = F.scal[f];
+        if (R.done) return;
+        if (zero_x0) R.bb64 = r64;
+        R.rr64 = r64;
+        R.outer += first ? 0 : 1;
+        // the segment that just ended failed (breakdown) or used up the iterations
+        if (!first && s.status != 0) {
+            R.done = 1;
+            s.stop = 1;
+            return;
+        }
+        const double rel64 = R.bb64 > 0.0 ? sqrt(r64 / R.bb64) : 0.0;
+        if (!isfinite(r64) || !isfinite(rz)) {
+            R.done = 1;
+            s.stop = 1;
+            s.status = 2;
+            return;
+        }
+        if (R.bb64 == 0.0 || rel64 <= R.tol) {
+            R.done = 1;
+            s.stop = 1;
             s.status = 0;
-            s.stop = 0;
-            if (s.iter >= s.max_iter) {
-                s.stop = 1;
-                s.status = 1;
-                R.done = 1;
-            }
+            return;
+        }
+        if (first) {
+            s.beta = 0.0;
+            s.iter = 0;
+        } else {
+            s.beta = (s.rz != 0.0) ? s.beta * (rz / s.rz) : 0.0;
+            // a fast-converging system reaches delta within a few iterations:
+            // ask for more reduction per segment so replacements stay rare
+            if (s.iter - R.last_iter < 8) R.delta = fmax(R.delta * R.delta, 1e-3);
+        }
+        R.last_iter = s.iter;
+        s.rz = rz;
+        s.rr = rr;
+        s.bb = rr;  // the segment's reference residual
+        const double need = R.tol / rel64;
+        s.rtol = fmin(0.5, fmax(R.delta, 0.5 * need));
+        s.alpha = 0.0;
+        s.status = 0;
+        s.stop = 0;
+        if (s.iter >= s.max_iter) {
+            s.stop = 1;
+            s.status = 1;
+            R.done = 1;
         }
     }
 }
@@ -1856,6 +1948,16 @@ launch_gather<float>(A, grid, st);
     hipLaunchKernelGGL(k_cg_update<float>, dim3(grid, A->nfields), dim3(VT), 0, st, *A);
     return hipGetLastError();
 }
+hipError_t sem_launch_gather_map(const uint32_t *ent_word, int64_t nent, const uint8_t *owner, int32_t *pmap, int64_t n,
+                                 hipStream_t st)
+{
+    if (n == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_fill<int32_t>, dim3(stream_grid(n)), dim3(VT), 0, st, pmap, -1, n);
+    if (nent > 0)
+        hipLaunchKernelGGL(k_gather_map, dim3((unsigned)((nent + VT - 1) / VT)), dim3(VT), 0, st, ent_word, nent, owner,
+                           pmap);
+    return hipGetLastError();
+}
 hipError_t sem_launch_cg_alpha(const double *partial, int64_t nblk, CgScalars *scal, int nfields, hipStream_t st)
 {
     hipLaunchKernelGGL(k_cg_alpha, dim3(nfields), dim3(RT), 0, st, partial, nblk, scal);
@@ -1870,17 +1972,31 @@ hipError_t sem_launch_cg1_update(const Cg1UpdateArgs *A, hipStream_t st)
 }
 hipError_t sem_launch_cg_finish(const CgFinishArgs *A, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_cg_finish, dim3(1), dim3(RT), 0, st, *A);
+    hipLaunchKernelGGL(k_cg_finish, dim3(A->nfields), dim3(RT), 0, st, *A);
     return hipGetLastError();
 }
-hipError_t sem_launch_rel_restart(const RelRestartArgs *A, unsigned grid, hipStream_t st)
+unsigned sem_rel_grid(int64_t n)
 {
-    hipLaunchKernelGGL(k_rel_restart, dim3(grid, A->nfields), dim3(VT), 0, st, *A);
+    const int64_t c = (int64_t)VT * REL_R, g = (n + c - 1) / c;
+    return (unsigned)(g < 1 ? 1 : g);
+}
+hipError_t sem_launch_rel_restart(const RelRestartArgs *A, hipStream_t st)
+{
+    const unsigned nb = sem_rel_grid(A->n), per = 8 * REL_RUN;
+    const dim3 g((nb + per - 1) / per * per);
+    if (A->nfields != 1 && A->nfields != 3) return hipErrorInvalidValue;
+    if (A->nfields == 1) {
+        if (A->pmap) hipLaunchKernelGGL((k_rel_restart<1, true>), g, dim3(VT), 0, st, *A, nb);
+        else hipLaunchKernelGGL((k_rel_restart<1, false>), g, dim3(VT), 0, st, *A, nb);
+    } else {
+        if (A->pmap) hipLaunchKernelGGL((k_rel_restart<3, true>), g, dim3(VT), 0, st, *A, nb);
+        else hipLaunchKernelGGL((k_rel_restart<3, false>), g, dim3(VT), 0, st, *A, nb);
+    }
     return hipGetLastError();
 }
-hipError_t sem_launch_rel_resume(const CgFinishArgs *F, RelState *rel, int first, hipStream_t st)
+hipError_t sem_launch_rel_resume(const CgFinishArgs *F, RelState *rel, int first, int zero_x0, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_rel_resume, dim3(1), dim3(RT), 0, st, *F, rel, first);
+    hipLaunchKernelGGL(k_rel_resume, dim3(F->nfields), dim3(RT), 0, st, *F, rel, first, zero_x0);
     return hipGetLastError();
 }
 hipError_t sem_launch_add_f32(double *x64, const float *x32, const int *skip, int64_t n, int nfields,

@@ -1089,6 +1089,7 @@ def _glued(P, seed, copies):
     (4, 6, 1, (2, 3, 4, 5, 8, 9)),
     (4, 6, 3, (2, 13, 16)),      # the most copies the lists take
     (4, 6, 1, (2, 3, 17)),       # one more: the gather-scatter runs
+    (4, 6, 3, (2, 17)),
 ])
 def test_pcg_gathering_update_is_the_assembled_one(nx, lx, nf, copies):
     """The FP64 solve whose update gathers w sums every point's copies in the order of the
