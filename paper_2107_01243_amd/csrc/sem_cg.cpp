@@ -445,10 +445,13 @@ static sem_status pcg_mixed_reliable(double *x, const double *b, int nf, sem_coe
     CgFinishArgs F{U.partial, (int64_t)ug, W.scal, nullptr, 0, nf};
     const int check_every = std::max(1, P->check_every);
     const int64_t max_polls = (int64_t)P->max_iter + 64 * 64;  // every poll runs >= 1 iteration or ends a segment
-    // Launches queued between polls after a segment has ended do no work but still
-    // cost a pass over the vectors, so the next poll is placed where the current
-    // segment is expected to end: at the length of the previous segment (check_every
-    // before any has ended, check_every / 4 once the estimate is passed).
+    // Launches queued between polls after a segment has ended do no work but still cost a
+    // pass of the grid over the stop flags, so the next poll is placed where the current
+    // segment is expected to end: at the length of the previous segment, then every quarter
+    // of check_every, or of that length where that is less.  Before any has ended, after 4,
+    // 12, 36, ... up to check_every iterations: an idle iteration costs 10 us on a small
+    // problem and 30 at 14M points and three fields, a poll about 20.
+    int probe = std::min(check_every, 4);
     int seg_len[3] = {0, 0, 0}, seg_start[3] = {0, 0, 0};
     for (int64_t poll = 0; poll < max_polls; ++poll) {
         HIP_TRY(hipMemcpyAsync(W.h_scal, W.scal, sizeof(CgScalars) * nf, hipMemcpyDeviceToHost, st));
@@ -477,10 +480,15 @@ static sem_status pcg_mixed_reliable(double *x, const double *b, int nf, sem_coe
         }
         int todo = check_every;
         for (int f = 0; f < nf; ++f) {
-            if (W.h_rel[f].done || W.h_scal[f].stop || seg_len[f] <= 0) continue;
+            if (W.h_rel[f].done || W.h_scal[f].stop) continue;
+            if (seg_len[f] <= 0) {
+                todo = std::min(todo, probe);
+                continue;
+            }
             const int rem = seg_len[f] - (W.h_scal[f].iter - seg_start[f]);
-            todo = std::min(todo, rem > 0 ? rem : std::max(1, check_every / 4));
+            todo = std::min(todo, rem > 0 ? rem : std::max(1, std::min(check_every, seg_len[f]) / 4));
         }
+        probe = std::min(check_every, 3 * probe);
         for (int it = 0; it < todo; ++it) {
             HIP_TRY(fns(c->lx).cg32(&M, c->Xh->D, nf, st));
             SEM_TRY(assemble_or_alpha(U, c, W, g, st));
