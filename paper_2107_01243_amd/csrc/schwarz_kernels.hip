@@ -367,6 +367,17 @@ __global__ __launch_bounds__(ProlongShape<LX>::NT) void k_prolong(ProlongArgs A)
     if (e >= A.nelv) return;
     const int a = t % LX, b = t / LX;
     const double *__restrict__ lin = A.lin;
+    // the element's values first (behind a store of z the compiler would hold back the next
+    // point's loads), then the corner values, two round trips away
+    double *z = A.z + e * L3;
+    const uint8_t *mu = A.mult + e * L3;
+    double zk[LX];
+    int mk[LX];
+#pragma unroll
+    for (int k = 0; k < LX; ++k) {
+        zk[k] = z[k * L2 + t];
+        mk[k] = mu[k * L2 + t];
+    }
     double c[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) c[q] = A.e0[A.cvert[e * 8 + q]];
@@ -378,12 +389,15 @@ __global__ __launch_bounds__(ProlongShape<LX>::NT) void k_prolong(ProlongArgs A)
         const double y1 = fma(ra1, c[4 * kc + 3], ra0 * c[4 * kc + 2]);
         f[kc] = fma(sb1, y1, sb0 * y0);
     }
-    double *z = A.z + e * L3;
-    const uint8_t *mu = A.mult + e * L3;
 #pragma unroll
     for (int k = 0; k < LX; ++k) {
         const double v = fma(lin[LX + k], f[1], lin[k] * f[0]);
-        z[k * L2 + t] = z[k * L2 + t] / (double)mu[k * L2 + t] + v;
+        // 1, 2, 4 or 8 copies: an exact scaling, for which the division's ~30 operations are
+        // not needed; 0 marks a Dirichlet point
+        const int m = mk[k];
+        double y = __builtin_ldexp(zk[k], 1 - __ffs(m));
+        if (m & (m - 1)) y = zk[k] / (double)m;
+        z[k * L2 + t] = m ? y + v : 0.0;
     }
 }
 

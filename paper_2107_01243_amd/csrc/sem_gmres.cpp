@@ -141,7 +141,9 @@ static sem_status schwarz_setup_base(sem_coef c, sem_gs g, hipStream_t st)
     HIP_TRY(hipMemcpy(Z.v_ptr, vptr.data(), vptr.size() * 8, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(Z.v_idx, vidx.data(), vidx.size() * 4, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(Z.v_dir, vdir.data(), vdir.size(), hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(Z.mult, g->m.mult.data(), (size_t)n, hipMemcpyHostToDevice));
+    std::vector<uint8_t> mult(g->m.mult.begin(), g->m.mult.end());
+    for (const int32_t t : c->msh->dir_idx) mult[t] = 0;
+    HIP_TRY(hipMemcpy(Z.mult, mult.data(), (size_t)n, hipMemcpyHostToDevice));
     // Galerkin coarse matrix: element blocks A0_e[c'][c] = phi_c'^T A_L phi_c from probes
     SEM_TRY(ensure_work(c, 1, false));
     Work &W = c->ws;
@@ -333,15 +335,15 @@ static sem_status schwarz_apply(sem_coef c, sem_gs g, double *z, const double *r
     const FdmArgs F{z,      r,      overlap ? Z.S_ov : Z.S, overlap ? Z.lam_ov : Z.lam, g->d_owner,
                     Z.lin,  Z.part, overlap ? Z.face : nullptr, c->h1s, c->h2s, c->nelv};
     HIP_TRY(fns(lx).fdm(&F, st));
-    SEM_TRY(launch_gs<double>(z, 1, g, nullptr, nullptr, st));
     const int64_t nv = Z.nv;
     double *x0 = Z.cv + 8 * nv;
     const CoarseArgs CC{Z.ell_ci, Z.ell_val, Z.width, Z.dinv0, Z.part, Z.v_ptr, Z.v_idx, Z.v_dir, x0, x0 + nv,
                         (CoarseRec *)Z.cv, (CoarseRec *)Z.cv + nv, Z.cpart + 4, Z.cpart, nv};
-    HIP_TRY(sem_launch_coarse_cg(&CC, coarse_iters, st));
+    // the sum of z over shared points runs in the launches of the coarse solve
+    const GsArgs<double> GA = gs_args<double>(z, 1, g, nullptr, nullptr);
+    HIP_TRY(sem_launch_coarse_cg(&CC, coarse_iters, &GA, st));
     const ProlongArgs PA{z, Z.mult, Z.lin, x0, Z.cvert, c->nelv};
     HIP_TRY(fns(lx).prolong(&PA, st));
-    HIP_TRY(sem_launch_mask(z, 0, c->msh->d_dir_idx, (int64_t)c->msh->dir_idx.size(), c->n, 1, st));
     return SEM_OK;
 }
 

@@ -94,7 +94,7 @@ hipError_t sem_launch_dcgs_finish(const double *, int64_t, int, double *, hipStr
 hipError_t sem_launch_arn(const ArnArgs *, int, hipStream_t);
 hipError_t sem_launch_arn_finish(const double *, int64_t, int, int, double *, hipStream_t);
 hipError_t sem_launch_corner(const CornerArgs *, hipStream_t);
-hipError_t sem_launch_coarse_cg(const CoarseArgs *, int, hipStream_t);
+hipError_t sem_launch_coarse_cg(const CoarseArgs *, int, const GsArgs<double> *, hipStream_t);
 int64_t sem_coarse_words(int64_t nv);
 int64_t sem_coarse_partials(int64_t nv);
 hipError_t sem_launch_elem_gb(const double *, const double *, double *, int64_t, int, hipStream_t);
@@ -291,7 +291,7 @@ struct SchwarzData {
     double *part = nullptr;               // [nelv * 8]
     double *cv = nullptr;                 // [sem_coarse_words(nv)]: records (2 x 4 nv), x, p
     double *cpart = nullptr;              // [sem_coarse_partials(nv)]: scalars, partial sums
-    uint8_t *mult = nullptr;              // [n]
+    uint8_t *mult = nullptr;              // [n], 0 on Dirichlet points
     // one-point overlap (built on first use): local operators on the element box
     // extended by one point beyond each face, and the face-neighbour table
     bool ov_valid = false;
@@ -343,7 +343,7 @@ sem_status gs_gather_map(sem_gs g, hipStream_t st);
 sem_status check_coef(sem_coef c, sem_mesh msh, sem_space Xh);
 
 template <typename T>
-sem_status launch_gs(T *u, int nf, sem_gs g, const CgScalars *skip, const AlphaJob *job, hipStream_t st)
+GsArgs<T> gs_args(T *u, int nf, sem_gs g, const CgScalars *skip, const AlphaJob *job)
 {
     GsArgs<T> A;
     A.u = u;
@@ -359,6 +359,13 @@ sem_status launch_gs(T *u, int nf, sem_gs g, const CgScalars *skip, const AlphaJ
     A.ent_word = g->d_ent_word;
     A.nent = g->entries ? (int64_t)g->m.ent_idx.size() : 0;
     A.max_group = g->m.max_group;
+    return A;
+}
+
+template <typename T>
+sem_status launch_gs(T *u, int nf, sem_gs g, const CgScalars *skip, const AlphaJob *job, hipStream_t st)
+{
+    const GsArgs<T> A = gs_args<T>(u, nf, g, skip, job);
     if (A.npairs + A.nblocks + A.nent == 0 && job == nullptr) return SEM_OK;
     hipError_t e;
     if constexpr (sizeof(T) == 8) e = sem_launch_gs_f64(&A, st);

@@ -142,8 +142,8 @@ struct FdmArgs {
     int64_t nelv;
 };
 
-// Coarse prolongation with the multiplicity average of the local solves:
-// z = z / mult + sum over the eight corners c of e0[cvert[e][c]] phi_c, phi_c the
+// Coarse prolongation with the multiplicity average of the local solves, 0 on Dirichlet
+// points (mult 0): z = z / mult + sum over the eight corners c of e0[cvert[e][c]] phi_c, phi_c the
 // trilinear corner function (a product of the linear functions in lin).
 struct ProlongArgs {
     double *z;

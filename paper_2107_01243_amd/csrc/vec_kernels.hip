@@ -208,24 +208,12 @@ __global__ __launch_bounds__(VT) void k_gs(GsArgs<T> A)
 // copies receive the identical, canonical sum; then each lane writes its own copy.
 // The shuffle loop runs max_group times for the whole wave (all lanes active).
 template <typename T>
-__global__ __launch_bounds__(VT) void k_gs_entries(GsArgs<T> A)
+__device__ __forceinline__ void gs_entries_wave(const GsArgs<T> &A, int64_t wave)
 {
-#if SEM_GS_XCD
-    const unsigned per = gridDim.x / 8;
-    const unsigned lb = (blockIdx.x % 8) * per + blockIdx.x / 8;
-#else
-    const unsigned lb = blockIdx.x;
-#endif
-    if (A.skip) {
-        // every field stopped: nothing to gather, and no step length left to set
-        bool live = false;
-        for (int f = 0; f < A.nfields; ++f) live = live || !A.skip[f].stop;
-        if (!live) return;
-    }
     // each wave owns GEPL consecutive 64-entry segments; lane l handles entry l of
     // each, so its GEPL index -> value loads are independent and in flight together
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t base = ((int64_t)lb * VT + (int64_t)wave * 64) * GEPL + lane;
+    const int lane = threadIdx.x & 63;
+    const int64_t base = wave * (64 * GEPL) + lane;
     int32_t e[GEPL];
     int cnt[GEPL], lead[GEPL];
     // a group's extent from the start flags of the segment: its first lane is the
@@ -264,6 +252,29 @@ __global__ __launch_bounds__(VT) void k_gs_entries(GsArgs<T> A)
         for (int k = 0; k < GEPL; ++k)
             if (e[k] >= 0) u[e[k]] = s[k];
     }
+}
+
+// Block b of nb (a multiple of 8) of the entry list: blocks are dealt to the XCDs in turn,
+// and XCD x takes one contiguous range of the list.
+__device__ __forceinline__ unsigned gs_block(unsigned b, unsigned nb)
+{
+#if SEM_GS_XCD
+    return (b % 8) * (nb / 8) + b / 8;
+#else
+    return b;
+#endif
+}
+
+template <typename T>
+__global__ __launch_bounds__(VT) void k_gs_entries(GsArgs<T> A)
+{
+    if (A.skip) {
+        // every field stopped: nothing to gather, and no step length left to set
+        bool live = false;
+        for (int f = 0; f < A.nfields; ++f) live = live || !A.skip[f].stop;
+        if (!live) return;
+    }
+    gs_entries_wave(A, (int64_t)gs_block(blockIdx.x, gridDim.x) * (VT / 64) + (threadIdx.x >> 6));
     if (A.alpha_job && blockIdx.x == 0) {
         __shared__ double sh[VT];
         fold_job<VT>(*A.alpha_job, A.nfields, sh);
@@ -674,9 +685,13 @@ __device__ __forceinline__ double small_sum(double v, double *sh)
 // LDS (the 256 registers a lane has with two waves per SIMD do not hold them; spilled to
 // memory, a step took 7 us).
 template <int RPT>
-__global__ __launch_bounds__(CST) void k_ccg_small(CoarseArgs A, int iters)
+__global__ __launch_bounds__(CST) void k_ccg_small(CoarseArgs A, int iters, GsArgs<double> G)
 {
-    constexpr int LW = RPT > 2 ? 10 : 0, RW = RESW - LW;
+    if (blockIdx.x > 0) {  // the other workgroups: the gather-scatter
+        gs_entries_wave(G, (int64_t)(blockIdx.x - 1) * (CST / 64) + (threadIdx.x >> 6));
+        return;
+    }
+    constexpr int LW = RPT > 2 ? 11 : 0, RW = RESW - LW;
     __shared__ double ps[CST * RPT];
     __shared__ double sh[2][CST / 64];
     __shared__ double al[LW > 0 ? LW * RPT * CST : 1];
@@ -745,9 +760,29 @@ __global__ __launch_bounds__(CST) void k_ccg_small(CoarseArgs A, int iters)
     }
 }
 
-// Start of the launch-per-step form: r = b, w = s = 0, p = x = 0.
-__global__ __launch_bounds__(VT) void k_ccg_start(CoarseArgs A)
+// Blocks [lo, hi) of the nb of a gather-scatter of z that a launch of the coarse solve also
+// runs: the coarse steps are a chain of short latency-bound launches that leaves the memory
+// idle, and the sum of the local solves over shared points does not depend on them.  At
+// 16.8M points and 35,937 vertices 11 launches of 14.7 us, against 8.8 us each and 75 us for
+// the gather-scatter alone (all of it in the first launch 170 us together, in the first two
+// 181); 960 elements, lx = 6: one launch of 52 us against 48 + 4.8.
+struct GsSlice {
+    GsArgs<double> G;
+    unsigned lo, hi, nb;
+};
+__device__ __forceinline__ void gs_slice(const GsSlice &S, unsigned b)
 {
+    if (b < S.hi - S.lo)
+        gs_entries_wave(S.G, (int64_t)gs_block(S.lo + b, S.nb) * (VT / 64) + (threadIdx.x >> 6));
+}
+
+// Start of the launch-per-step form: r = b, w = s = 0, p = x = 0.
+__global__ __launch_bounds__(VT) void k_ccg_start(CoarseArgs A, unsigned nc, GsSlice S)
+{
+    if (blockIdx.x >= nc) {
+        gs_slice(S, blockIdx.x - nc);
+        return;
+    }
     const int64_t v = (int64_t)blockIdx.x * VT + threadIdx.x;
     if (v >= A.nv) return;
     A.rec0[v] = CoarseRec{coarse_rhs(A, v), 0.0, 0.0, A.dinv[v]};
@@ -773,12 +808,16 @@ __global__ __launch_bounds__(VT) void k_ccg_start(CoarseArgs A)
 #endif
 constexpr int SPL = SEM_CCG_SPL;
 constexpr int CCG_PRE = 28 / SPL;  // entries per lane requested ahead (27-point rows)
-__global__ __launch_bounds__(VT) void k_ccg_step(CoarseArgs A, int it, int last)
+__global__ __launch_bounds__(VT) void k_ccg_step(CoarseArgs A, int it, int last, unsigned nc, GsSlice S)
 {
+    if (blockIdx.x >= nc) {
+        gs_slice(S, blockIdx.x - nc);
+        return;
+    }
     __shared__ double sh[4][VT / 64];
     const CoarseRec *ro = (it & 1) ? A.rec1 : A.rec0;
     CoarseRec *rn = (it & 1) ? A.rec0 : A.rec1;
-    const int64_t g = gridDim.x;
+    const int64_t g = nc;
     const int part = threadIdx.x % SPL, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t v = ((int64_t)blockIdx.x * VT + threadIdx.x) / SPL;
     const bool in = v < A.nv;
@@ -2082,20 +2121,43 @@ static int64_t ccg_grid(int64_t nv) { return (nv * SPL + VT - 1) / VT; }
 int64_t sem_coarse_words(int64_t nv) { return 10 * nv; }
 int64_t sem_coarse_partials(int64_t nv) { return 4 * ccg_grid(nv) + 4; }
 
-// iters fixed-count Jacobi-CG steps on the coarse system from x = 0, no host sync.
-hipError_t sem_launch_coarse_cg(const CoarseArgs *A, int iters, hipStream_t st)
+// iters fixed-count Jacobi-CG steps on the coarse system from x = 0, no host sync, with the
+// gather-scatter G of z (one field, no skip, no job) in the same launches where it can be.
+hipError_t sem_launch_coarse_cg(const CoarseArgs *A, int iters, const GsArgs<double> *G, hipStream_t st)
 {
-    if (A->nv == 0) return hipSuccess;
-    if (A->width < 1 || A->nv > 0x7fffffffLL) return hipErrorInvalidValue;
+    if (A->width < 1 || A->nv > 0x7fffffffLL || G->nfields != 1 || G->skip || G->alpha_job) return hipErrorInvalidValue;
+    unsigned nb = G->nent > 0 ? gs_grid((G->nent + GEPL - 1) / GEPL) : 0;
+    // points of more than 64 copies, or no coarse system: a launch of its own
+    if (A->nv == 0 || G->npairs + G->nblocks > 0) {
+        if (G->npairs + G->nblocks + G->nent > 0) {
+            const hipError_t e = launch_gs_t<double>(G, st);
+            if (e != hipSuccess || A->nv == 0) return e;
+        }
+        if (A->nv == 0) return hipSuccess;
+        nb = 0;
+    }
     if (iters > 0 && A->nv <= CCG_SMALL && A->width <= RESW) {
-        if (A->nv <= CST) hipLaunchKernelGGL(k_ccg_small<1>, dim3(1), dim3(CST), 0, st, *A, iters);
-        else if (A->nv <= 2 * CST) hipLaunchKernelGGL(k_ccg_small<2>, dim3(1), dim3(CST), 0, st, *A, iters);
-        else hipLaunchKernelGGL(k_ccg_small<3>, dim3(1), dim3(CST), 0, st, *A, iters);
+        const dim3 g(1 + (nb * VT + CST - 1) / CST);
+        if (A->nv <= CST) hipLaunchKernelGGL(k_ccg_small<1>, g, dim3(CST), 0, st, *A, iters, *G);
+        else if (A->nv <= 2 * CST) hipLaunchKernelGGL(k_ccg_small<2>, g, dim3(CST), 0, st, *A, iters, *G);
+        else hipLaunchKernelGGL(k_ccg_small<3>, g, dim3(CST), 0, st, *A, iters, *G);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(k_ccg_start, dim3((unsigned)((A->nv + VT - 1) / VT)), dim3(VT), 0, st, *A);
-    for (int it = 0; it <= iters && iters > 0; ++it)
-        hipLaunchKernelGGL(k_ccg_step, dim3((unsigned)ccg_grid(A->nv)), dim3(VT), 0, st, *A, it, it == iters ? 1 : 0);
+    const int launches = 2 + iters;  // start, iters steps, the last update
+    auto slice = [&](int k) {
+        auto at = [&](int q) { return (unsigned)((int64_t)(nb / 8) * q / launches) * 8; };
+        return iters > 0 ? GsSlice{*G, at(k), at(k + 1), nb} : GsSlice{*G, 0, nb, nb};
+    };
+    {
+        const GsSlice S = slice(0);
+        const unsigned nc = (unsigned)((A->nv + VT - 1) / VT);
+        hipLaunchKernelGGL(k_ccg_start, dim3(nc + (S.hi - S.lo)), dim3(VT), 0, st, *A, nc, S);
+    }
+    for (int it = 0; it <= iters && iters > 0; ++it) {
+        const GsSlice S = slice(1 + it);
+        const unsigned nc = (unsigned)ccg_grid(A->nv);
+        hipLaunchKernelGGL(k_ccg_step, dim3(nc + (S.hi - S.lo)), dim3(VT), 0, st, *A, it, it == iters ? 1 : 0, nc, S);
+    }
     return hipGetLastError();
 }
 hipError_t sem_launch_elem_gb(const double *G, const double *B, double *out, int64_t nelv, int lx3,
