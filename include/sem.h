@@ -26,7 +26,8 @@
  *   pointers are caller-owned CPU memory.  Handles and every internal buffer are
  *   owned by the library and released by the matching *_destroy call.
  * Streams.  `stream` is a hipStream_t passed as void* (NULL = the null stream).
- *   sem_ax_helm, sem_gs_op, sem_mask and sem_ax_helm_adjoint only enqueue work
+ *   sem_ax_helm, sem_gs_op, sem_mask, sem_assemble and sem_ax_helm_adjoint only enqueue
+ *   work (the first call on a handle also uploads its maps)
  *   and return.  sem_pcg_solve synchronises the stream to poll convergence.
  * Errors.  Every call returns a sem_status; nothing aborts or throws.  Invalid
  *   arguments are rejected before any launch.  sem_last_error() returns a
@@ -142,6 +143,12 @@ sem_status sem_gs_op(void *u, int nfields, sem_gs gs, sem_dtype dt, void *stream
 
 /* u <- 0 on the mesh's Dirichlet points (Eq. 5), nfields contiguous fields. */
 sem_status sem_mask(void *u, int nfields, sem_mesh msh, sem_dtype dt, void *stream);
+
+/* b = QQ^T u, 0 on the Dirichlet points: sem_gs_op and sem_mask out of place in one pass
+ * (device, dtype dt, nfields (1 or 3) contiguous local fields; b and u must not overlap).
+ * The same values as those two calls on a copy of u. */
+sem_status sem_assemble(void *b, const void *u, int nfields, sem_mesh msh, sem_gs gs, sem_dtype dt,
+                        void *stream);
 
 /* ---------------------------------------------------------------- coefficients (coef)
  * Geometric factors of Eq. 9 from nodal coordinates xyz_dev (device FP64, 3*n_p:

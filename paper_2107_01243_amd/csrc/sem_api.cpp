@@ -149,6 +149,44 @@ sem_status gs_gather_map(sem_gs g, hipStream_t st)
     return SEM_OK;
 }
 
+// One pass (k_assemble) or copy, gather-scatter and mask.  Up to 2M points the launches are
+// what costs; beyond, points with copies are the dearer ones of the pass, and their share
+// falls with lx.  Measured, us, one pass against three: FP64 lx = 5 at 8M points 71 / 59, lx = 7
+// at 6M 39 / 41, lx = 8 at 16.8M 122 / 135; FP32 lx = 7 at 6M with three fields 82 / 66, lx = 8
+// at 16.8M 72 / 63, lx = 12 at 13.8M 46 / 47, three fields 123 / 160; at 2.1M, lx = 8: FP64
+// 14.7 / 23.5, FP32 10.5 / 18.5.
+template <typename T>
+static bool assembles_in_one_pass(sem_mesh msh)
+{
+    return msh->n <= (1 << 21) || msh->lx >= (sizeof(T) == 8 ? 7 : 9);
+}
+
+template <typename T>
+static sem_status assemble_t(T *b, const T *u, int nf, sem_mesh msh, sem_gs g, hipStream_t st)
+{
+    int32_t *pmap = nullptr;
+    if (assembles_in_one_pass<T>(msh)) pmap = g->d_pmap.load(std::memory_order_acquire);
+    if (!pmap && assembles_in_one_pass<T>(msh)) {
+        // building the map allocates and waits, which a captured stream does not allow
+        hipStreamCaptureStatus cap;
+        HIP_TRY(hipStreamIsCapturing(st, &cap));
+        if (cap == hipStreamCaptureStatusNone) {
+            SEM_TRY(gs_gather_map(g, st));
+            pmap = g->d_pmap.load(std::memory_order_acquire);
+        }
+    }
+    if (!pmap) {
+        HIP_TRY(hipMemcpyAsync(b, u, sizeof(T) * msh->n * nf, hipMemcpyDeviceToDevice, st));
+        SEM_TRY(launch_gs<T>(b, nf, g, nullptr, nullptr, st));
+        HIP_TRY(sem_launch_mask(b, sizeof(T) == 4, msh->d_dir_idx, (int64_t)msh->dir_idx.size(), msh->n, nf, st));
+        return SEM_OK;
+    }
+    const AssembleArgs<T> A{b, u, pmap, g->d_ent_word, msh->d_dir, msh->n, nf};
+    if constexpr (sizeof(T) == 8) HIP_TRY(sem_launch_assemble_f64(&A, st));
+    else HIP_TRY(sem_launch_assemble_f32(&A, st));
+    return SEM_OK;
+}
+
 sem_status check_coef(sem_coef c, sem_mesh msh, sem_space Xh)
 {
     if (!c || !msh || !Xh) return fail(SEM_ERR_INVALID, "NULL handle");
@@ -460,6 +498,22 @@ sem_status sem_mask(void *u, int nfields, sem_mesh msh, sem_dtype dt, void *stre
     HIP_TRY(sem_launch_mask(u, dt == SEM_F32, msh->d_dir_idx, (int64_t)msh->dir_idx.size(), msh->n, nfields,
                             S(stream)));
     return SEM_OK;
+}
+
+sem_status sem_assemble(void *b, const void *u, int nfields, sem_mesh msh, sem_gs gs, sem_dtype dt, void *stream)
+{
+    if (!msh) return fail(SEM_ERR_INVALID, "msh is NULL");
+    if (!gs || gs->msh != msh) return fail(SEM_ERR_INVALID, "gs is NULL or built for another mesh");
+    if (nfields != 1 && nfields != 3) return fail(SEM_ERR_INVALID, "nfields must be 1 or 3");
+    if (dt != SEM_F64 && dt != SEM_F32) return fail(SEM_ERR_INVALID, "bad dtype");
+    const size_t bytes = (size_t)msh->n * nfields * (dt == SEM_F64 ? 8 : 4);
+    if (bytes == 0) return SEM_OK;
+    if (!b || !u) return fail(SEM_ERR_INVALID, "b or u is NULL");
+    if (overlap(b, bytes, u, bytes)) return fail(SEM_ERR_INVALID, "b and u overlap");
+    SEM_TRY(gs_upload(gs));
+    SEM_TRY(mesh_upload(msh));
+    if (dt == SEM_F64) return assemble_t<double>((double *)b, (const double *)u, nfields, msh, gs, S(stream));
+    return assemble_t<float>((float *)b, (const float *)u, nfields, msh, gs, S(stream));
 }
 
 // ------------------------------------------------------------------ coef

@@ -73,6 +73,8 @@ hipError_t sem_launch_cg_init_f32(const CgInitArgs<float> *, unsigned, hipStream
 hipError_t sem_launch_cg_start(const CgFinishArgs *, hipStream_t);
 hipError_t sem_launch_cg_update_f64(const CgUpdateArgs<double> *, unsigned, hipStream_t);
 hipError_t sem_launch_cg_update_f32(const CgUpdateArgs<float> *, unsigned, hipStream_t);
+hipError_t sem_launch_assemble_f64(const AssembleArgs<double> *, hipStream_t);
+hipError_t sem_launch_assemble_f32(const AssembleArgs<float> *, hipStream_t);
 hipError_t sem_launch_gather_map(const uint32_t *, int64_t, const uint8_t *, int32_t *, int64_t, hipStream_t);
 hipError_t sem_launch_cg_alpha(const double *, int64_t, CgScalars *, int, hipStream_t);
 hipError_t sem_launch_cg_finish(const CgFinishArgs *, hipStream_t);

@@ -96,6 +96,18 @@ struct CgUpdateArgs {
     int64_t nm = 0;
 };
 
+// out = QQ^T in, 0 where dir (nullptr: nowhere) is set; pmap and ent_word as above.
+template <typename T>
+struct AssembleArgs {
+    T *out;
+    const T *in;
+    const int32_t *pmap;
+    const uint32_t *ent_word;
+    const uint8_t *dir;
+    int64_t n;
+    int nfields;
+};
+
 struct CgFinishArgs {
     const double *partial;
     int64_t nblk;

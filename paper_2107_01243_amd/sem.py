@@ -62,6 +62,7 @@ _SIGS = {
     "sem_gs_sizes": ([_vp, _vp, _vp, _vp], C.c_int),
     "sem_gs_export_maps": ([_vp, _vp, _vp, _vp, _vp], C.c_int),
     "sem_gs_destroy": ([_vp], None),
+    "sem_assemble": ([_vp, _vp, C.c_int, _vp, _vp, C.c_int, _vp], C.c_int),
     "sem_gs_op": ([_vp, C.c_int, _vp, C.c_int, _vp], C.c_int),
     "sem_mask": ([_vp, C.c_int, _vp, C.c_int, _vp], C.c_int),
     "sem_coef_create": ([_vp, _vp, _vp, C.c_uint, _vp, C.POINTER(_vp)], C.c_int),
@@ -325,6 +326,11 @@ def mask(u, msh: Mesh, nfields: int = 1, stream=None):
     return u
 
 
+def _assemble(b, u, msh: Mesh, gs: GS, nfields: int):
+    _check(_L.sem_assemble(_ptr(b), _ptr(u), nfields, msh._h, gs._h, _dtype(u), _stream()))
+    return b
+
+
 def jacobi_inverse(coef: Coef, msh: Mesh, Xh: Space, gs: GS, stream=None):
     d = torch.empty(msh.n, dtype=torch.float64, device="cuda")
     _check(_L.sem_jacobi_inverse(_ptr(d), coef._h, msh._h, Xh._h, gs._h, _stream(stream)))
@@ -536,14 +542,19 @@ class BoxProblem:
     def apply(self, u, nfields=1):
         """mask QQ^T A_L u."""
         w = self.ax(u, nfields)
+        if self.n <= 1 << 20:  # bound by its launches: one less of them
+            return _assemble(torch.empty_like(w), w, self.msh, self.gs, nfields)
         self.gs.op(w, nfields)
         return mask(w, self.msh, nfields)
 
     def assemble(self, f_local, nfields=1):
         """b = mask QQ^T f (copy)."""
-        b = f_local.clone()
-        self.gs.op(b, nfields)
-        return mask(b, self.msh, nfields)
+        if isinstance(f_local, torch.Tensor) and f_local.requires_grad and torch.is_grad_enabled():
+            b = f_local.clone()  # the copy stays in the caller's graph
+            self.gs.op(b, nfields)
+            return mask(b, self.msh, nfields)
+        _dev(f_local, nfields * self.msh.n, "u")
+        return _assemble(torch.empty_like(f_local), f_local, self.msh, self.gs, nfields)
 
     def solve(self, b, nfields=1, **kw):
         x = torch.zeros_like(b)

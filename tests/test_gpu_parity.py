@@ -1094,8 +1094,8 @@ def _glued(P, seed, copies):
 def test_pcg_gathering_update_is_the_assembled_one(nx, lx, nf, copies):
     """The FP64 solve whose update gathers w sums every point's copies in the order of the
     gather-scatter: solution, iteration count and residual equal, to the bit, those of the
-    solve that assembles w first (the allocation-free one on a handle without the lists);
-    after the lists exist it uses them too, with the same result.  The FP32 iteration, where
+    solve that assembles w first (the allocation-free one on a handle without the map);
+    after the map exists it uses it too, with the same result.  The FP32 iteration, where
     it gathers, must meet the tolerance on the FP64 residual."""
     say(f"[gathering update] nx={nx} lx={lx} nf={nf} copies={copies}")
     P = sem.BoxProblem.build(nx, lx, 0.05, fp32=True)
@@ -1103,8 +1103,9 @@ def test_pcg_gathering_update_is_the_assembled_one(nx, lx, nf, copies):
         msh, gs, coef = _glued(P, 7, copies)
         P = sem.BoxProblem(P.Xh, msh, gs, coef, P.xyz, None, None, nx, lx)
     P.coef.set_helmholtz(1.0, 1.0)
-    f = to_dev(workloads.uniform(P.n * nf, workloads.SEED_RHS))
-    b = P.assemble(f, nf)
+    b = to_dev(workloads.uniform(P.n * nf, workloads.SEED_RHS))
+    P.gs.op(b, nf)  # (not assemble(), which builds the map)
+    sem.mask(b, P.msh, nf)
     args = (P.coef, P.msh, P.Xh, P.gs)
     kw = dict(nfields=nf, rtol=1e-10, check_every=7)
     xa, xg, xn = (torch.full_like(b, float("nan")) for _ in range(3))
@@ -1120,3 +1121,74 @@ def test_pcg_gathering_update_is_the_assembled_one(nx, lx, nf, copies):
     for k in range(nf):
         rk, bk = r[k * P.n:(k + 1) * P.n], b[k * P.n:(k + 1) * P.n]
         assert float((rk * rk / P.mult).sum().sqrt() / (bk * bk / P.mult).sum().sqrt()) <= 1.05e-10
+
+
+@pytest.mark.parametrize("nx,lx,copies", [
+    (1, 8, None), (3, 5, None), (2, 12, None), (7, 7, None), (16, 3, None),
+    (18, 7, None),               # 2000376 points: below the line at 2^21
+    (33, 4, None),               # 2299968: above it, FP64 and FP32 in three passes
+    (19, 7, None),               # 2352637: FP64 in one pass, FP32 in three
+    (15, 9, None),               # 2460375: both in one pass
+    (4, 6, (2, 3, 4, 5, 8, 9)), (4, 6, (2, 13, 16)), (4, 6, (2, 3, 17)),
+])
+def test_assembly_in_one_pass(nx, lx, copies):
+    """assemble() equals, to the bit, a copy followed by the gather-scatter and the mask: the
+    sums are taken in the same order.  Infinities, NaN and negative zeros included, and the
+    input is left as it was."""
+    say(f"[assembly] nx={nx} lx={lx} copies={copies}")
+    P = sem.BoxProblem.build(nx, lx, 0.05, fp32=True)
+    if copies is not None:
+        msh, gs, coef = _glued(P, 7, copies)
+        P = sem.BoxProblem(P.Xh, msh, gs, coef, P.xyz, None, None, nx, lx)
+    for nf in (1, 3):
+        for dt in (torch.float64, torch.float32):
+            u = to_dev(workloads.uniform(P.n * nf, workloads.SEED_RHS), dt)
+            u[5::97] = -0.0
+            u[P.n // 2] = float("inf")
+            u[P.n // 3] = float("nan")
+            keep = u.clone()
+            ref = u.clone()
+            P.gs.op(ref, nf)
+            sem.mask(ref, P.msh, nf)
+            ints = torch.int64 if dt == torch.float64 else torch.int32
+            for _ in range(2):
+                b = P.assemble(u, nf)
+                same = (b.view(ints) == ref.view(ints)) | (b.isnan() & ref.isnan())
+                assert bool(same.all()) and torch.equal(u.view(ints), keep.view(ints))
+    with pytest.raises(ValueError):
+        P.assemble(u[:-1], 3)
+    with pytest.raises(TypeError):
+        P.assemble(u.cpu(), 3)
+    # a tensor of the caller's graph stays in it
+    g = to_dev(workloads.uniform(P.n, workloads.SEED_RHS)).requires_grad_(True)
+    assert P.assemble(g).requires_grad
+    w = P.apply(u[:P.n].nan_to_num(0.0, 0.0, 0.0))
+    ref = P.ax(u[:P.n].nan_to_num(0.0, 0.0, 0.0))
+    P.gs.op(ref)
+    assert torch.equal(w, sem.mask(ref, P.msh))
+
+
+def test_assembly_under_capture():
+    """A captured assembly, on a handle whose point map no call has built yet (the three
+    passes) and on one where it is there (one pass), replayed with eager work between."""
+    say("[assembly capture]")
+    for warm in (False, True):
+        P = sem.BoxProblem.build(5, 6, 0.05)
+        u = to_dev(workloads.uniform(P.n, workloads.SEED_RHS))
+        ref = u.clone()
+        P.gs.op(ref)
+        sem.mask(ref, P.msh)
+        if warm:
+            P.assemble(u)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            b = P.assemble(u)
+        for k in range(4):
+            b.fill_(7.0)
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(b, ref)
+            u.mul_(2.0)
+            ref.mul_(2.0)
+            torch.cuda.synchronize()
