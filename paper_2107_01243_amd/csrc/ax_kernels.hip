@@ -322,8 +322,9 @@ __device__ __forceinline__ void load_row(T (&r)[LX], const T *__restrict__ p, bo
 // Geometric-factor pencils are streamed once per application and the six planes
 // (6 words per point) never fit the 256 MB last-level cache at production sizes, so
 // they are read with non-temporal loads: this keeps the cache for the vectors
-// (u, w, the Krylov vectors) that are reused between launches.
-template <int LX, typename T>
+// (u, w, the Krylov vectors) that are reused between launches.  KEEP: a CG iteration whose
+// whole set fits the cache reads and writes it plainly, and then finds it there.
+template <int LX, typename T, bool KEEP = false>
 __device__ __forceinline__ void load_g(T (&r)[LX], const T *__restrict__ p, bool act)
 {
     if (!act) {
@@ -332,7 +333,7 @@ __device__ __forceinline__ void load_g(T (&r)[LX], const T *__restrict__ p, bool
         return;
     }
 #pragma unroll
-    for (int k = 0; k < LX; ++k) r[k] = __builtin_nontemporal_load(p + k * LX * LX);
+    for (int k = 0; k < LX; ++k) r[k] = KEEP ? p[k * LX * LX] : __builtin_nontemporal_load(p + k * LX * LX);
 }
 
 template <int LX, typename T>
@@ -451,7 +452,7 @@ __global__ SEM_BOUNDS2((Shape<LX, T>::NT), (Shape<LX, T>::MINW)) void k_ax_helm(
 // Single-reduction CG (CG1 = true, Chronopoulos-Gear): u = dinv r (not stored),
 // w = A_L u.  Either way the workgroup's partial sum of v . w (v = p or u) is written:
 // v^T A v by the unassembled identity of Eq. 10.
-template <int LX, typename T, int NF, bool GEN, bool CG1>
+template <int LX, typename T, int NF, bool GEN, bool CG1, bool KEEP>
 __global__ SEM_BOUNDS2((Shape<LX, T>::NT), (Shape<LX, T>::MINW)) void k_cg_matvec(CgMatvecArgs<T> A, DEo<LX, T> D)
 {
     using S = Shape<LX, T>;
@@ -475,15 +476,15 @@ __global__ SEM_BOUNDS2((Shape<LX, T>::NT), (Shape<LX, T>::MINW)) void k_cg_matve
 
     T g[6][LX];
 #pragma unroll
-    for (int f = 0; f < 6; ++f) load_g<LX, T>(g[f], A.G + f * A.n + row, act);
+    for (int f = 0; f < 6; ++f) load_g<LX, T, KEEP>(g[f], A.G + f * A.n + row, act);
     RowCoef<LX, T, GEN> c;
     load_coef<LX, T, GEN>(c, A, row, act);
     T dinv[LX];
-    // the CG vectors too are streamed with non-temporal hints: one iteration moves
-    // several times the last-level cache, and keeping them out of it leaves room for
+    // the CG vectors too are streamed with non-temporal hints, unless KEEP: one iteration
+    // moves several times the last-level cache, and keeping them out of it leaves room for
     // the gather-scatter's index lists and w, which the next kernel reads (measured:
     // 0.763 -> 0.687 s per FP64 solve at 32^3 x lx=8)
-    load_g<LX, T>(dinv, A.dinv + row, act);
+    load_g<LX, T, KEEP>(dinv, A.dinv + row, act);
 
     double part[NF];
 #pragma unroll 1
@@ -492,18 +493,22 @@ __global__ SEM_BOUNDS2((Shape<LX, T>::NT), (Shape<LX, T>::MINW)) void k_cg_matve
         const CgScalars *sc = A.scal + f;
         if (sc->stop) continue;  // uniform: every lane reads the same flag
         T r[LX], p[LX];
-        load_g<LX, T>(r, A.r + f * A.n + row, act);
+        load_g<LX, T, KEEP>(r, A.r + f * A.n + row, act);
         if constexpr (CG1) {
 #pragma unroll
             for (int i = 0; i < LX; ++i) p[i] = dinv[i] * r[i];
         } else {
             const T beta = (T)sc->beta;
-            load_g<LX, T>(p, A.p + f * A.n + row, act);
+            load_g<LX, T, KEEP>(p, A.p + f * A.n + row, act);
 #pragma unroll
             for (int i = 0; i < LX; ++i) p[i] = fma(beta, p[i], dinv[i] * r[i]);
             if (act) {
 #pragma unroll
-                for (int k = 0; k < LX; ++k) __builtin_nontemporal_store(p[k], A.p + f * A.n + row + k * LX * LX);
+                for (int k = 0; k < LX; ++k) {
+                    T *q = A.p + f * A.n + row + k * LX * LX;
+                    if constexpr (KEEP) *q = p[k];
+                    else __builtin_nontemporal_store(p[k], q);
+                }
             }
         }
         T ur[LX], us[LX], ut[LX];
@@ -1691,8 +1696,19 @@ void launch_cg_nf(const sem::CgMatvecArgs<T> &A, const sem::DEo<SEM_LX, T> &Dm, 
         });
     } else {
         const bool gen = A.h1 || A.h2 || A.h2s != T(0);
-        if (gen) hipLaunchKernelGGL((sem::k_cg_matvec<SEM_LX, T, NF, true, CG1>), dim3(grid), dim3(S::NT), 0, st, A, Dm);
-        else hipLaunchKernelGGL((sem::k_cg_matvec<SEM_LX, T, NF, false, CG1>), dim3(grid), dim3(S::NT), 0, st, A, Dm);
+        auto go = [&](auto keep) {
+            constexpr bool KEEP = decltype(keep)::value;
+            if (gen)
+                hipLaunchKernelGGL((sem::k_cg_matvec<SEM_LX, T, NF, true, CG1, KEEP>), dim3(grid), dim3(S::NT), 0, st, A,
+                                   Dm);
+            else
+                hipLaunchKernelGGL((sem::k_cg_matvec<SEM_LX, T, NF, false, CG1, KEEP>), dim3(grid), dim3(S::NT), 0, st, A,
+                                   Dm);
+        };
+        if constexpr (!CG1) {
+            if (A.keep) return go(std::true_type{});
+        }
+        go(std::false_type{});
     }
 }
 

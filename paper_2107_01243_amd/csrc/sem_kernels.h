@@ -85,6 +85,7 @@ struct CgMatvecArgs {
     int64_t nelv;
     const CgScalars *scal;  // one per field
     double *partial;        // [field][workgroup]
+    int keep = 0;           // what an iteration touches fits the last-level cache
     const void *deo = nullptr;  // device copy of the even-odd D of this lx and precision
 };
 

@@ -94,6 +94,7 @@ struct CgUpdateArgs {
     // length (nm = 0: it is in scal)
     const double *mpart = nullptr;
     int64_t nm = 0;
+    int keep = 0;  // what an iteration touches fits the last-level cache
 };
 
 // out = QQ^T in, 0 where dir (nullptr: nowhere) is set; pmap and ent_word as above.

@@ -59,6 +59,20 @@ template <typename T> struct UpdChunk;
 template <> struct UpdChunk<double> { static constexpr int UV = SEM_UPD64, GV = 2; };
 template <> struct UpdChunk<float> { static constexpr int UV = SEM_UPD32, GV = 4; };
 
+// A value that is streamed, or (KEEP) one that stays in the last-level cache.
+template <bool KEEP, typename T>
+__device__ __forceinline__ T ld(const T *p)
+{
+    if constexpr (KEEP) return *p;
+    else return __builtin_nontemporal_load(p);
+}
+template <bool KEEP, typename T>
+__device__ __forceinline__ void stv(T v, T *p)
+{
+    if constexpr (KEEP) *p = v;
+    else __builtin_nontemporal_store(v, p);
+}
+
 // Sum `nblk` partials in a fixed order inside one workgroup of NTH lanes: lane t
 // accumulates entries t, t+NTH, ... into four interleaved accumulators (loads in
 // flight), combines them, then a fixed binary tree in LDS.  Deterministic for a
@@ -1057,7 +1071,7 @@ __global__ __launch_bounds__(RT) void k_cg_start(CgFinishArgs A)
 // Workgroup b streams the contiguous chunk of UV * VT points starting at b * UV * VT
 // (UV per precision: see upd_chunk); its two partials are reduced by wave
 // butterflies and then the four waves in order (deterministic, one barrier).
-template <typename T>
+template <typename T, bool KEEP>
 __global__ __launch_bounds__(VT) void k_cg_update(CgUpdateArgs<T> A)
 {
     constexpr int UV = UpdChunk<T>::UV;
@@ -1088,10 +1102,10 @@ __global__ __launch_bounds__(VT) void k_cg_update(CgUpdateArgs<T> A)
 #pragma unroll
         for (int u = 0; u < UV; ++u) {
             const int64_t t = min(t0 + (int64_t)u * VT, A.n - 1);
-            di[u] = __builtin_nontemporal_load(A.dinv + t);
-            xv[u] = __builtin_nontemporal_load(x + t);
-            pv[u] = __builtin_nontemporal_load(p + t);
-            rv[u] = __builtin_nontemporal_load(r + t);
+            di[u] = ld<KEEP>(A.dinv + t);
+            xv[u] = ld<KEEP>(x + t);
+            pv[u] = ld<KEEP>(p + t);
+            rv[u] = ld<KEEP>(r + t);
             wv[u] = w[t];
             own[u] = A.owner[t];
         }
@@ -1105,11 +1119,11 @@ __global__ __launch_bounds__(VT) void k_cg_update(CgUpdateArgs<T> A)
             for (int u = 0; u < UV; ++u) {
                 const int64_t t = t0 + (int64_t)u * VT;
                 if (t >= A.n) break;
-                __builtin_nontemporal_store(fma(alpha, pv[u], xv[u]), x + t);
+                stv<KEEP>(fma(alpha, pv[u], xv[u]), x + t);
                 T ri = rv[u];
                 if (di[u] != T(0)) {
                     ri = fma(-alpha, wv[u], ri);
-                    __builtin_nontemporal_store(ri, r + t);
+                    stv<KEEP>(ri, r + t);
                 }
                 if (own[u]) {
                     rz += (double)ri * (double)(di[u] * ri);
@@ -1125,15 +1139,15 @@ __global__ __launch_bounds__(VT) void k_cg_update(CgUpdateArgs<T> A)
             const int64_t t_end = min(A.n, t0 + (int64_t)UV * VT);
 #pragma unroll
             for (int64_t t = t0 + threadIdx.x; t < t_end; t += VT) {
-                const T di = __builtin_nontemporal_load(A.dinv + t);
-                // x, p, r and dinv are streamed with non-temporal hints (x is touched
+                const T di = ld<KEEP>(A.dinv + t);
+                // unless KEEP, x, p, r and dinv are streamed (x is touched
                 // only here; the others are next read a whole iteration later), so that
                 // the last-level cache keeps w and the gather-scatter's index lists.
-                __builtin_nontemporal_store(fma(alpha, __builtin_nontemporal_load(p + t), __builtin_nontemporal_load(x + t)), x + t);
-                T ri = __builtin_nontemporal_load(r + t);
+                stv<KEEP>(fma(alpha, ld<KEEP>(p + t), ld<KEEP>(x + t)), x + t);
+                T ri = ld<KEEP>(r + t);
                 if (di != T(0)) {
                     ri = fma(-alpha, w[t], ri);
-                    __builtin_nontemporal_store(ri, r + t);
+                    stv<KEEP>(ri, r + t);
                 }
                 if (A.owner[t]) {
                     rz += (double)ri * (double)(di * ri);
@@ -1181,7 +1195,7 @@ __global__ __launch_bounds__(VT) void k_cg_update(CgUpdateArgs<T> A)
 // four consecutive entries of the gather-scatter's list, at any of them
 struct __attribute__((packed, aligned(4))) List4 { uint32_t e[4]; };
 constexpr int GATHER_NM = 1024;  // most partial sums of the matvec that it folds
-template <typename T, int NM>
+template <typename T, int NM, bool KEEP>
 __global__ __launch_bounds__(VT) void k_cg_update_gather(CgUpdateArgs<T> A, unsigned nblk, int run)
 {
     constexpr int UV = UpdChunk<T>::GV;
@@ -1219,10 +1233,10 @@ __global__ __launch_bounds__(VT) void k_cg_update_gather(CgUpdateArgs<T> A, unsi
         for (int u = 0; u < UV; ++u) {
             const int64_t t = min(t0 + (int64_t)u * VT, A.n - 1);
             v[u][0] = w[t];
-            di[u] = __builtin_nontemporal_load(A.dinv + t);
-            xv[u] = __builtin_nontemporal_load(x + t);
-            pv[u] = __builtin_nontemporal_load(p + t);
-            rv[u] = __builtin_nontemporal_load(r + t);
+            di[u] = ld<KEEP>(A.dinv + t);
+            xv[u] = ld<KEEP>(x + t);
+            pv[u] = ld<KEEP>(p + t);
+            rv[u] = ld<KEEP>(r + t);
         }
 #pragma unroll
         for (int u = 0; u < UV; ++u) {
@@ -1285,11 +1299,11 @@ __global__ __launch_bounds__(VT) void k_cg_update_gather(CgUpdateArgs<T> A, unsi
                             if (c + k < cnt) wi += a[k];
                     }
                 }
-                __builtin_nontemporal_store(fma(alpha, pv[u], xv[u]), x + t);
+                stv<KEEP>(fma(alpha, pv[u], xv[u]), x + t);
                 T ri = rv[u];
                 if (di[u] != T(0)) {
                     ri = fma(-alpha, wi, ri);
-                    __builtin_nontemporal_store(ri, r + t);
+                    stv<KEEP>(ri, r + t);
                 }
                 if (own) {
                     rz += (double)ri * (double)(di[u] * ri);
@@ -1978,8 +1992,14 @@ static hipError_t launch_gather(const CgUpdateArgs<T> *A, unsigned grid, hipStre
     const int run = grid > 4096 ? 4 : 2;
     const unsigned per = 8u << run;
     const dim3 g((grid + per - 1) / per * per, A->nfields);
-    if (A->nm == 0) hipLaunchKernelGGL((k_cg_update_gather<T, 0>), g, dim3(VT), 0, st, *A, grid, run);
-    else hipLaunchKernelGGL((k_cg_update_gather<T, GATHER_NM / VT>), g, dim3(VT), 0, st, *A, grid, run);
+    constexpr int NM = GATHER_NM / VT;
+    if (A->keep) {
+        if (A->nm == 0) hipLaunchKernelGGL((k_cg_update_gather<T, 0, true>), g, dim3(VT), 0, st, *A, grid, run);
+        else hipLaunchKernelGGL((k_cg_update_gather<T, NM, true>), g, dim3(VT), 0, st, *A, grid, run);
+    } else {
+        if (A->nm == 0) hipLaunchKernelGGL((k_cg_update_gather<T, 0, false>), g, dim3(VT), 0, st, *A, grid, run);
+        else hipLaunchKernelGGL((k_cg_update_gather<T, NM, false>), g, dim3(VT), 0, st, *A, grid, run);
+    }
     return hipGetLastError();
 }
 template <typename T>
@@ -2078,7 +2098,8 @@ hipError_t sem_launch_cg_update_f64(const CgUpdateArgs<double> *A, unsigned grid
 launch_gather<double>(A, grid, st);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(k_cg_update<double>, dim3(grid, A->nfields), dim3(VT), 0, st, *A);
+    if (A->keep) hipLaunchKernelGGL((k_cg_update<double, true>), dim3(grid, A->nfields), dim3(VT), 0, st, *A);
+    else hipLaunchKernelGGL((k_cg_update<double, false>), dim3(grid, A->nfields), dim3(VT), 0, st, *A);
     return hipGetLastError();
 }
 hipError_t sem_launch_cg_update_f32(const CgUpdateArgs<float> *A, unsigned grid, hipStream_t st)
@@ -2088,7 +2109,8 @@ hipError_t sem_launch_cg_update_f32(const CgUpdateArgs<float> *A, unsigned grid,
 launch_gather<float>(A, grid, st);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(k_cg_update<float>, dim3(grid, A->nfields), dim3(VT), 0, st, *A);
+    if (A->keep) hipLaunchKernelGGL((k_cg_update<float, true>), dim3(grid, A->nfields), dim3(VT), 0, st, *A);
+    else hipLaunchKernelGGL((k_cg_update<float, false>), dim3(grid, A->nfields), dim3(VT), 0, st, *A);
     return hipGetLastError();
 }
 hipError_t sem_launch_assemble_f64(const AssembleArgs<double> *A, hipStream_t st) { return launch_assemble(A, st); }
