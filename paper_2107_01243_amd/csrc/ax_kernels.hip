@@ -500,6 +500,19 @@ __global__ SEM_BOUNDS2((Shape<LX, T>::NT), (Shape<LX, T>::MINW)) void k_cg_matve
         } else {
             const T beta = (T)sc->beta;
             load_g<LX, T, KEEP>(p, A.p + f * A.n + row, act);
+            if (cg_matvec_takes_x(LX, sizeof(T) == 8, NF) && A.x && sc->pend) {
+                const T alpha = (T)sc->alpha;
+                T *xp = A.x + f * A.n + row, x[LX];
+                load_g<LX, T, KEEP>(x, xp, act);
+                if (act) {
+#pragma unroll
+                    for (int k = 0; k < LX; ++k) {
+                        const T v = fma(alpha, p[k], x[k]);
+                        if constexpr (KEEP) xp[k * LX * LX] = v;
+                        else __builtin_nontemporal_store(v, xp + k * LX * LX);
+                    }
+                }
+            }
 #pragma unroll
             for (int i = 0; i < LX; ++i) p[i] = fma(beta, p[i], dinv[i] * r[i]);
             if (act) {
@@ -989,6 +1002,14 @@ __device__ __forceinline__ void cg_lean_body(const DS &D, const CgMatvecArgs<T> 
             } else {
                 const T beta = (T)sc->beta;
                 lpencil<LX, T, true>(p, A.p + fe, t);
+                if (cg_matvec_takes_x(LX, sizeof(T) == 8, NF) && A.x && sc->pend) {
+                    const T alpha = (T)sc->alpha;
+                    T x[LX];
+                    lpencil<LX, T, true>(x, A.x + fe, t);
+#pragma unroll
+                    for (int k = 0; k < LX; ++k)
+                        __builtin_nontemporal_store(fma(alpha, p[k], x[k]), A.x + fe + k * LX * LX + t);
+                }
 #pragma unroll
                 for (int i = 0; i < LX; ++i) p[i] = fma(beta, p[i], dv[i] * r[i]);
 #pragma unroll
@@ -1340,6 +1361,18 @@ __device__ __forceinline__ void tile_body(const Args &A, const T *__restrict__ D
             } else {
                 const T beta = (T)A.scal[f].beta;
                 L.template load<true>(A.p + fe, u);
+                if constexpr (cg_matvec_takes_x(LX, sizeof(T) == 8, NF)) {
+                    if (A.x && A.scal[f].pend) {
+                        const T alpha = (T)A.scal[f].alpha;
+                        T x[H][R];
+                        L.template load<true>(A.x + fe, x);
+#pragma unroll
+                        for (int h = 0; h < H; ++h)
+#pragma unroll
+                            for (int t = 0; t < R; ++t) x[h][t] = fma(alpha, u[h][t], x[h][t]);
+                        L.template store<true>(A.x + fe, x);
+                    }
+                }
 #pragma unroll
                 for (int h = 0; h < H; ++h)
 #pragma unroll

@@ -77,6 +77,7 @@ hipError_t sem_launch_assemble_f64(const AssembleArgs<double> *, hipStream_t);
 hipError_t sem_launch_assemble_f32(const AssembleArgs<float> *, hipStream_t);
 hipError_t sem_launch_gather_map(const uint32_t *, int64_t, const uint8_t *, int32_t *, int64_t, hipStream_t);
 hipError_t sem_launch_cg_alpha(const double *, int64_t, CgScalars *, int, hipStream_t);
+hipError_t sem_launch_cg_flush(double *, const double *, const CgScalars *, int64_t, int, hipStream_t);
 hipError_t sem_launch_cg_finish(const CgFinishArgs *, hipStream_t);
 hipError_t sem_launch_cg1_update(const Cg1UpdateArgs *, hipStream_t);
 hipError_t sem_launch_dots(const DotArgs *, unsigned, hipStream_t);

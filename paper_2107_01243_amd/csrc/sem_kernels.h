@@ -66,7 +66,17 @@ struct CgScalars {
     int stop;       // nonzero: this field's iterates are frozen
     int status;     // 0 running/converged, 1 not converged, 2 breakdown
     int primed;     // single-reduction CG: 0 until the first step length is set
+    int pend;       // x lacks alpha p of the last iteration (see CgMatvecArgs::x)
 };
+
+// Whether the CG matvec can also complete x with the p that it reads (CgMatvecArgs::x),
+// which saves the update's read of p.  Measured, us per FP64 iteration, x in the matvec
+// against x in the update: 8^3 points in 4096 elements 56.3 / 57.3 (three fields 135 / 141),
+// in 13824 182 / 188 (412 / 437), in 32768 421 / 428 (1015 / 1065), 9^3 in 10648 212 / 214
+// (582 / 602), 12^3 in 8000 341 / 354; 7^3 in 17576 with h2 184 / 182, 6^3 in 64000 380 / 372,
+// 5^3 with three fields 610 / 598.  Three fields at lx = 12 have no registers left for x (28
+// spilled: 1047 / 890).  FP32 of one field at lx = 9 139 / 135.
+constexpr bool cg_matvec_takes_x(int lx, bool f64, int nf) { return f64 && lx >= 8 && !(lx == 12 && nf == 3); }
 
 // p = dinv r + beta p;  w = A_L p;  per-workgroup partial sums of p.w.
 // Single-reduction form: u = dinv r;  w = A_L u;  partial sums of u.w.
@@ -85,6 +95,9 @@ struct CgMatvecArgs {
     int64_t nelv;
     const CgScalars *scal;  // one per field
     double *partial;        // [field][workgroup]
+    // two-reduction form: x += alpha p of the iteration before (where pend is set), with the
+    // p that is read here anyway; nullptr: the update has done it
+    T *x = nullptr;
     int keep = 0;           // what an iteration touches fits the last-level cache
     const void *deo = nullptr;  // device copy of the even-odd D of this lx and precision
 };

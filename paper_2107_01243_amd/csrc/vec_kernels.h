@@ -74,7 +74,7 @@ struct CgInitArgs {
 
 template <typename T>
 struct CgUpdateArgs {
-    T *x;
+    T *x;  // nullptr (FP64 only): the matvec completes it
     T *r;
     const T *p;
     const T *w;

@@ -150,6 +150,7 @@ __device__ inline void cg_set_alpha(CgScalars &sc, double pw)
         sc.stop = 1;
         sc.status = 2;
         sc.alpha = 0.0;
+        sc.pend = 0;
     } else {
         sc.alpha = sc.rz / pw;
     }
@@ -1143,7 +1144,7 @@ __global__ __launch_bounds__(VT) void k_cg_update(CgUpdateArgs<T> A)
                 // unless KEEP, x, p, r and dinv are streamed (x is touched
                 // only here; the others are next read a whole iteration later), so that
                 // the last-level cache keeps w and the gather-scatter's index lists.
-                stv<KEEP>(fma(alpha, ld<KEEP>(p + t), ld<KEEP>(x + t)), x + t);
+                if (A.x) stv<KEEP>(fma(alpha, ld<KEEP>(p + t), ld<KEEP>(x + t)), x + t);
                 T ri = ld<KEEP>(r + t);
                 if (di != T(0)) {
                     ri = fma(-alpha, w[t], ri);
@@ -1234,9 +1235,12 @@ __global__ __launch_bounds__(VT) void k_cg_update_gather(CgUpdateArgs<T> A, unsi
             const int64_t t = min(t0 + (int64_t)u * VT, A.n - 1);
             v[u][0] = w[t];
             di[u] = ld<KEEP>(A.dinv + t);
-            xv[u] = ld<KEEP>(x + t);
-            pv[u] = ld<KEEP>(p + t);
             rv[u] = ld<KEEP>(r + t);
+            xv[u] = pv[u] = T(0);
+            if (A.x) {
+                xv[u] = ld<KEEP>(x + t);
+                pv[u] = ld<KEEP>(p + t);
+            }
         }
 #pragma unroll
         for (int u = 0; u < UV; ++u) {
@@ -1267,10 +1271,11 @@ __global__ __launch_bounds__(VT) void k_cg_update_gather(CgUpdateArgs<T> A, unsi
             for (int o = 32; o > 0; o >>= 1) pw += __shfl_xor(pw, o, 64);
             const double rz0 = sc.rz;
             // every workgroup finds the same; on a breakdown none updates anything, and the
-            // stop flag that the first one sets makes no difference to one that reads it
+            // stop flag that the first one sets makes no difference to one that reads it (alpha,
+            // which it also keeps for x, none of them reads)
             ok = pw > 0.0 && isfinite(pw) && isfinite(rz0);
             alpha = ok ? (T)(rz0 / pw) : T(0);
-            if (!ok && lb == 0 && threadIdx.x == 0) cg_set_alpha(sc, pw);
+            if (lb == 0 && threadIdx.x == 0) cg_set_alpha(sc, pw);
         } else {
             alpha = (T)sc.alpha;
         }
@@ -1299,7 +1304,7 @@ __global__ __launch_bounds__(VT) void k_cg_update_gather(CgUpdateArgs<T> A, unsi
                             if (c + k < cnt) wi += a[k];
                     }
                 }
-                stv<KEEP>(fma(alpha, pv[u], xv[u]), x + t);
+                if (A.x) stv<KEEP>(fma(alpha, pv[u], xv[u]), x + t);
                 T ri = rv[u];
                 if (di[u] != T(0)) {
                     ri = fma(-alpha, wi, ri);
@@ -1419,6 +1424,16 @@ __global__ __launch_bounds__(VT) void k_assemble(AssembleArgs<T> A, unsigned nbl
 #pragma unroll
         for (int f = 0; f < NF; ++f) A.out[f * n + t] = dir[u] ? T(0) : s[f];
     }
+}
+
+// x += alpha p of the last iteration for the fields that lack it (see CgMatvecArgs::x).
+__global__ __launch_bounds__(VT) void k_cg_flush(double *x, const double *p, const CgScalars *scal, int64_t n)
+{
+    const int f = blockIdx.y;
+    if (!scal[f].pend) return;
+    const double alpha = scal[f].alpha;
+    for (int64_t t = (int64_t)blockIdx.x * CHUNK + threadIdx.x, t_end = min(n, (int64_t)(blockIdx.x + 1) * CHUNK); t < t_end; t += VT)
+        x[f * n + t] = fma(alpha, p[f * n + t], x[f * n + t]);
 }
 
 // Step lengths from the matvec's partial sums where they are too many for every workgroup
@@ -1571,6 +1586,7 @@ __global__ __launch_bounds__(RT) void k_cg_finish(CgFinishArgs A)
     if (threadIdx.x == 0) {
         s.iter += 1;
         s.rr = rr;
+        s.pend = 1;
         const double rel = sqrt(rr / s.bb);
         if (A.hist && s.iter < A.hist_len) A.hist[(int64_t)f * A.hist_len + s.iter] = rel;
         s.beta = rz / s.rz;
@@ -1798,6 +1814,7 @@ __global__ __launch_bounds__(RT) void k_cg_resume(CgFinishArgs F, const int *red
     for (int f = 0; f < F.nfields; ++f) {
         const double rz = block_sum_fixed<RT>(F.partial + (0 * F.nfields + f) * F.nblk, F.nblk, sh);
         const double rr = block_sum_fixed<RT>(F.partial + (1 * F.nfields + f) * F.nblk, F.nblk, sh);
+        if (threadIdx.x == 0) F.scal[f].pend = 0;  // x is complete at the end of a run
         if (threadIdx.x == 0 && redo[f]) {
             CgScalars &s = F.scal[f];
             s.beta = (s.rz != 0.0) ? s.beta * (rz / s.rz) : 0.0;
@@ -2128,6 +2145,11 @@ hipError_t sem_launch_gather_map(const uint32_t *ent_word, int64_t nent, const u
 hipError_t sem_launch_cg_alpha(const double *partial, int64_t nblk, CgScalars *scal, int nfields, hipStream_t st)
 {
     hipLaunchKernelGGL(k_cg_alpha, dim3(nfields), dim3(RT), 0, st, partial, nblk, scal);
+    return hipGetLastError();
+}
+hipError_t sem_launch_cg_flush(double *x, const double *p, const CgScalars *scal, int64_t n, int nf, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_cg_flush, dim3(stream_grid(n), nf), dim3(VT), 0, st, x, p, scal, n);
     return hipGetLastError();
 }
 hipError_t sem_launch_cg1_update(const Cg1UpdateArgs *A, hipStream_t st)

@@ -1214,3 +1214,35 @@ def test_pcg_kept_in_cache_is_the_streamed_one(nx, lx, nf):
     # the energy norm; with h2 = 1000 the condition number is below 1e3 here
     for x in xs[1:]:
         assert float((x - xs[0]).norm() / xs[0].norm()) <= 2e-7
+
+
+@pytest.mark.parametrize("nx,lx,nf,iters", [(11, 8, 1, 1), (11, 8, 3, 2), (10, 10, 1, 7), (7, 12, 1, 5), (9, 9, 3, 30),
+                                            (7, 12, 3, 6)])
+def test_pcg_x_completed_by_matvec(nx, lx, nf, iters):
+    """Where the matvec completes x (from 2^19 points on, not three fields of lx = 12), a solve
+    stopped after any number of steps returns the iterate of those steps: it equals the
+    oracle's textbook PCG to rounding, x0 and fields that stop at different steps included."""
+    say(f"[x in matvec] nx={nx} lx={lx} nf={nf} iters={iters}")
+    P, O = pair(nx, lx)
+    assert P.n > 1 << 19
+    P.coef.set_helmholtz(1.0, 100.0)
+    O.set_coef(1.0, 100.0)
+    one = to_dev(workloads.uniform(P.n, workloads.SEED_RHS))
+    f = torch.cat([one * (k + 1.0) for k in range(nf)])
+    if nf == 3:
+        f[P.n:2 * P.n] = 0.0  # a field that stops before the first step
+    b = P.assemble(f, nf)
+    x = torch.zeros_like(b)
+    info = sem.pcg_solve(x, b, P.coef, P.msh, P.Xh, P.gs, nfields=nf, rtol=0.0, max_iter=iters, check_every=3)
+    xo = O.pcg(host(b[:P.n]), rtol=0.0, max_iter=iters)[0]
+    for k in range(nf):
+        ref = 0.0 * xo if nf == 3 and k == 1 else (k + 1.0) * xo
+        assert info[k]["iters"] == (0 if nf == 3 and k == 1 else iters)
+        # the iterates are the same recurrence in another order of summation: rounding grows
+        # with the steps, 1e-15 each times a condition number of the step lengths below 1e3
+        assert np.abs(host(x[k * P.n:(k + 1) * P.n]) - ref).max() <= 1e-12 * iters * max(np.abs(ref).max(), 1e-300) + 0.0
+    # continuing from that iterate: the same residual as the solve's own at convergence
+    i2 = sem.pcg_solve(x, b, P.coef, P.msh, P.Xh, P.gs, nfields=nf, rtol=1e-9, use_x0=True)
+    assert all(i["converged"] for i in i2)
+    P.coef.set_helmholtz(1.0, 0.0)
+    O.set_coef(1.0, 0.0)
