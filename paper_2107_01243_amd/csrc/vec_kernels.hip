@@ -335,11 +335,27 @@ __global__ __launch_bounds__(VT) void k_comb(CombArgs A)
     }
 }
 
+// Sum over the wave, to every lane, all 64 active.  Cross-lane moves of the vector unit take a
+// few cycles a step where shuffles through LDS take over a hundred: a step of the coarse solve
+// in one workgroup 3.4 -> 3.1 us at 1331 vertices and 1.24 -> 0.95 us at 343, with the
+// single-reduction form.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_plus(double v)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, true);
+    return v + __hiloint2double(hi, lo);
+}
 __device__ __forceinline__ double wave_sum(double v)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    v = dpp_plus<0x111, 0xf>(v);  // row_shr 1, 2, 4, 8: lane 15 of each row of 16 has its sum
+    v = dpp_plus<0x112, 0xf>(v);
+    v = dpp_plus<0x114, 0xf>(v);
+    v = dpp_plus<0x118, 0xf>(v);
+    v = dpp_plus<0x142, 0xa>(v);  // row_bcast 15 into rows 1 and 3
+    v = dpp_plus<0x143, 0xc>(v);  // row_bcast 31 into rows 2 and 3
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
+                            __builtin_amdgcn_readlane(__double2loint(v), 63));
 }
 
 constexpr int log2up(int m) { return m <= 1 ? 0 : 1 + log2up((m + 1) / 2); }
@@ -658,10 +674,10 @@ __global__ __launch_bounds__(VT) void k_corner(CornerArgs A)
 // dependent memory round trips, not bytes.  Two forms, chosen by nv in
 // sem_launch_coarse_cg:
 //  * k_ccg_small: the whole solve in one workgroup, for systems that its registers and
-//    LDS hold (nv <= 1536, rows of at most 28 entries).  Per step 1.2 us at nv <= 512,
-//    1.6 us at 1000, 3.4 us at 1331, against 5.0-5.8 us of a launch per step.
-//  * k_ccg_start + k_ccg_step: one launch per step in the single-reduction form; 5.9 us
-//    per step at 2197 vertices, 6.4 us at 15,625 (10.6 and 11.1 us with the two
+//    LDS hold (nv <= 1536, rows of at most 28 entries).  Per step 0.95 us at nv <= 512,
+//    1.3 us at 1000, 3.1 us at 1331, against 5.7 us of a launch per step.
+//  * k_ccg_start + k_ccg_step: one launch per step in the single-reduction form; 5.7 us
+//    per step at 2197 vertices, 6.1 us at 15,625 (10.6 and 11.1 us with the two
 //    launches per step of the textbook form; the one-workgroup form needs the matrix
 //    read again every step there, 27 x 12 bytes per row through one compute unit).
 
@@ -679,22 +695,29 @@ constexpr int CCG_SMALL = 3 * CST;    // largest system it takes
 
 constexpr int RESW = 28;    // most entries per row (a hexahedral box has 27)
 
-// Sum over the workgroup in one fixed order, returned to every lane; one barrier.  Two
-// consecutive calls use different buffers, so a lane still reading one call's sums
-// cannot meet the next call's writes.
-__device__ __forceinline__ double small_sum(double v, double *sh)
+// Sums of a and b over the workgroup in one fixed order, returned to every lane; one
+// barrier.  Another must follow before the next call.
+__device__ __forceinline__ void small_sum2(double &a, double &b, double (*sh)[CST / 64])
 {
-    v = wave_sum(v);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    a = wave_sum(a);
+    b = wave_sum(b);
+    if ((threadIdx.x & 63) == 0) {
+        sh[0][threadIdx.x >> 6] = a;
+        sh[1][threadIdx.x >> 6] = b;
+    }
     __syncthreads();
-    double s = sh[0];
+    a = sh[0][0];
+    b = sh[1][0];
 #pragma unroll
-    for (int q = 1; q < CST / 64; ++q) s += sh[q];
-    return s;
+    for (int q = 1; q < CST / 64; ++q) {
+        a += sh[0][q];
+        b += sh[1][q];
+    }
 }
 
-// Whole coarse solve in one workgroup: lane t owns rows t, t + 512, ... (RPT of them)
-// with x, r and p in registers and p shared through LDS for the matrix product.  The
+// Whole coarse solve in one workgroup, in the single-reduction form of k_ccg_step (two
+// barriers a step): lane t owns rows t, t + 512, ... (RPT of them) with the vectors in
+// registers and u = D r shared through LDS for the matrix product.  The
 // matrix stays on the compute unit for all steps: columns packed two to a register,
 // values in registers, and with three rows per lane the last LW entries of each row in
 // LDS (the 256 registers a lane has with two waves per SIMD do not hold them; spilled to
@@ -706,13 +729,12 @@ __global__ __launch_bounds__(CST) void k_ccg_small(CoarseArgs A, int iters, GsAr
         gs_entries_wave(G, (int64_t)(blockIdx.x - 1) * (CST / 64) + (threadIdx.x >> 6));
         return;
     }
-    constexpr int LW = RPT > 2 ? 11 : 0, RW = RESW - LW;
+    constexpr int LW = RPT > 2 ? 12 : 0, RW = RESW - LW;
     __shared__ double ps[CST * RPT];
     __shared__ double sh[2][CST / 64];
     __shared__ double al[LW > 0 ? LW * RPT * CST : 1];
-    double x[RPT], r[RPT], p[RPT], d[RPT], q[RPT], a[RPT][RW];
+    double x[RPT], r[RPT], p[RPT], s[RPT], d[RPT], a[RPT][RW];
     unsigned c2[RPT][RESW / 2];
-    double acc = 0.0;
 #pragma unroll
     for (int h = 0; h < RPT; ++h) {
         const int64_t v = threadIdx.x + h * CST;
@@ -729,44 +751,44 @@ __global__ __launch_bounds__(CST) void k_ccg_small(CoarseArgs A, int iters, GsAr
         r[h] = in ? coarse_rhs(A, v) : 0.0;
         d[h] = in ? A.dinv[v] : 0.0;
         x[h] = 0.0;
-        p[h] = d[h] * r[h];
-        acc = fma(r[h], p[h], acc);
+        p[h] = 0.0;
+        s[h] = 0.0;
     }
-    double rz = small_sum(acc, sh[0]);
+    double gam = 0.0, alpha = 0.0;
     for (int it = 0; it < iters; ++it) {
 #pragma unroll
-        for (int h = 0; h < RPT; ++h) ps[threadIdx.x + h * CST] = p[h];
+        for (int h = 0; h < RPT; ++h) ps[threadIdx.x + h * CST] = d[h] * r[h];
         __syncthreads();
-        acc = 0.0;
+        double w[RPT], g = 0.0, del = 0.0;
 #pragma unroll
         for (int h = 0; h < RPT; ++h) {
-            double s = 0.0;
+            double y = 0.0;
 #pragma unroll
-            for (int w = 0; w < RESW; ++w) {
-                const double av = w < RW ? a[h][w] : al[((w - RW) * RPT + h) * CST + threadIdx.x];
-                s = fma(av, ps[(w & 1) ? c2[h][w / 2] >> 16 : c2[h][w / 2] & 0xffffu], s);
+            for (int k = 0; k < RESW; ++k) {
+                const double av = k < RW ? a[h][k] : al[((k - RW) * RPT + h) * CST + threadIdx.x];
+                y = fma(av, ps[(k & 1) ? c2[h][k / 2] >> 16 : c2[h][k / 2] & 0xffffu], y);
                 // bound the LDS reads in flight (their results would spill)
                 if constexpr (RPT > 2) {
-                    if (w % 7 == 6) __builtin_amdgcn_sched_barrier(0);
+                    if (k % 7 == 6) __builtin_amdgcn_sched_barrier(0);
                 }
             }
-            q[h] = s;
-            acc = fma(p[h], s, acc);
+            w[h] = y;
+            const double u = d[h] * r[h];
+            g = fma(r[h], u, g);
+            del = fma(u, y, del);
         }
-        const double pq = small_sum(acc, sh[1]);
-        const double alpha = (pq > 0.0 && isfinite(pq)) ? rz / pq : 0.0;
-        acc = 0.0;
+        small_sum2(g, del, sh);
+        const double beta = gam != 0.0 ? g / gam : 0.0;  // (0 at the first step)
+        const double den = it > 0 ? del - beta * g / alpha : del;
+        alpha = (den > 0.0 && isfinite(den)) ? g / den : 0.0;
+        gam = g;
 #pragma unroll
         for (int h = 0; h < RPT; ++h) {
+            p[h] = fma(beta, p[h], d[h] * r[h]);
+            s[h] = fma(beta, s[h], w[h]);
             x[h] = fma(alpha, p[h], x[h]);
-            r[h] = fma(-alpha, q[h], r[h]);
-            acc = fma(r[h], d[h] * r[h], acc);
+            r[h] = fma(-alpha, s[h], r[h]);
         }
-        const double rzn = small_sum(acc, sh[0]);
-        const double beta = (rz != 0.0) ? rzn / rz : 0.0;
-        rz = rzn;
-#pragma unroll
-        for (int h = 0; h < RPT; ++h) p[h] = fma(beta, p[h], d[h] * r[h]);
     }
 #pragma unroll
     for (int h = 0; h < RPT; ++h) {
