@@ -28,6 +28,7 @@
 #include <type_traits>
 
 #include "sem_kernels.h"
+#include "sem_wave.h"
 #include "sem_pencil.h"
 
 #ifndef SEM_LX
@@ -537,7 +538,7 @@ __global__ SEM_BOUNDS2((Shape<LX, T>::NT), (Shape<LX, T>::MINW)) void k_cg_matve
         part[f] = s;
     }
     // workgroup reduction in a fixed order (deterministic): the first wave (always
-    // full, NT >= 64) sums strided slices, then a butterfly inside that wave.
+    // full, NT >= 64) sums strided slices, then that wave its lanes.
 #pragma unroll
     for (int q = 0; q < NF; ++q) red[q][tid] = part[q];
     __syncthreads();
@@ -546,8 +547,7 @@ __global__ SEM_BOUNDS2((Shape<LX, T>::NT), (Shape<LX, T>::MINW)) void k_cg_matve
         for (int q = 0; q < NF; ++q) {
             double v = 0.0;
             for (int k = tid; k < S::NT; k += 64) v += red[q][k];
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+            v = wave_sum(v);
             if (tid == 0) A.partial[(int64_t)q * gridDim.x + blockIdx.x] = v;
         }
     }
@@ -1041,8 +1041,7 @@ __device__ __forceinline__ void cg_lean_body(const DS &D, const CgMatvecArgs<T> 
         for (int q = 0; q < NF; ++q) {
             double v = 0.0;
             for (unsigned k = t; k < S::NT; k += 64) v += red[q][k];
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+            v = wave_sum(v);
             if (t == 0) A.partial[(int64_t)q * gridDim.x + blockIdx.x] = v;
         }
     }
@@ -1420,8 +1419,7 @@ __device__ __forceinline__ void tile_body(const Args &A, const T *__restrict__ D
             if (f + 1 < NF) L.template load<false>(A.u + fe + A.n, u);
         L.template store<false>(A.w + fe, w);
         if constexpr (CG) {
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) dot += __shfl_xor(dot, off, 64);
+            dot = wave_sum(dot);
             if (L.c + 16 * L.g == 0) red[f][L.wave] = dot;
         }
     }

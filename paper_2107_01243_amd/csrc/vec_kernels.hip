@@ -15,6 +15,7 @@
 #include <stdint.h>
 
 #include "sem_kernels.h"
+#include "sem_wave.h"
 #include "vec_kernels.h"
 
 #ifndef SEM_GS_XCD
@@ -75,7 +76,7 @@ __device__ __forceinline__ void stv(T v, T *p)
 
 // Sum `nblk` partials in a fixed order inside one workgroup of NTH lanes: lane t
 // accumulates entries t, t+NTH, ... into four interleaved accumulators (loads in
-// flight), combines them, then a fixed binary tree in LDS.  Deterministic for a
+// flight), combines them, then a fixed binary tree, in LDS down to a wave's width.  Deterministic for a
 // given (nblk, NTH).  Returns the sum to every lane.
 template <int NTH>
 __device__ double block_sum_fixed(const double *part, int64_t nblk, double *sh)
@@ -92,11 +93,11 @@ __device__ double block_sum_fixed(const double *part, int64_t nblk, double *sh)
     for (; q < nblk; q += NTH) a0 += part[q];
     sh[tid] = (a0 + a1) + (a2 + a3);
     __syncthreads();
-    for (int w = NTH / 2; w > 0; w >>= 1) {
+    for (int w = NTH / 2; w >= 64; w >>= 1) {
         if (tid < w) sh[tid] += sh[tid + w];
         __syncthreads();
     }
-    const double r = sh[0];
+    const double r = wave_sum(sh[tid & 63]);
     __syncthreads();
     return r;
 }
@@ -333,29 +334,6 @@ __global__ __launch_bounds__(VT) void k_comb(CombArgs A)
             if (i < A.l) s = fma(A.c[i], A.V[i * A.ld + t], s);
         A.y[t] = s;
     }
-}
-
-// Sum over the wave, to every lane, all 64 active.  Cross-lane moves of the vector unit take a
-// few cycles a step where shuffles through LDS take over a hundred: a step of the coarse solve
-// in one workgroup 3.4 -> 3.1 us at 1331 vertices and 1.24 -> 0.95 us at 343, with the
-// single-reduction form.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_plus(double v)
-{
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, true);
-    return v + __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ double wave_sum(double v)
-{
-    v = dpp_plus<0x111, 0xf>(v);  // row_shr 1, 2, 4, 8: lane 15 of each row of 16 has its sum
-    v = dpp_plus<0x112, 0xf>(v);
-    v = dpp_plus<0x114, 0xf>(v);
-    v = dpp_plus<0x118, 0xf>(v);
-    v = dpp_plus<0x142, 0xa>(v);  // row_bcast 15 into rows 1 and 3
-    v = dpp_plus<0x143, 0xc>(v);  // row_bcast 31 into rows 2 and 3
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
-                            __builtin_amdgcn_readlane(__double2loint(v), 63));
 }
 
 constexpr int log2up(int m) { return m <= 1 ? 0 : 1 + log2up((m + 1) / 2); }
@@ -655,8 +633,7 @@ __global__ __launch_bounds__(VT) void k_corner(CornerArgs A)
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
         double x = acc[c];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+        x = wave_sum(x);
         if (lane == 0) sh[c][wave] = x;
     }
     __syncthreads();
@@ -961,8 +938,7 @@ __global__ __launch_bounds__(VT) void k_elem_gb(const double *G, const double *B
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
         double x = s[d];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+        x = wave_sum(x);
         if (lane == 0) sh[d][wave] = x;
     }
     __syncthreads();
@@ -1092,8 +1068,8 @@ __global__ __launch_bounds__(RT) void k_cg_start(CgFinishArgs A)
 
 // x += alpha p; r -= alpha w (not on Dirichlet points); partials of (r, dinv r), (r, r).
 // Workgroup b streams the contiguous chunk of UV * VT points starting at b * UV * VT
-// (UV per precision: see upd_chunk); its two partials are reduced by wave
-// butterflies and then the four waves in order (deterministic, one barrier).
+// (UV per precision: see upd_chunk); its two partials are reduced per wave
+// and then over the four waves in order (deterministic, one barrier).
 template <typename T, bool KEEP>
 __global__ __launch_bounds__(VT) void k_cg_update(CgUpdateArgs<T> A)
 {
@@ -1179,11 +1155,8 @@ __global__ __launch_bounds__(VT) void k_cg_update(CgUpdateArgs<T> A)
             }
         }
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        rz += __shfl_xor(rz, off, 64);
-        rr += __shfl_xor(rr, off, 64);
-    }
+    rz = wave_sum(rz);
+    rr = wave_sum(rr);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (lane == 0) {
         sh[0][wave] = rz;
@@ -1289,8 +1262,7 @@ __global__ __launch_bounds__(VT) void k_cg_update_gather(CgUpdateArgs<T> A, unsi
         if constexpr (NM > 0) {
             __syncthreads();
             pw = (sp[lane] + sp[lane + 128]) + (sp[lane + 64] + sp[lane + 192]);
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) pw += __shfl_xor(pw, o, 64);
+            pw = wave_sum(pw);
             const double rz0 = sc.rz;
             // every workgroup finds the same; on a breakdown none updates anything, and the
             // stop flag that the first one sets makes no difference to one that reads it (alpha,
@@ -1339,11 +1311,8 @@ __global__ __launch_bounds__(VT) void k_cg_update_gather(CgUpdateArgs<T> A, unsi
             }
         }
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        rz += __shfl_xor(rz, o, 64);
-        rr += __shfl_xor(rr, o, 64);
-    }
+    rz = wave_sum(rz);
+    rr = wave_sum(rr);
     if (lane == 0) {
         sh[0][wave] = rz;
         sh[1][wave] = rr;
@@ -1483,8 +1452,7 @@ __global__ __launch_bounds__(RT) void k_cg_alpha(const double *part, int64_t nbl
             s[k] = (v[0] + v[VT]) + (v[2 * VT] + v[3 * VT]);
         }
         double pw = (s[0] + s[2]) + (s[1] + s[3]);
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) pw += __shfl_xor(pw, o, 64);
+        pw = wave_sum(pw);
         if (tid == 0) cg_set_alpha(scal[f], pw);
     }
 }
@@ -1492,7 +1460,7 @@ __global__ __launch_bounds__(RT) void k_cg_alpha(const double *part, int64_t nbl
 // Single-reduction CG update (Chronopoulos-Gear): with u = dinv r recomputed on the
 // fly, p = u + beta p, s = w + beta s (s = A p carried as a vector), x += alpha p,
 // r -= alpha s on non-Dirichlet points, and the partial sums of the new (r, dinv r)
-// and (r, r) over owned points (wave butterflies, then the waves in order).  They are
+// and (r, r) over owned points (per wave, then the waves in order).  They are
 // reduced together with the next matvec's (u, A u): one reduction phase per iteration.
 __global__ __launch_bounds__(VT) void k_cg1_update(Cg1UpdateArgs A)
 {
@@ -1528,11 +1496,8 @@ __global__ __launch_bounds__(VT) void k_cg1_update(Cg1UpdateArgs A)
             }
         }
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        rz += __shfl_xor(rz, off, 64);
-        rr += __shfl_xor(rr, off, 64);
-    }
+    rz = wave_sum(rz);
+    rr = wave_sum(rr);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (lane == 0) {
         sh[0][wave] = rz;
@@ -1554,7 +1519,7 @@ __global__ __launch_bounds__(VT) void k_cg1_update(Cg1UpdateArgs A)
 // End of one CG iteration: beta = rz_new / rz_old, convergence and iteration cap.
 // Two sums of nblk partials in one pass, fixed order: lane t accumulates entries
 // t, t + NTH, ... of both arrays (four interleaved accumulators each, eight loads in
-// flight), a butterfly per wave, then the NTH / 64 wave sums in order.  Every lane
+// flight), a sum per wave, then the NTH / 64 wave sums in order.  Every lane
 // gets both results.
 template <int NTH>
 __device__ void block_sum2_fixed(const double *pa, const double *pb, int64_t nblk, double *sh, double &ra,
@@ -1575,11 +1540,8 @@ __device__ void block_sum2_fixed(const double *pa, const double *pb, int64_t nbl
         b[0] += pb[q];
     }
     double x = (a[0] + a[1]) + (a[2] + a[3]), y = (b[0] + b[1]) + (b[2] + b[3]);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        x += __shfl_xor(x, off, 64);
-        y += __shfl_xor(y, off, 64);
-    }
+    x = wave_sum(x);
+    y = wave_sum(y);
     if ((tid & 63) == 0) {
         sh[2 * (tid >> 6)] = x;
         sh[2 * (tid >> 6) + 1] = y;
