@@ -323,9 +323,24 @@ __device__ __forceinline__ void load_row(T (&r)[LX], const T *__restrict__ p, bo
 // Geometric-factor pencils are streamed once per application and the six planes
 // (6 words per point) never fit the 256 MB last-level cache at production sizes, so
 // they are read with non-temporal loads: this keeps the cache for the vectors
-// (u, w, the Krylov vectors) that are reused between launches.  KEEP: a CG iteration whose
-// whole set fits the cache reads and writes it plainly, and then finds it there.
-template <int LX, typename T, bool KEEP = false>
+// (u, w, the Krylov vectors) that are reused between launches.  KEEP: plain loads, for a set
+// that fits the cache and is found there by the next launch, and where STREAM is unset: a
+// line read non-temporally is dropped after its first use, and rows of lx^2 values that are
+// not whole lines share lines between a wave's loads, which are then fetched again.
+// Measured, us, non-temporal -> plain, one field of 25 million points, Poisson: FP32 lx = 5
+// 170 -> 140, 6 186 -> 149, 7 181 -> 150, 9 172 -> 144, 8 144 -> 159; 20 million: lx = 10
+// 130 -> 116, 11 139 -> 126, 13 135 -> 121, 15 181 -> 176, 16 150 -> 147 (with h1 and h2 fields
+// 175 -> 179; three fields 360 -> 330).  FP64 lx = 5 294 -> 282, 6 284 -> 297, 7 293 -> 295,
+// 8 282 -> 314, 9 270 -> 275; lx = 10 252 -> 237, 11 266 -> 260, 13 266 -> 256, 14 274 -> 273,
+// 16 254 -> 260; three fields lx = 10 452 -> 464, 11 482 -> 487.  (STREAM is not for the CG
+// matvecs, which pass their vectors to the next kernels through the cache: FP32 of one field
+// at lx = 9 gains, 135 -> 123 us an iteration, but at lx = 12 196 -> 217, of three at lx = 9
+// 282 -> 304, FP64 at lx = 5 231 -> 247.)
+template <int LX, typename T, int NF>
+constexpr bool STREAM = sizeof(T) == 4 ? (LX & (LX - 1)) == 0 && !(LX == 16 && NF == 3)
+                                       : LX != 5 && !(NF == 1 && (LX == 10 || LX == 11 || LX == 13));
+
+template <int LX, typename T, bool KEEP>
 __device__ __forceinline__ void load_g(T (&r)[LX], const T *__restrict__ p, bool act)
 {
     if (!act) {
@@ -410,7 +425,7 @@ __device__ __forceinline__ void add_mass(const RowCoef<LX, T, GEN> &c, const T (
 
 // ------------------------------------------------------------------ w = A_L u
 // NF fields share one read of G (and B, h1, h2).
-template <int LX, typename T, int NF, bool GEN>
+template <int LX, typename T, int NF, bool GEN, bool KEEP>
 __global__ SEM_BOUNDS2((Shape<LX, T>::NT), (Shape<LX, T>::MINW)) void k_ax_helm(AxArgs<T> A, DEo<LX, T> D)
 {
     using S = Shape<LX, T>;
@@ -426,7 +441,7 @@ __global__ SEM_BOUNDS2((Shape<LX, T>::NT), (Shape<LX, T>::MINW)) void k_ax_helm(
 
     T g[6][LX];
 #pragma unroll
-    for (int f = 0; f < 6; ++f) load_g<LX, T>(g[f], A.G + f * A.n + row, act);
+    for (int f = 0; f < 6; ++f) load_g<LX, T, KEEP>(g[f], A.G + f * A.n + row, act);
     RowCoef<LX, T, GEN> c;
     load_coef<LX, T, GEN>(c, A, row, act);
     // the next field's row is loaded while the current one is processed
@@ -912,17 +927,17 @@ __device__ __forceinline__ void ax_lean_body(const DS &D, const AxArgs<T> &A)
     T *hp = park + t, *mp = park + (H1F ? LX * LX * LX : 0) + t;
     if constexpr (HOLD) {
 #pragma unroll
-        for (int q = 0; q < 6; ++q) lpencil<LX, T, true>(g[q], Ge + q * A.n, t);
+        for (int q = 0; q < 6; ++q) lpencil<LX, T, STREAM<LX, T, NF>>(g[q], Ge + q * A.n, t);
         T v[LX];
         if constexpr (H1F) {
-            lpencil<LX, T, true>(v, h1e, t);
+            lpencil<LX, T, STREAM<LX, T, NF>>(v, h1e, t);
 #pragma unroll
             for (int k = 0; k < LX; ++k) hp[k * (LX * LX)] = v[k];
         }
         if constexpr (MASS) {
-            lpencil<LX, T, true>(v, Be, t);
+            lpencil<LX, T, STREAM<LX, T, NF>>(v, Be, t);
             T v2[LX];
-            if constexpr (kind_mass(KIND) == 2) lpencil<LX, T, true>(v2, h2e, t);
+            if constexpr (kind_mass(KIND) == 2) lpencil<LX, T, STREAM<LX, T, NF>>(v2, h2e, t);
 #pragma unroll
             for (int k = 0; k < LX; ++k) mp[k * (LX * LX)] = (kind_mass(KIND) == 2 ? v2[k] : A.h2s) * v[k];
         }
@@ -939,7 +954,7 @@ __device__ __forceinline__ void ax_lean_body(const DS &D, const AxArgs<T> &A)
                 grad_nb<LX, T, NB>(D, u, lds.buf, a, b, ur, us, ut);
             }
             if constexpr (HOLD) apply_G_regs<LX, T, KIND>(g, hp, A.h1s, ur, us, ut);
-            else apply_G_lean<LX, T, KIND, NF == 1>(fresh(Ge), H1F ? fresh(h1e) : h1e, A.h1s, A.n, t, ur, us, ut);
+            else apply_G_lean<LX, T, KIND, NF == 1 && STREAM<LX, T, NF>>(fresh(Ge), H1F ? fresh(h1e) : h1e, A.h1s, A.n, t, ur, us, ut);
             div_nb<LX, T, NB>(D, ur, us, ut, lds.buf, a, b, w);
         }
         if constexpr (HOLD && MASS) {
@@ -1313,7 +1328,7 @@ __device__ __forceinline__ void tile_body(const Args &A, const T *__restrict__ D
     if constexpr (!CG) L.template load<false>(A.u + e0, u);
     T G[6][H][R];
 #pragma unroll
-    for (int q = 0; q < 6; ++q) L.template load<true>(A.G + q * A.n + e0, G[q]);
+    for (int q = 0; q < 6; ++q) L.template load<CG || STREAM<LX, T, NF>>(A.G + q * A.n + e0, G[q]);
     // h1 and h2 B at the lane's points: with several fields in LDS (each lane reads back
     // its own values), since next to G they do not fit the registers
     constexpr bool H1F = kind_h1f(KIND), MASS = kind_mass(KIND) != 0, PARK = NF > 1;
@@ -1321,7 +1336,7 @@ __device__ __forceinline__ void tile_body(const Args &A, const T *__restrict__ D
     T h1[H1F && !PARK ? H : 1][R], mb[MASS && !PARK ? H : 1][R];
     if constexpr (H1F) {
         T v[H][R];
-        L.template load<PARK>(A.h1 + e0, v);
+        L.template load<PARK && (CG || STREAM<LX, T, NF>)>(A.h1 + e0, v);
 #pragma unroll
         for (int h = 0; h < H; ++h)
 #pragma unroll
@@ -1332,8 +1347,8 @@ __device__ __forceinline__ void tile_body(const Args &A, const T *__restrict__ D
     }
     if constexpr (MASS) {
         T v[H][R], m2[H][R];
-        L.template load<PARK>(A.B + e0, v);
-        if constexpr (kind_mass(KIND) == 2) L.template load<PARK>(A.h2 + e0, m2);
+        L.template load<PARK && (CG || STREAM<LX, T, NF>)>(A.B + e0, v);
+        if constexpr (kind_mass(KIND) == 2) L.template load<PARK && (CG || STREAM<LX, T, NF>)>(A.h2 + e0, m2);
 #pragma unroll
         for (int h = 0; h < H; ++h)
 #pragma unroll
@@ -1467,7 +1482,7 @@ __device__ __forceinline__ void adj_lean_body(const DS &D, const AdjArgs<T> &A)
         lpencil<LX, T, false>(u, A.u + e0, t);
         grad_lean<LX, T>(D, u, s0, s1, a, b, wr, ws, wt);
     }
-    apply_G_lean<LX, T, KPOISSON, true>(fresh(A.G + e0), (const T *)nullptr, T(1), A.n, t, wr, ws, wt);
+    apply_G_lean<LX, T, KPOISSON, STREAM<LX, T, 1>>(fresh(A.G + e0), (const T *)nullptr, T(1), A.n, t, wr, ws, wt);
     T vr[LX], vs[LX], vt[LX];
     {
         T v[LX];
@@ -1509,7 +1524,7 @@ __global__ SEM_BOUNDS2((Shape<LX, T>::NT), (Shape<LX, T>::MINW)) void k_ax_adjoi
     load_row<LX, T>(v, A.v + row, act);
     T g[6][LX];
 #pragma unroll
-    for (int f = 0; f < 6; ++f) load_g<LX, T>(g[f], A.G + f * A.n + row, act);
+    for (int f = 0; f < 6; ++f) load_g<LX, T, !STREAM<LX, T, 1>>(g[f], A.G + f * A.n + row, act);
     T ur[LX], us[LX], ut[LX], vr[LX], vs[LX], vt[LX];
     grad<LX, T>(D, u, s0, s1, a, b, ur, us, ut);
     grad<LX, T>(D, v, s0, s1, a, b, vr, vs, vt);
@@ -1692,8 +1707,18 @@ void launch_ax_nf(const sem::AxArgs<T> &A, const sem::DEo<SEM_LX, T> &Dm, unsign
         });
     } else {
         const bool gen = A.h1 || A.h2 || A.h2s != T(0);
-        if (gen) hipLaunchKernelGGL((sem::k_ax_helm<SEM_LX, T, NF, true>), dim3(grid), dim3(S::NT), 0, st, A, Dm);
-        else hipLaunchKernelGGL((sem::k_ax_helm<SEM_LX, T, NF, false>), dim3(grid), dim3(S::NT), 0, st, A, Dm);
+        auto go = [&](auto keep) {
+            constexpr bool KEEP = decltype(keep)::value;
+            if (gen) hipLaunchKernelGGL((sem::k_ax_helm<SEM_LX, T, NF, true, KEEP>), dim3(grid), dim3(S::NT), 0, st, A, Dm);
+            else hipLaunchKernelGGL((sem::k_ax_helm<SEM_LX, T, NF, false, KEEP>), dim3(grid), dim3(S::NT), 0, st, A, Dm);
+        };
+        if constexpr (sem::STREAM<SEM_LX, T, NF>) {
+            // what one application touches fits the last-level cache: 2.5 million points, lx = 8
+            // FP64 27 -> 25 us, three Helmholtz fields (260 MB) 51 -> 48
+            const int words = 6 + (A.h1 != nullptr) + (A.h2 || A.h2s != T(0)) + (A.h2 != nullptr) + 2 * NF;
+            if (!A.keep || A.n * (int64_t)sizeof(T) * words > 300000000) return go(std::false_type{});
+        }
+        go(std::true_type{});
     }
 }
 

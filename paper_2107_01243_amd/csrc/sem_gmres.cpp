@@ -367,17 +367,19 @@ sem_status sem_schwarz_apply(double *z, const double *r, sem_coef coef, sem_mesh
 
 // ------------------------------------------------------------------ flexible GMRES
 // w = mask QQ^T A_L z; up to a million points, where launches are what costs, assembled out
-// of the scratch vector W.w in one pass (5 us; gather-scatter and mask 8.5).
+// of the scratch vector W.w in one pass (5 us; gather-scatter and mask 8.5).  G is streamed
+// also where it would fit the cache, which the basis vectors need (960 elements, lx = 6: 4.30 ms a
+// solve, 4.47 with G kept).
 static sem_status gmres_apply(sem_coef c, sem_gs g, double *w, const double *z, hipStream_t st)
 {
     const int32_t *pmap = c->n <= (1 << 20) ? g->d_pmap.load(std::memory_order_acquire) : nullptr;
     if (pmap) {
-        SEM_TRY(launch_ax<double>(c, c->ws.w, z, 1, st));
+        SEM_TRY(launch_ax<double>(c, c->ws.w, z, 1, st, 0));
         const AssembleArgs<double> A{w, c->ws.w, pmap, g->d_ent_word, c->msh->d_dir, c->n, 1};
         HIP_TRY(sem_launch_assemble_f64(&A, st));
         return SEM_OK;
     }
-    SEM_TRY(launch_ax<double>(c, w, z, 1, st));
+    SEM_TRY(launch_ax<double>(c, w, z, 1, st, 0));
     SEM_TRY(launch_gs<double>(w, 1, g, nullptr, nullptr, st));
     HIP_TRY(sem_launch_mask(w, 0, c->msh->d_dir_idx, (int64_t)c->msh->dir_idx.size(), c->n, 1, st));
     return SEM_OK;

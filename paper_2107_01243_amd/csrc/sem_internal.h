@@ -378,9 +378,10 @@ sem_status launch_gs(T *u, int nf, sem_gs g, const CgScalars *skip, const AlphaJ
 }
 
 template <typename T>
-sem_status launch_ax(sem_coef c, T *w, const T *u, int nf, hipStream_t st)
+sem_status launch_ax(sem_coef c, T *w, const T *u, int nf, hipStream_t st, int keep = 1)
 {
     AxArgs<T> A;
+    A.keep = keep;
     A.w = w;
     A.u = u;
     A.n = c->n;

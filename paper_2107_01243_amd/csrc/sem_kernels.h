@@ -51,6 +51,7 @@ struct AxArgs {
     int64_t n;    // points per field
     int64_t nelv;
     const void *deo = nullptr;  // device copy of the even-odd D of this lx and precision
+    int keep = 1;  // may be left to the last-level cache where it fits
 };
 
 // Per-field scalars of one CG solve, resident in device memory.
