@@ -62,7 +62,8 @@ PROFILE_LX12_MD = os.path.join(ROOT, "profiles", "velocity3_48x48x48_lx12_kernel
 PRESSURE_RESTART = 10
 PROFILE_SOURCES = ["paper_2107_01243_amd/csrc/ax_kernels.hip", "paper_2107_01243_amd/csrc/vec_kernels.hip",
                    "paper_2107_01243_amd/csrc/schwarz_kernels.hip", "paper_2107_01243_amd/csrc/sem_pencil.h",
-                   "paper_2107_01243_amd/csrc/sem_kernels.h", "paper_2107_01243_amd/csrc/vec_kernels.h"]
+                   "paper_2107_01243_amd/csrc/sem_kernels.h", "paper_2107_01243_amd/csrc/vec_kernels.h",
+                   "paper_2107_01243_amd/csrc/sem_wave.h"]
 
 
 def profiled_traffic(kernel, md=None):
@@ -263,10 +264,10 @@ def cpu_baseline(wl, gpu_iters, full_solve=False, mixed=None):
     return out
 
 
-LX12_KERNELS = {"ax_f64_poisson_1field": "sem::k_ax_helm_lean<12, double, 1, 0>",
-                "ax_f64_helmholtz_1field": "sem::k_ax_helm_lean<12, double, 1, 1>",
-                "ax_f64_helmholtz_3field": "sem::k_ax_helm_lean<12, double, 3, 1>",
-                "ax_f32_helmholtz_3field": "sem::k_ax_helm_lean<12, float, 3, 1>",
+LX12_KERNELS = {"ax_f64_poisson_1field": "sem::k_ax_helm_tile<12, double, 1, 0>",
+                "ax_f64_helmholtz_1field": "sem::k_ax_helm_tile<12, double, 1, 2>",
+                "ax_f64_helmholtz_3field": "sem::k_ax_helm_tile<12, double, 3, 2>",
+                "ax_f32_helmholtz_3field": "sem::k_ax_helm_lean<12, float, 3, 2>",
                 "adjoint_f64": "sem::k_ax_adjoint_lean<12, double>"}
 LX12_WORDS = {"ax_f64_poisson_1field": (8, 8), "ax_f64_helmholtz_1field": (9, 8),
               "ax_f64_helmholtz_3field": (13, 8), "ax_f32_helmholtz_3field": (13, 4),
@@ -743,7 +744,7 @@ def main():
             log(f"projected solve {k + 1}/{a.proj_steps}: {proj_rec[-1][0]:.3f}s, {pinfo['iters']} it")
         del proj
 
-    traffic = profiled_traffic("sem::k_ax_helm<8, double, 1, false>")
+    traffic = profiled_traffic("sem::k_ax_helm<8, double, 1, false, false>")
     ax_s = sum(rec["ax_ms"]) / 1e3 / (a.reps * a.steps)
     gdofs = P.n / ax_s / 1e9
     achieved = AX_WORDS_PER_POINT * 8 * P.n / ax_s / 1e9
@@ -785,7 +786,7 @@ def main():
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                      "traffic_unit": "bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-scaled)",
                      "algorithmic_bytes": AX_WORDS_PER_POINT * 8 * P.n,
-                     "kernel": "k_ax_helm<8, double, 1, false>", "bytes_per_point": AX_WORDS_PER_POINT * 8},
+                     "kernel": "k_ax_helm<8, double, 1, false, false>", "bytes_per_point": AX_WORDS_PER_POINT * 8},
     }
     if rec["mixed_s"]:
         out.update({
@@ -814,11 +815,11 @@ def main():
                                 "frac": round(bpp * P.n / t / 1e9 / HBM_PEAK_GBS, 4)}
                             for k, (t, bpp) in kern.items()}
     out["pcg_fp64_gpoint_iters_per_s"] = round(P.n * out["pcg_fp64_iters"] / out["pcg_fp64_solve_s"] / 1e9, 3)
-    # algorithmic HBM bytes of one FP64 PCG iteration: matvec 11 words per point (r, dinv,
-    # p_old, six G in; p, w out), update 7 words + the owner byte (x, p, r, w, dinv in;
-    # x, r out), gather-scatter 22 B per shared entry (index 4, metadata 2, value in and out)
+    # algorithmic HBM bytes of one FP64 PCG iteration: matvec 13 words per point (r, dinv,
+    # p_old, x, six G in; p, w, x out), update 4 words + the owner byte (r, w, dinv in; r out),
+    # gather-scatter 20 B per shared entry (index 4, value in and out)
     npairs, _, nbe = P.gs.sizes()
-    it_bytes = P.n * (11 * 8 + 7 * 8 + 1) + (2 * npairs + nbe) * 22
+    it_bytes = P.n * (13 * 8 + 4 * 8 + 1) + (2 * npairs + nbe) * 20
     it_gbs = it_bytes / (out["pcg_fp64_ms_per_iter"] / 1e3) / 1e9
     out["pcg_fp64_iter_bytes"] = int(it_bytes)
     out["pcg_fp64_GBs"] = round(it_gbs, 1)

@@ -1066,7 +1066,8 @@ __global__ __launch_bounds__(RT) void k_cg_start(CgFinishArgs A)
     }
 }
 
-// x += alpha p; r -= alpha w (not on Dirichlet points); partials of (r, dinv r), (r, r).
+// x += alpha p (where A.x is set: see CgMatvecArgs::x); r -= alpha w (not on Dirichlet
+// points); partials of (r, dinv r), (r, r).
 // Workgroup b streams the contiguous chunk of UV * VT points starting at b * UV * VT
 // (UV per precision: see upd_chunk); its two partials are reduced per wave
 // and then over the four waves in order (deterministic, one barrier).
