@@ -468,7 +468,7 @@ __global__ SEM_BOUNDS2((Shape<LX, T>::NT), (Shape<LX, T>::MINW)) void k_ax_helm(
 // Single-reduction CG (CG1 = true, Chronopoulos-Gear): u = dinv r (not stored),
 // w = A_L u.  Either way the workgroup's partial sum of v . w (v = p or u) is written:
 // v^T A v by the unassembled identity of Eq. 10.
-template <int LX, typename T, int NF, bool GEN, bool CG1, bool KEEP>
+template <int LX, typename T, int NF, bool GEN, bool CG1, bool KEEP, bool FOLD>
 __global__ SEM_BOUNDS2((Shape<LX, T>::NT), (Shape<LX, T>::MINW)) void k_cg_matvec(CgMatvecArgs<T> A, DEo<LX, T> D)
 {
     using S = Shape<LX, T>;
@@ -488,7 +488,10 @@ __global__ SEM_BOUNDS2((Shape<LX, T>::NT), (Shape<LX, T>::MINW)) void k_cg_matve
     bool live = false;
 #pragma unroll
     for (int f = 0; f < NF; ++f) live = live || !A.scal[f].stop;
-    if (!live) return;
+    if (!live) {
+        if (FOLD && blockIdx.x == 0 && tid < NF) A.scal_out[tid] = A.scal[tid];
+        return;
+    }
 
     T g[6][LX];
 #pragma unroll
@@ -502,19 +505,57 @@ __global__ SEM_BOUNDS2((Shape<LX, T>::NT), (Shape<LX, T>::MINW)) void k_cg_matve
     // 0.763 -> 0.687 s per FP64 solve at 32^3 x lx=8)
     load_g<LX, T, KEEP>(dinv, A.dinv + row, act);
 
+    // FOLD: the end of the previous iteration, by every workgroup for itself, while G is on
+    // its way (the sums of k_cg_finish, in its order); the first one hands the state on.  It
+    // takes out a launch, 3.5 us of dependent accesses: 6^3 points in 64 elements 15.8 -> 13.7 us
+    // per iteration, in 512 15.9 -> 15.0.  With three fields it is slower, 21.1 -> 22.0 and 25.4 ->
+    // 26.8, where the three ends come one after the other.
+    static_assert(!FOLD || NF == 1, "one field");
+    __shared__ double us[FOLD ? 8 : 1];
+    __shared__ double fb[FOLD ? NF : 1];
+    __shared__ int fs[FOLD ? NF : 1];
+    if constexpr (FOLD) {
+        const int lane = tid & 63, wave = tid >> 6;
+        constexpr int NW = S::NT / 64;  // whole waves
+        for (int f = 0; f < NF; ++f) {
+            if (wave < NW) {
+                for (int c = wave; c < 8; c += NW) {  // four chunks of 64 of each of the two sums
+                    const int q = (c & 3) * 64 + lane;
+                    const double v = q < A.nup ? A.upart[((int64_t)(c >> 2) * NF + f) * A.nup + q] : 0.0;
+                    const double t = wave_sum(v);
+                    if (lane == 0) us[c] = t;
+                }
+            }
+            __syncthreads();
+            if (tid == 0) {
+                CgScalars sc = A.scal[f];
+                if (!sc.stop && sc.primed)
+                    cg_end_iteration(sc, ((us[0] + us[1]) + us[2]) + us[3], ((us[4] + us[5]) + us[6]) + us[7]);
+                fb[f] = sc.beta;
+                fs[f] = sc.stop;
+                if (blockIdx.x == 0) {
+                    sc.primed = 0;
+                    A.scal_out[f] = sc;
+                }
+            }
+            __syncthreads();
+        }
+        if (fs[0]) return;
+    }
+
     double part[NF];
 #pragma unroll 1
     for (int f = 0; f < NF; ++f) {
         part[f] = 0.0;
         const CgScalars *sc = A.scal + f;
-        if (sc->stop) continue;  // uniform: every lane reads the same flag
+        if (FOLD ? fs[f] : sc->stop) continue;  // uniform: every lane reads the same flag
         T r[LX], p[LX];
         load_g<LX, T, KEEP>(r, A.r + f * A.n + row, act);
         if constexpr (CG1) {
 #pragma unroll
             for (int i = 0; i < LX; ++i) p[i] = dinv[i] * r[i];
         } else {
-            const T beta = (T)sc->beta;
+            const T beta = (T)(FOLD ? fb[f] : sc->beta);
             load_g<LX, T, KEEP>(p, A.p + f * A.n + row, act);
             if (cg_matvec_takes_x(LX, sizeof(T) == 8, NF) && A.x && sc->pend) {
                 const T alpha = (T)sc->alpha;
@@ -1752,19 +1793,22 @@ void launch_cg_nf(const sem::CgMatvecArgs<T> &A, const sem::DEo<SEM_LX, T> &Dm, 
         });
     } else {
         const bool gen = A.h1 || A.h2 || A.h2s != T(0);
-        auto go = [&](auto keep) {
-            constexpr bool KEEP = decltype(keep)::value;
+        auto go = [&](auto keep, auto fold) {
+            constexpr bool KEEP = decltype(keep)::value, FOLD = decltype(fold)::value;
             if (gen)
-                hipLaunchKernelGGL((sem::k_cg_matvec<SEM_LX, T, NF, true, CG1, KEEP>), dim3(grid), dim3(S::NT), 0, st, A,
-                                   Dm);
+                hipLaunchKernelGGL((sem::k_cg_matvec<SEM_LX, T, NF, true, CG1, KEEP, FOLD>), dim3(grid), dim3(S::NT), 0, st,
+                                   A, Dm);
             else
-                hipLaunchKernelGGL((sem::k_cg_matvec<SEM_LX, T, NF, false, CG1, KEEP>), dim3(grid), dim3(S::NT), 0, st, A,
-                                   Dm);
+                hipLaunchKernelGGL((sem::k_cg_matvec<SEM_LX, T, NF, false, CG1, KEEP, FOLD>), dim3(grid), dim3(S::NT), 0, st,
+                                   A, Dm);
         };
         if constexpr (!CG1) {
-            if (A.keep) return go(std::true_type{});
+            if constexpr (sizeof(T) == 8 && NF == 1) {
+                if (A.nup > 0) return go(std::true_type{}, std::true_type{});
+            }
+            if (A.keep) return go(std::true_type{}, std::false_type{});
         }
-        go(std::false_type{});
+        go(std::false_type{}, std::false_type{});
     }
 }
 

@@ -261,6 +261,7 @@ sem_status ensure_work(sem_coef c, int nf, bool mixed)
     W.nb = nb;
     SEM_TRY(dalloc(&W.partial, W.partial_len));
     SEM_TRY(dalloc(&W.scal, nf));
+    SEM_TRY(dalloc(&W.scal2, nf));
     SEM_TRY(dalloc(&W.job64, 1));
     SEM_TRY(dalloc(&W.job32, 1));
     SEM_TRY(dalloc(&W.job_cg1, 1));

@@ -149,6 +149,17 @@ sem_status cg_iterate(sem_coef c, Work &W, sem_gs g, int nf, T *x, T *r, T *p, T
     gather_in_update(U, c, W, g);
     const unsigned ug = sem_update_grid(n, f64 ? 0 : 1, U.pmap != nullptr);
     CgFinishArgs F{U.partial, (int64_t)ug, W.scal, hist, hist_len, nf};
+    // small problems of one field: the end of an iteration in the next matvec (k_cg_matvec has
+    // the figures), two launches per iteration and one before the host looks at the state
+    const bool fold = f64 && nf == 1 && c->lx < 10 && W.scal2 && U.nm > 0 && ug <= 256;
+    if (fold) {
+        M.nup = (int)ug;
+        M.upart = U.partial;
+        M.scal_out = W.scal2;
+        U.scal = W.scal2;
+        U.scal_out = W.scal;
+        F.settle = 1;
+    }
     if (check_every < 1) check_every = 1;
     const int64_t max_batches = (int64_t)(max_iter + check_every - 1) / check_every + 2;
     // first poll right after initialisation (b = 0 or an exact initial guess)
@@ -169,8 +180,9 @@ sem_status cg_iterate(sem_coef c, Work &W, sem_gs g, int nf, T *x, T *r, T *p, T
             SEM_TRY(assemble_or_alpha(U, c, W, g, st));
             if constexpr (sizeof(T) == 8) HIP_TRY(sem_launch_cg_update_f64(&U, ug, st));
             else HIP_TRY(sem_launch_cg_update_f32(&U, ug, st));
-            HIP_TRY(sem_launch_cg_finish(&F, st));
+            if (!fold) HIP_TRY(sem_launch_cg_finish(&F, st));
         }
+        if (fold) HIP_TRY(sem_launch_cg_finish(&F, st));
         HIP_TRY(hipMemcpyAsync(W.h_scal, W.scal, sizeof(CgScalars) * nf, hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
     }

@@ -236,6 +236,7 @@ struct Work {
     int64_t partial_len = 0;
     int64_t nb = 0;                 // partial sums per row of W.partial
     CgScalars *scal = nullptr;      // device [fields]
+    CgScalars *scal2 = nullptr;     // the same, where the matvec ends an iteration; may be nullptr
     CgScalars *h_scal = nullptr;    // pinned mirror
     AlphaJob *job64 = nullptr;      // device, for the FP64 matvec grid
     AlphaJob *job32 = nullptr;      // device, for the FP32 matvec grid
@@ -257,7 +258,7 @@ struct Work {
     {
         dfree(r); dfree(p); dfree(w); dfree(z); dfree(q);
         dfree(r32); dfree(y32); dfree(p32); dfree(w32); dfree(ri32);
-        dfree(partial); dfree(scal); dfree(job64); dfree(job32); dfree(dots); dfree(fcg); dfree(done); dfree(rel);
+        dfree(partial); dfree(scal); dfree(scal2); dfree(job64); dfree(job32); dfree(dots); dfree(fcg); dfree(done); dfree(rel);
         dfree(job_cg1); dfree(s);
         dfree(gm); dfree(gm_part); dfree(gm_out);
         if (gm_hout) (void)hipHostFree(gm_hout);

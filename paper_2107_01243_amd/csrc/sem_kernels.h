@@ -2,6 +2,7 @@
 // of libsem (internal; not part of the C ABI).
 #pragma once
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 namespace sem {
@@ -66,9 +67,25 @@ struct CgScalars {
     int max_iter;
     int stop;       // nonzero: this field's iterates are frozen
     int status;     // 0 running/converged, 1 not converged, 2 breakdown
-    int primed;     // single-reduction CG: 0 until the first step length is set
+    int primed;     // single-reduction CG: 0 until the first step length is set; with the end of
+                    // an iteration in the matvec: 1 while an update's sums wait for it
     int pend;       // x lacks alpha p of the last iteration (see CgMatvecArgs::x)
 };
+
+// End of one CG iteration: beta = rz_new / rz_old, convergence and iteration cap.
+__host__ __device__ inline void cg_end_iteration(CgScalars &s, double rz, double rr)
+{
+    s.iter += 1;
+    s.rr = rr;
+    s.pend = 1;
+    const double rel = sqrt(rr / s.bb);
+    s.beta = rz / s.rz;
+    s.rz = rz;
+    if (s.rtol > 0.0 && rel <= s.rtol) s.stop = 1;
+    else if (!isfinite(rr) || !isfinite(rz)) { s.stop = 1; s.status = 2; }
+    else if (rz == 0.0) s.stop = 1;
+    else if (s.iter >= s.max_iter) { s.stop = 1; s.status = (s.rtol > 0.0) ? 1 : 0; }
+}
 
 // Whether the CG matvec can also complete x with the p that it reads (CgMatvecArgs::x),
 // which saves the update's read of p.  Measured, us per FP64 iteration, x in the matvec
@@ -99,6 +116,12 @@ struct CgMatvecArgs {
     // two-reduction form: x += alpha p of the iteration before (where pend is set), with the
     // p that is read here anyway; nullptr: the update has done it
     T *x = nullptr;
+    // nup > 0 (FP64, one field, lx < 10): the end of the previous iteration is done here, from the update's nup partial
+    // sums per field of (r, z) and (r, r) (upart: [2][field][nup]); scal is then only read, and
+    // the state goes to scal_out, where the next update takes it (see cg_end_iteration)
+    CgScalars *scal_out = nullptr;
+    const double *upart = nullptr;
+    int nup = 0;
     int keep = 0;           // what an iteration touches fits the last-level cache
     const void *deo = nullptr;  // device copy of the even-odd D of this lx and precision
 };

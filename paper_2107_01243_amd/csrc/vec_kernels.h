@@ -94,6 +94,8 @@ struct CgUpdateArgs {
     // length (nm = 0: it is in scal)
     const double *mpart = nullptr;
     int64_t nm = 0;
+    // with nm: the state is read from scal and, with the step length, written here
+    CgScalars *scal_out = nullptr;
     int keep = 0;  // what an iteration touches fits the last-level cache
 };
 
@@ -116,6 +118,7 @@ struct CgFinishArgs {
     double *hist;     // optional [field][hist_len] relative residual history
     int hist_len;
     int nfields;
+    int settle = 0;   // only fields whose update's sums wait (primed), which is then cleared
 };
 
 // Per-field state of the reliable-update mixed solve (device resident).

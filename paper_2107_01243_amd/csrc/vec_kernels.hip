@@ -1221,6 +1221,7 @@ __global__ __launch_bounds__(VT) void k_cg_update_gather(CgUpdateArgs<T> A, unsi
     }
     CgScalars &sc = A.scal[f];
     double rz = 0.0, rr = 0.0;
+    if (NM > 0 && A.scal_out && sc.stop && lb == 0 && threadIdx.x == 0) A.scal_out[f] = sc;
     if (!sc.stop) {
         T *x = A.x + off, *r = A.r + off;
         const T *p = A.p + off, *w = A.w + off;
@@ -1270,7 +1271,16 @@ __global__ __launch_bounds__(VT) void k_cg_update_gather(CgUpdateArgs<T> A, unsi
             // which it also keeps for x, none of them reads)
             ok = pw > 0.0 && isfinite(pw) && isfinite(rz0);
             alpha = ok ? (T)(rz0 / pw) : T(0);
-            if (lb == 0 && threadIdx.x == 0) cg_set_alpha(sc, pw);
+            if (lb == 0 && threadIdx.x == 0) {
+                if (A.scal_out) {
+                    CgScalars S = sc;
+                    cg_set_alpha(S, pw);
+                    S.primed = !S.stop;
+                    A.scal_out[f] = S;
+                } else {
+                    cg_set_alpha(sc, pw);
+                }
+            }
         } else {
             alpha = (T)sc.alpha;
         }
@@ -1564,22 +1574,14 @@ __global__ __launch_bounds__(RT) void k_cg_finish(CgFinishArgs A)
     __shared__ double sh[2 * (RT / 64)];
     const int f = blockIdx.x;
     CgScalars &s = A.scal[f];
-    if (s.stop) return;
+    if (s.stop || (A.settle && !s.primed)) return;
     double rz, rr;
     block_sum2_fixed<RT>(A.partial + (0 * A.nfields + f) * A.nblk, A.partial + (1 * A.nfields + f) * A.nblk, A.nblk, sh,
                          rz, rr);
     if (threadIdx.x == 0) {
-        s.iter += 1;
-        s.rr = rr;
-        s.pend = 1;
-        const double rel = sqrt(rr / s.bb);
-        if (A.hist && s.iter < A.hist_len) A.hist[(int64_t)f * A.hist_len + s.iter] = rel;
-        s.beta = rz / s.rz;
-        s.rz = rz;
-        if (s.rtol > 0.0 && rel <= s.rtol) s.stop = 1;
-        else if (!isfinite(rr) || !isfinite(rz)) { s.stop = 1; s.status = 2; }
-        else if (rz == 0.0) s.stop = 1;
-        else if (s.iter >= s.max_iter) { s.stop = 1; s.status = (s.rtol > 0.0) ? 1 : 0; }
+        cg_end_iteration(s, rz, rr);
+        if (A.settle) s.primed = 0;
+        if (A.hist && s.iter < A.hist_len) A.hist[(int64_t)f * A.hist_len + s.iter] = sqrt(rr / s.bb);
     }
 }
 

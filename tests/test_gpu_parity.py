@@ -1085,6 +1085,8 @@ def _glued(P, seed, copies):
     (7, 7, 1, None),
     (16, 3, 3, None),
     (11, 9, 1, None),            # the step length in its own launch
+    (6, 8, 3, None),             # 216 of at most 256 partial sums for the matvec to fold
+    (8, 8, 1, None),             # 512: the end of an iteration in its own launch
     (20, 5, 1, None),            # the largest of the small range
     (4, 6, 1, (2, 3, 4, 5, 8, 9)),
     (4, 6, 3, (2, 13, 16)),      # the most copies the lists take
