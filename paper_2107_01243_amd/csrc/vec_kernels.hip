@@ -1219,9 +1219,9 @@ __global__ __launch_bounds__(VT) void k_cg_update_gather(CgUpdateArgs<T> A, unsi
         pw = full ? (a[0] + a[1]) + (a[2] + a[3]) : (a[0] + a[1]) + a[2];
         sp[threadIdx.x] = pw;
     }
-    CgScalars &sc = A.scal[f];
+    const CgScalars &sc = A.scal[f];
     double rz = 0.0, rr = 0.0;
-    if (NM > 0 && A.scal_out && sc.stop && lb == 0 && threadIdx.x == 0) A.scal_out[f] = sc;
+    if (NM > 0 && sc.stop && lb == 0 && threadIdx.x == 0) A.scal_out[f] = sc;
     if (!sc.stop) {
         T *x = A.x + off, *r = A.r + off;
         const T *p = A.p + off, *w = A.w + off;
@@ -1266,20 +1266,16 @@ __global__ __launch_bounds__(VT) void k_cg_update_gather(CgUpdateArgs<T> A, unsi
             pw = (sp[lane] + sp[lane + 128]) + (sp[lane + 64] + sp[lane + 192]);
             pw = wave_sum(pw);
             const double rz0 = sc.rz;
-            // every workgroup finds the same; on a breakdown none updates anything, and the
-            // stop flag that the first one sets makes no difference to one that reads it (alpha,
-            // which it also keeps for x, none of them reads)
+            // every workgroup finds the same, and on a breakdown none updates anything; the state
+            // with the step length or the breakdown in it goes to another place than the one
+            // that they all read, so the branch and the barrier in it are uniform
             ok = pw > 0.0 && isfinite(pw) && isfinite(rz0);
             alpha = ok ? (T)(rz0 / pw) : T(0);
             if (lb == 0 && threadIdx.x == 0) {
-                if (A.scal_out) {
-                    CgScalars S = sc;
-                    cg_set_alpha(S, pw);
-                    S.primed = !S.stop;
-                    A.scal_out[f] = S;
-                } else {
-                    cg_set_alpha(sc, pw);
-                }
+                CgScalars S = sc;
+                cg_set_alpha(S, pw);
+                S.primed = !S.stop;
+                A.scal_out[f] = S;
             }
         } else {
             alpha = (T)sc.alpha;
@@ -1573,14 +1569,19 @@ __global__ __launch_bounds__(RT) void k_cg_finish(CgFinishArgs A)
 {
     __shared__ double sh[2 * (RT / 64)];
     const int f = blockIdx.x;
-    CgScalars &s = A.scal[f];
-    if (s.stop || (A.settle && !s.primed)) return;
+    const CgScalars &from = A.src ? A.src[f] : A.scal[f];
+    if (from.stop || (A.settle && !from.primed)) {
+        if (A.src && threadIdx.x == 0) A.scal[f] = from;
+        return;
+    }
     double rz, rr;
     block_sum2_fixed<RT>(A.partial + (0 * A.nfields + f) * A.nblk, A.partial + (1 * A.nfields + f) * A.nblk, A.nblk, sh,
                          rz, rr);
     if (threadIdx.x == 0) {
+        CgScalars s = from;
         cg_end_iteration(s, rz, rr);
-        if (A.settle) s.primed = 0;
+        s.primed = 0;
+        A.scal[f] = s;
         if (A.hist && s.iter < A.hist_len) A.hist[(int64_t)f * A.hist_len + s.iter] = sqrt(rr / s.bb);
     }
 }
@@ -1992,7 +1993,8 @@ static unsigned arn_grid(int64_t n)
 template <typename T>
 static hipError_t launch_gather(const CgUpdateArgs<T> *A, unsigned grid, hipStream_t st)
 {
-    if (A->nm > GATHER_NM || (A->nm > 0 && !A->mpart)) return hipErrorInvalidValue;
+    if (A->nm > GATHER_NM || (A->nm > 0 && (!A->mpart || !A->scal_out || A->scal_out == A->scal)))
+        return hipErrorInvalidValue;
     const int run = grid > 4096 ? 4 : 2;
     const unsigned per = 8u << run;
     const dim3 g((grid + per - 1) / per * per, A->nfields);

@@ -1248,3 +1248,49 @@ def test_pcg_x_completed_by_matvec(nx, lx, nf, iters):
     assert all(i["converged"] for i in i2)
     P.coef.set_helmholtz(1.0, 0.0)
     O.set_coef(1.0, 0.0)
+
+
+@pytest.mark.parametrize("nx,lx,nf", [(3, 6, 1), (8, 8, 1), (3, 10, 1), (3, 6, 3), (2, 10, 3), (11, 9, 3),
+                                      (11, 10, 1)])
+def test_breakdown_of_one_field(nx, lx, nf):
+    """A field whose first search direction has p.Ap < 0 ends with BREAKDOWN before any step,
+    x = 0, and the others go on: three steps equal to the oracle's (1e-12 a step, as where the
+    matvec completes x).  In the forms of the update: the end of an iteration in the matvec
+    (6^3 points in 27 elements) or in its own launch (512 elements: 512 sums of the update;
+    lx >= 10; three fields), the step length in its own launch (1331 elements of 10^3 points:
+    1331 sums of the matvec), the allocation-free solve, which gives the same bits, and the
+    FP32 iteration."""
+    say(f"[breakdown] nx={nx} lx={lx} nf={nf}")
+    P, O = pair(nx, lx, 0.0)
+    h2 = -45.0  # below minus the lowest eigenvalue of the box, 3 pi^2
+    P.coef.set_helmholtz(1.0, h2)
+    O.set_coef(1.0, h2)
+    s = torch.sin(math.pi * P.xyz.view(3, -1)).prod(0)  # (p = dinv b: the lowest mode)
+    dinv = sem.jacobi_inverse(P.coef, P.msh, P.Xh, P.gs)
+    smooth = torch.where(dinv != 0.0, s / dinv, 0.0)
+    P.gs.op(smooth)
+    smooth /= P.mult
+    rough = [P.assemble(to_dev(workloads.uniform(P.n, k))) for k in workloads.SEED_RHS_FIELDS]
+    bs = [smooth] if nf == 1 else [rough[0], smooth, rough[2]]
+    bad = nf // 2
+    b = torch.cat(bs)
+    args = (P.coef, P.msh, P.Xh, P.gs)
+    kw = dict(nfields=nf, rtol=0.0, max_iter=3, raise_on_fail=False)
+    xs = []
+    for solve in (sem.pcg_solve, sem.pcg_solve_noalloc):
+        if solve is sem.pcg_solve_noalloc and P.n * nf > sem.NOALLOC_MAX_POINTS:
+            continue
+        x = torch.full_like(b, float("nan"))
+        info = solve(x, b, *args, **kw)
+        assert [i["iters"] for i in info] == [0 if f == bad else 3 for f in range(nf)]
+        with pytest.raises(sem.SemError, match=f"BREAKDOWN.*field {bad}|field {bad}.*BREAKDOWN"):
+            solve(x, b, *args, **{**kw, "raise_on_fail": True})
+        for f in range(nf):
+            ref = np.zeros(P.n) if f == bad else O.pcg(host(bs[f]), rtol=0.0, max_iter=3)[0]
+            assert np.abs(host(x[f * P.n:(f + 1) * P.n]) - ref).max() <= 3e-12 * np.abs(ref).max()
+        xs.append(x)
+    assert torch.equal(xs[0], xs[-1])
+    with pytest.raises(sem.SemError, match="BREAKDOWN"):
+        sem.pcg_solve(x, b, *args, nfields=nf, rtol=1e-8, max_iter=3, mixed="reliable")
+    P.coef.set_helmholtz(1.0, 0.0)
+    O.set_coef(1.0, 0.0)
