@@ -167,10 +167,13 @@ __device__ void fold_job(const AlphaJob &J, int nfields, double *sh)
             const double pw = block_sum_fixed<NTH>(J.partial + f * J.nblk, J.nblk, sh);
             if (threadIdx.x == 0) cg_set_alpha(J.scal[f], pw);
         } else {
-            const double d = block_sum_fixed<NTH>(J.partial + f * J.nblk, J.nblk, sh);
             CgScalars &sc = J.scal[f];
+            // read before the barriers of the first sum, and so by every wave before lane 0
+            // writes the state: the branch below holds barriers too
+            const bool primed = sc.primed != 0;
+            const double d = block_sum_fixed<NTH>(J.partial + f * J.nblk, J.nblk, sh);
             double g = sc.rz, rr = sc.rr;  // before the first step: from the start kernels
-            if (sc.primed) {               // uniform: every lane reads the same flag
+            if (primed) {
                 g = block_sum_fixed<NTH>(J.partial2 + (0 * nfields + f) * J.nblk2, J.nblk2, sh);
                 rr = block_sum_fixed<NTH>(J.partial2 + (1 * nfields + f) * J.nblk2, J.nblk2, sh);
             }
