@@ -1996,6 +1996,7 @@ static unsigned arn_grid(int64_t n)
 template <typename T>
 static hipError_t launch_gather(const CgUpdateArgs<T> *A, unsigned grid, hipStream_t st)
 {
+    if ((int64_t)grid * VT * UpdChunk<T>::GV < A->n) return hipErrorInvalidValue;
     if (A->nm > GATHER_NM || (A->nm > 0 && (!A->mpart || !A->scal_out || A->scal_out == A->scal)))
         return hipErrorInvalidValue;
     const int run = grid > 4096 ? 4 : 2;
@@ -2102,22 +2103,16 @@ hipError_t sem_launch_cg_start(const CgFinishArgs *A, hipStream_t st)
 }
 hipError_t sem_launch_cg_update_f64(const CgUpdateArgs<double> *A, unsigned grid, hipStream_t st)
 {
+    if (A->pmap) return launch_gather<double>(A, grid, st);
     if ((int64_t)grid * VT * UpdChunk<double>::UV < A->n) return hipErrorInvalidValue;
-    if (A->pmap) {
-launch_gather<double>(A, grid, st);
-        return hipGetLastError();
-    }
     if (A->keep) hipLaunchKernelGGL((k_cg_update<double, true>), dim3(grid, A->nfields), dim3(VT), 0, st, *A);
     else hipLaunchKernelGGL((k_cg_update<double, false>), dim3(grid, A->nfields), dim3(VT), 0, st, *A);
     return hipGetLastError();
 }
 hipError_t sem_launch_cg_update_f32(const CgUpdateArgs<float> *A, unsigned grid, hipStream_t st)
 {
+    if (A->pmap) return launch_gather<float>(A, grid, st);
     if ((int64_t)grid * VT * UpdChunk<float>::UV < A->n) return hipErrorInvalidValue;
-    if (A->pmap) {
-launch_gather<float>(A, grid, st);
-        return hipGetLastError();
-    }
     if (A->keep) hipLaunchKernelGGL((k_cg_update<float, true>), dim3(grid, A->nfields), dim3(VT), 0, st, *A);
     else hipLaunchKernelGGL((k_cg_update<float, false>), dim3(grid, A->nfields), dim3(VT), 0, st, *A);
     return hipGetLastError();

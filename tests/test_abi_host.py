@@ -141,3 +141,36 @@ def test_host_error_paths():
         sem.box_mesh(2, 2, 2, 20, 0.0)
     with pytest.raises(sem.SemError):
         sem.box_mesh(0, 2, 2, 4, 0.0)
+
+
+class _CgUpdateArgs(C.Structure):  # sem::CgUpdateArgs
+    _fields_ = [(nm, C.c_void_p) for nm in ("x", "r", "p", "w", "dinv", "owner", "scal", "partial")] + \
+               [("n", C.c_int64), ("nfields", C.c_int), ("pmap", C.c_void_p), ("ent_word", C.c_void_p),
+                ("mpart", C.c_void_p), ("nm", C.c_int64), ("scal_out", C.c_void_p), ("keep", C.c_int)]
+
+
+@pytest.mark.parametrize("f32", [0, 1])
+@pytest.mark.parametrize("n", [1, 5000, 1 << 20])
+def test_gathering_update_refuses_what_it_cannot_run(L, f32, n):
+    """The launcher of the CG update that gathers returns hipErrorInvalidValue (1), before any
+    launch, for a grid that does not cover the points at the points per lane of this form, for
+    more partial sums of the matvec than it folds, and for sums without a place to read them
+    from or to write the state to."""
+    launch = L.sem_launch_cg_update_f32 if f32 else L.sem_launch_cg_update_f64
+    launch.argtypes, launch.restype = [C.POINTER(_CgUpdateArgs), C.c_uint, C.c_void_p], C.c_int
+    L.sem_update_grid.argtypes, L.sem_update_grid.restype = [C.c_int64, C.c_int, C.c_int], C.c_uint
+    L.sem_gather_fold_max.restype = C.c_int64
+    most = L.sem_gather_fold_max()
+    grid = L.sem_update_grid(n, f32, 1)
+
+    def args(**kw):
+        A = _CgUpdateArgs(**{nm: 4096 for nm, t in _CgUpdateArgs._fields_ if t is C.c_void_p})
+        A.n, A.nfields, A.nm, A.scal_out = n, 1, 1, 8192
+        for k, v in kw.items():
+            setattr(A, k, v)
+        return C.byref(A)
+
+    assert launch(args(), grid - 1, None) == 1
+    assert launch(args(nm=0), grid - 1, None) == 1
+    for bad in (dict(nm=most + 1), dict(mpart=None), dict(scal_out=None), dict(scal_out=4096)):
+        assert launch(args(**bad), grid, None) == 1, bad
