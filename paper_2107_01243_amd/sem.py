@@ -12,6 +12,7 @@ from dataclasses import dataclass
 
 import numpy as np
 import torch
+from torch.autograd import forward_ad
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libsem.so")
@@ -326,6 +327,13 @@ def mask(u, msh: Mesh, nfields: int = 1, stream=None):
     return u
 
 
+def _plain(t):
+    """Whether t's values are its memory in order and no autograd mode follows it, so that a
+    library pass that reads it stands for a copy of it."""
+    return (t.is_contiguous() and not t.is_neg() and not (t.requires_grad and torch.is_grad_enabled())
+            and forward_ad.unpack_dual(t).tangent is None)
+
+
 def _assemble(b, u, msh: Mesh, gs: GS, nfields: int):
     _check(_L.sem_assemble(_ptr(b), _ptr(u), nfields, msh._h, gs._h, _dtype(u), _stream()))
     return b
@@ -549,12 +557,14 @@ class BoxProblem:
 
     def assemble(self, f_local, nfields=1):
         """b = mask QQ^T f (copy)."""
-        if isinstance(f_local, torch.Tensor) and f_local.requires_grad and torch.is_grad_enabled():
-            b = f_local.clone()  # the copy stays in the caller's graph
-            self.gs.op(b, nfields)
-            return mask(b, self.msh, nfields)
-        _dev(f_local, nfields * self.msh.n, "u")
-        return _assemble(torch.empty_like(f_local), f_local, self.msh, self.gs, nfields)
+        if _plain(f_local):
+            _dev(f_local, nfields * self.msh.n, "u")
+            return _assemble(torch.empty_like(f_local), f_local, self.msh, self.gs, nfields)
+        # a clone of a strided or expanded tensor is contiguous, one of a tensor with a gradient
+        # or a tangent keeps it
+        b = f_local.clone()
+        self.gs.op(b, nfields)
+        return mask(b, self.msh, nfields)
 
     def solve(self, b, nfields=1, **kw):
         x = torch.zeros_like(b)

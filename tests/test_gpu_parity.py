@@ -1317,3 +1317,33 @@ def test_single_reduction_fields_of_their_own_start(nx, lx):
             assert rel_inf(X[k], xo) <= 1e-11
     P.coef.set_helmholtz(1.0, 0.0)
     O.set_coef(1.0, 0.0)
+
+
+@pytest.mark.parametrize("nx,nf,dt", [(2, 1, torch.float64), (3, 3, torch.float32), (20, 1, torch.float32)])
+def test_assembly_of_views(nx, nf, dt):
+    """assemble() takes what its copy takes: columns of a matrix, every other value, an expanded
+    value, a negated view; and a tensor with a tangent, which the result keeps.  Equal to
+    the bit to the assembly of a contiguous copy; a transposed matrix, whose copy is not
+    contiguous, is refused."""
+    say(f"[assembly of views] nx={nx} nf={nf} {dt}")
+    P = sem.BoxProblem.build(nx, 6, 0.05)
+    n = P.n * nf
+    X = to_dev(workloads.uniform(3 * n, workloads.SEED_RHS), dt).view(n, 3)
+    c = torch.tensor([1.25], dtype=dt, device=DEV)
+    for v in (X[:, 0], X.view(-1)[::3], X[:, 2], c.expand(n),
+              torch._neg_view(X[:, 1].contiguous())):
+        u = v.clone()
+        assert u.is_contiguous()
+        ref = u.clone()
+        P.gs.op(ref, nf)
+        sem.mask(ref, P.msh, nf)
+        assert torch.equal(P.assemble(v, nf), ref) and torch.equal(P.assemble(u, nf), ref)
+        assert torch.equal(v, u)
+    with torch.autograd.forward_ad.dual_level():
+        d = torch.autograd.forward_ad.make_dual(u, u + 1.0)
+        out, tan = torch.autograd.forward_ad.unpack_dual(P.assemble(d, nf))
+        assert torch.equal(out, ref) and torch.equal(tan, u + 1.0)
+    with pytest.raises(ValueError, match="contiguous"):
+        P.assemble(u.view(2, -1).t(), nf)
+    with pytest.raises(ValueError):
+        P.assemble(X[:-1, 0], nf)
