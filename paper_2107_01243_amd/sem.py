@@ -550,18 +550,18 @@ class BoxProblem:
     def apply(self, u, nfields=1):
         """mask QQ^T A_L u."""
         w = self.ax(u, nfields)
-        if self.n <= 1 << 20:  # bound by its launches: one less of them
+        if self.n <= 1 << 20 and self.gs.msh is self.msh:  # bound by its launches: one less of them
             return _assemble(torch.empty_like(w), w, self.msh, self.gs, nfields)
         self.gs.op(w, nfields)
         return mask(w, self.msh, nfields)
 
     def assemble(self, f_local, nfields=1):
         """b = mask QQ^T f (copy)."""
-        if _plain(f_local):
+        if _plain(f_local) and self.gs.msh is self.msh:
             _dev(f_local, nfields * self.msh.n, "u")
             return _assemble(torch.empty_like(f_local), f_local, self.msh, self.gs, nfields)
         # a clone of a strided or expanded tensor is contiguous, one of a tensor with a gradient
-        # or a tangent keeps it
+        # or a tangent keeps it; and the two passes take a gs of one mesh and the walls of another
         b = f_local.clone()
         self.gs.op(b, nfields)
         return mask(b, self.msh, nfields)

@@ -1347,3 +1347,23 @@ def test_assembly_of_views(nx, nf, dt):
         P.assemble(u.view(2, -1).t(), nf)
     with pytest.raises(ValueError):
         P.assemble(X[:-1, 0], nf)
+
+
+@pytest.mark.parametrize("lx", [4, 7])
+def test_assembly_with_another_meshs_gs(lx):
+    """A problem whose gs was built for another mesh of the same ids (a mesh with other walls):
+    assemble() and apply() sum with the gs and mask with the problem's own mesh."""
+    say(f"[assembly, another mesh's gs] lx={lx}")
+    P = sem.BoxProblem.build(3, lx, 0.05)
+    walls = np.zeros(P.n, np.uint8)
+    walls[np.asarray(P.glb) % 5 == 0] = 1
+    msh = sem.Mesh(P.msh.nelv, lx, P.glb, walls)
+    Q = sem.BoxProblem(P.Xh, msh, P.gs, sem.Coef(P.Xh, msh, xyz=P.xyz), P.xyz, P.glb, walls, 3, lx)
+    u = to_dev(workloads.uniform(3 * P.n, workloads.SEED_RHS))
+    for nf in (1, 3):
+        v = u[:nf * P.n]
+        for f, out in ((v, Q.assemble(v, nf)), (Q.ax(v, nf), Q.apply(v, nf))):
+            ref = f.clone()
+            P.gs.op(ref, nf)
+            assert torch.equal(out, sem.mask(ref, msh, nf))
+            assert float(out.view(nf, -1)[:, to_dev(walls, torch.bool)].abs().max()) == 0.0
