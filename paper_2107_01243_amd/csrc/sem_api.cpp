@@ -124,18 +124,34 @@ sem_status gs_upload(sem_gs g)
     return SEM_OK;
 }
 
-// Per-point map of the kernels that gather (see CgUpdateArgs).  Not built (the solver then
-// runs the gather-scatter) when a point has more than 16 copies, when an entry's position
-// does not fit its word, or when memory is short.
+// While it lives, calls of this thread that a capture forbids (an allocation, a wait) neither
+// fail for, nor invalidate, a capture of another stream.
+struct RelaxedCaptureMode {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCaptureMode() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~RelaxedCaptureMode() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+// Per-point map of the kernels that gather (see CgUpdateArgs), built once per handle on the
+// stream st (not under capture), which is waited for.  Not built (the callers then run the
+// gather-scatter) when a point has more than 16 copies, when an entry's position does not fit
+// its word, or when memory is short; that is not tried again, since each later call would
+// pay for the failing allocation.
 sem_status gs_gather_map(sem_gs g, hipStream_t st)
 {
     const auto &m = g->m;
     std::lock_guard<std::mutex> lock(g->pmap_mu);
     if (g->pmap_tried || m.n == 0) return SEM_OK;
     const int64_t nent = (int64_t)m.ent_idx.size();
+    const RelaxedCaptureMode relaxed;
     int32_t *pmap = nullptr;
-    if (g->entries && m.big_idx.empty() && m.max_group <= 16 && nent < (1 << 26) - 64 &&
-        hipMalloc((void **)&pmap, m.n * sizeof(int32_t)) == hipSuccess) {
+    if (g->entries && m.big_idx.empty() && m.max_group <= 16 && nent < (1 << 26) - 64) {
+        if (hipMalloc((void **)&pmap, m.n * sizeof(int32_t)) != hipSuccess) {
+            (void)hipGetLastError();
+            pmap = nullptr;
+        }
+    }
+    if (pmap) {
         hipError_t e = sem_launch_gather_map(g->d_ent_word, nent, g->d_owner, pmap, m.n, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);  // (other streams may use it next)
         if (e != hipSuccess) {
@@ -144,7 +160,6 @@ sem_status gs_gather_map(sem_gs g, hipStream_t st)
         }
         g->d_pmap.store(pmap, std::memory_order_release);
     }
-    (void)hipGetLastError();  // of a failed allocation
     g->pmap_tried = true;
     return SEM_OK;
 }

@@ -1367,3 +1367,30 @@ def test_assembly_with_another_meshs_gs(lx):
             P.gs.op(ref, nf)
             assert torch.equal(out, sem.mask(ref, msh, nf))
             assert float(out.view(nf, -1)[:, to_dev(walls, torch.bool)].abs().max()) == 0.0
+
+
+def test_first_assembly_beside_a_capture():
+    """The first assembly on a handle, which builds its point map, on one stream while another
+    stream is captured: it is done, and the capture stays valid."""
+    say("[first assembly beside a capture]")
+    P, Q = sem.BoxProblem.build(5, 6, 0.05), sem.BoxProblem.build(4, 6, 0.05)
+    u, v = (to_dev(workloads.uniform(p.n, workloads.SEED_RHS)) for p in (P, Q))
+    ref, refq = u.clone(), v.clone()
+    for p, r in ((P, ref), (Q, refq)):
+        p.gs.op(r)
+        sem.mask(r, p.msh)
+    P.assemble(u)
+    out, side, graph = torch.zeros_like(v), torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        b = P.assemble(u)
+        with torch.cuda.stream(side):
+            sem._assemble(out, v, Q.msh, Q.gs, 1)
+        c = b + 1.0
+    torch.cuda.synchronize()
+    assert torch.equal(out, refq)
+    for _ in range(3):
+        b.fill_(7.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(b, ref) and torch.equal(c, ref + 1.0)
