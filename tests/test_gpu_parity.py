@@ -1394,3 +1394,27 @@ def test_first_assembly_beside_a_capture():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(b, ref) and torch.equal(c, ref + 1.0)
+
+
+@pytest.mark.parametrize("nx,lx,nf", [(17, 9, 1), (16, 8, 3), (15, 9, 3), (11, 12, 3)])
+def test_pcg_streamed_and_gathered(nx, lx, nf):
+    """The FP64 solve in the forms of large problems, where one iteration moves more than the
+    300 MB that stay in the cache and the update gathers w, in runs of 4 chunks per XCD (4096
+    chunks) and of 16 (more): three and four steps equal to the oracle's PCG, 1e-12 a step as
+    where the matvec completes x, which it does here but for three fields of lx = 12."""
+    say(f"[streamed, gathered] nx={nx} lx={lx} nf={nf}")
+    P, O = pair(nx, lx)
+    P.coef.set_helmholtz(1.0, 100.0)
+    O.set_coef(1.0, 100.0)
+    assert P.n * 8 * (8 + 4 * nf) > 300e6
+    one = to_dev(workloads.uniform(P.n, workloads.SEED_RHS))
+    b = P.assemble(torch.cat([one * (k + 1.0) for k in range(nf)]), nf)
+    for iters in (3, 4):
+        x, info = P.solve(b, nfields=nf, rtol=0.0, max_iter=iters)
+        xo = O.pcg(host(b[:P.n]), rtol=0.0, max_iter=iters)[0]
+        for k in range(nf):
+            assert info[k]["iters"] == iters
+            ref = (k + 1.0) * xo
+            assert np.abs(host(x[k * P.n:(k + 1) * P.n]) - ref).max() <= 1e-12 * iters * np.abs(ref).max()
+    P.coef.set_helmholtz(1.0, 0.0)
+    O.set_coef(1.0, 0.0)
