@@ -489,7 +489,7 @@ __global__ SEM_BOUNDS2((Shape<LX, T>::NT), (Shape<LX, T>::MINW)) void k_cg_matve
 #pragma unroll
     for (int f = 0; f < NF; ++f) live = live || !A.scal[f].stop;
     if (!live) {
-        if (FOLD && blockIdx.x == 0 && tid < NF) A.scal_out[tid] = A.scal[tid];
+        if (FOLD && blockIdx.x == 0 && tid == 0) *A.scal_out = *A.scal;
         return;
     }
 
@@ -511,36 +511,32 @@ __global__ SEM_BOUNDS2((Shape<LX, T>::NT), (Shape<LX, T>::MINW)) void k_cg_matve
     // per iteration, in 512 15.9 -> 15.0.  With three fields it is slower, 21.1 -> 22.0 and 25.4 ->
     // 26.8, where the three ends come one after the other.
     static_assert(!FOLD || NF == 1, "one field");
-    __shared__ double us[FOLD ? 8 : 1];
-    __shared__ double fb[FOLD ? NF : 1];
-    __shared__ int fs[FOLD ? NF : 1];
+    __shared__ double fsum[FOLD ? 8 : 1], fbeta;
+    __shared__ int fstop;
     if constexpr (FOLD) {
         const int lane = tid & 63, wave = tid >> 6;
         constexpr int NW = S::NT / 64;  // whole waves
-        for (int f = 0; f < NF; ++f) {
-            if (wave < NW) {
-                for (int c = wave; c < 8; c += NW) {  // four chunks of 64 of each of the two sums
-                    const int q = (c & 3) * 64 + lane;
-                    const double v = q < A.nup ? A.upart[((int64_t)(c >> 2) * NF + f) * A.nup + q] : 0.0;
-                    const double t = wave_sum(v);
-                    if (lane == 0) us[c] = t;
-                }
+        if (wave < NW) {
+            for (int h = wave; h < 8; h += NW) {  // four chunks of 64 of each of the two sums
+                const int q = (h & 3) * 64 + lane;
+                const double v = wave_sum(q < A.nup ? A.upart[(h >> 2) * A.nup + q] : 0.0);
+                if (lane == 0) fsum[h] = v;
             }
-            __syncthreads();
-            if (tid == 0) {
-                CgScalars sc = A.scal[f];
-                if (!sc.stop && sc.primed)
-                    cg_end_iteration(sc, ((us[0] + us[1]) + us[2]) + us[3], ((us[4] + us[5]) + us[6]) + us[7]);
-                fb[f] = sc.beta;
-                fs[f] = sc.stop;
-                if (blockIdx.x == 0) {
-                    sc.primed = 0;
-                    A.scal_out[f] = sc;
-                }
-            }
-            __syncthreads();
         }
-        if (fs[0]) return;
+        __syncthreads();
+        if (tid == 0) {
+            CgScalars sc = *A.scal;
+            if (!sc.stop && sc.primed)
+                cg_end_iteration(sc, ((fsum[0] + fsum[1]) + fsum[2]) + fsum[3], ((fsum[4] + fsum[5]) + fsum[6]) + fsum[7]);
+            fbeta = sc.beta;
+            fstop = sc.stop;
+            if (blockIdx.x == 0) {
+                sc.primed = 0;
+                *A.scal_out = sc;
+            }
+        }
+        __syncthreads();
+        if (fstop) return;
     }
 
     double part[NF];
@@ -548,16 +544,17 @@ __global__ SEM_BOUNDS2((Shape<LX, T>::NT), (Shape<LX, T>::MINW)) void k_cg_matve
     for (int f = 0; f < NF; ++f) {
         part[f] = 0.0;
         const CgScalars *sc = A.scal + f;
-        if (FOLD ? fs[f] : sc->stop) continue;  // uniform: every lane reads the same flag
+        if (!FOLD && sc->stop) continue;  // uniform: every lane reads the same flag
         T r[LX], p[LX];
         load_g<LX, T, KEEP>(r, A.r + f * A.n + row, act);
         if constexpr (CG1) {
 #pragma unroll
             for (int i = 0; i < LX; ++i) p[i] = dinv[i] * r[i];
         } else {
-            const T beta = (T)(FOLD ? fb[f] : sc->beta);
+            const T beta = (T)(FOLD ? fbeta : sc->beta);
             load_g<LX, T, KEEP>(p, A.p + f * A.n + row, act);
-            if (cg_matvec_takes_x(LX, sizeof(T) == 8, NF) && A.x && sc->pend) {
+            // (not with FOLD: see cg_iterate)
+            if (!FOLD && cg_matvec_takes_x(LX, sizeof(T) == 8, NF) && A.x && sc->pend) {
                 const T alpha = (T)sc->alpha;
                 T *xp = A.x + f * A.n + row, x[LX];
                 load_g<LX, T, KEEP>(x, xp, act);

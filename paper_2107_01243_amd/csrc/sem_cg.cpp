@@ -153,8 +153,9 @@ sem_status cg_iterate(sem_coef c, Work &W, sem_gs g, int nf, T *x, T *r, T *p, T
     CgFinishArgs F{U.partial, (int64_t)ug, W.scal, hist, hist_len, nf};
     F.src = U.scal_out;
     // small problems of one field: the end of an iteration in the next matvec (k_cg_matvec has
-    // the figures), two launches per iteration and one before the host looks at the state
-    const bool fold = f64 && nf == 1 && c->lx < 10 && U.nm > 0 && ug <= 256;
+    // the figures), two launches per iteration and one before the host looks at the state (at
+    // most 131,072 points, so x is not in the matvec; the history is the finish's to write)
+    const bool fold = f64 && nf == 1 && c->lx < 10 && U.nm > 0 && ug <= 256 && !x_in_matvec && !hist;
     if (fold) {
         M.nup = (int)ug;
         M.upart = U.partial;
