@@ -133,7 +133,8 @@ struct RelaxedCaptureMode {
 };
 
 // Per-point map of the kernels that gather (see CgUpdateArgs), built once per handle on the
-// stream st (not under capture), which is waited for.  Not built (the callers then run the
+// stream st, which is waited for; left for a later call where st is under capture, which allows
+// neither the allocation nor the wait.  Not built (the callers then run the
 // gather-scatter) when a point has more than 16 copies, when an entry's position does not fit
 // its word, or when memory is short; that is not tried again, since each later call would
 // pay for the failing allocation.
@@ -142,6 +143,12 @@ sem_status gs_gather_map(sem_gs g, hipStream_t st)
     const auto &m = g->m;
     std::lock_guard<std::mutex> lock(g->pmap_mu);
     if (g->pmap_tried || m.n == 0) return SEM_OK;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess) {  // (the null stream beside a capture)
+        (void)hipGetLastError();
+        return SEM_OK;
+    }
+    if (cap != hipStreamCaptureStatusNone) return SEM_OK;
     const int64_t nent = (int64_t)m.ent_idx.size();
     const RelaxedCaptureMode relaxed;
     int32_t *pmap = nullptr;
@@ -180,12 +187,9 @@ template <typename T>
 static sem_status assemble_t(T *b, const T *u, int nf, sem_mesh msh, sem_gs g, hipStream_t st)
 {
     int32_t *pmap = nullptr;
-    if (assembles_in_one_pass<T>(msh)) pmap = g->d_pmap.load(std::memory_order_acquire);
-    if (!pmap && assembles_in_one_pass<T>(msh)) {
-        // building the map allocates and waits, which a captured stream does not allow
-        hipStreamCaptureStatus cap;
-        HIP_TRY(hipStreamIsCapturing(st, &cap));
-        if (cap == hipStreamCaptureStatusNone) {
+    if (assembles_in_one_pass<T>(msh)) {
+        pmap = g->d_pmap.load(std::memory_order_acquire);
+        if (!pmap) {
             SEM_TRY(gs_gather_map(g, st));
             pmap = g->d_pmap.load(std::memory_order_acquire);
         }
