@@ -330,8 +330,10 @@ def mask(u, msh: Mesh, nfields: int = 1, stream=None):
 def _plain(t):
     """Whether t's values are its memory in order and no autograd mode follows it, so that a
     library pass that reads it stands for a copy of it."""
-    return (t.is_contiguous() and not t.is_neg() and not (t.requires_grad and torch.is_grad_enabled())
-            and forward_ad.unpack_dual(t).tangent is None)
+    if t.requires_grad and torch.is_grad_enabled() or not t.is_contiguous() or t.is_neg():
+        return False
+    # (unpack_dual costs 0.3 us of a small assembly's 9 and finds nothing outside a dual level)
+    return getattr(forward_ad, "_current_level", 0) < 0 or forward_ad.unpack_dual(t).tangent is None
 
 
 def _assemble(b, u, msh: Mesh, gs: GS, nfields: int):
@@ -558,7 +560,8 @@ class BoxProblem:
     def assemble(self, f_local, nfields=1):
         """b = mask QQ^T f (copy)."""
         if _plain(f_local) and self.gs.msh is self.msh:
-            _dev(f_local, nfields * self.msh.n, "u")
+            if not f_local.is_cuda or f_local.numel() != nfields * self.msh.n:
+                _dev(f_local, nfields * self.msh.n, "u")  # raises
             return _assemble(torch.empty_like(f_local), f_local, self.msh, self.gs, nfields)
         # a clone of a strided or expanded tensor is contiguous, one of a tensor with a gradient
         # or a tangent keeps it; and the two passes take a gs of one mesh and the walls of another
