@@ -50,8 +50,7 @@ static int64_t matvec_blocks(sem_coef c)
 }
 
 // The gathering form of U where it is used.  Up to sem_gather_fold_max() partial sums of
-// the matvec it also computes the step length; its own sums then go past the matvec's, and
-// the state goes from W.scal to W.scal2 (the finish brings it back).
+// the matvec it also computes the step length; its own sums then go past the matvec's.
 template <typename T>
 static void gather_in_update(CgUpdateArgs<T> &U, sem_coef c, Work &W, sem_gs g)
 {
@@ -62,7 +61,6 @@ static void gather_in_update(CgUpdateArgs<T> &U, sem_coef c, Work &W, sem_gs g)
     if (matvec_blocks<T>(c) > sem_gather_fold_max()) return;
     U.mpart = W.partial;
     U.nm = matvec_blocks<T>(c);
-    U.scal_out = W.scal2;
     U.partial = W.partial + 3 * W.nb;
 }
 
@@ -151,18 +149,16 @@ sem_status cg_iterate(sem_coef c, Work &W, sem_gs g, int nf, T *x, T *r, T *p, T
     gather_in_update(U, c, W, g);
     const unsigned ug = sem_update_grid(n, f64 ? 0 : 1, U.pmap != nullptr);
     CgFinishArgs F{U.partial, (int64_t)ug, W.scal, hist, hist_len, nf};
-    F.src = U.scal_out;
     // small problems of one field: the end of an iteration in the next matvec (k_cg_matvec has
     // the figures), two launches per iteration and one before the host looks at the state (at
     // most 131,072 points, so x is not in the matvec; the history is the finish's to write)
-    const bool fold = f64 && nf == 1 && c->lx < 10 && U.nm > 0 && ug <= 256 && !x_in_matvec && !hist;
+    const bool fold = f64 && nf == 1 && c->lx < 10 && W.scal2 && U.nm > 0 && ug <= 256 && !x_in_matvec && !hist;
     if (fold) {
         M.nup = (int)ug;
         M.upart = U.partial;
         M.scal_out = W.scal2;
         U.scal = W.scal2;
         U.scal_out = W.scal;
-        F.src = nullptr;
         F.settle = 1;
     }
     if (check_every < 1) check_every = 1;
@@ -486,7 +482,6 @@ static sem_status pcg_mixed_reliable(double *x, const double *b, int nf, sem_coe
     gather_in_update(U, c, W, g);
     const unsigned ug = sem_update_grid(n, 1, U.pmap != nullptr);
     CgFinishArgs F{U.partial, (int64_t)ug, W.scal, nullptr, 0, nf};
-    F.src = U.scal_out;
     const int check_every = std::max(1, P->check_every);
     const int64_t max_polls = (int64_t)P->max_iter + 64 * 64;  // every poll runs >= 1 iteration or ends a segment
     // Launches queued between polls after a segment has ended do no work but still cost a

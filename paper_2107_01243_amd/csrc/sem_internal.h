@@ -236,7 +236,7 @@ struct Work {
     int64_t partial_len = 0;
     int64_t nb = 0;                 // partial sums per row of W.partial
     CgScalars *scal = nullptr;      // device [fields]
-    CgScalars *scal2 = nullptr;     // the same, for launches that would write what they read
+    CgScalars *scal2 = nullptr;     // the same, where the matvec ends an iteration; may be nullptr
     CgScalars *h_scal = nullptr;    // pinned mirror
     AlphaJob *job64 = nullptr;      // device, for the FP64 matvec grid
     AlphaJob *job32 = nullptr;      // device, for the FP32 matvec grid

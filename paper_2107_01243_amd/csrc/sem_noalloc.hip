@@ -27,14 +27,12 @@ constexpr int64_t kOffDinv = kOffW + kMaxPoints;
 constexpr int64_t kOffPartial = kOffDinv + kMaxPoints;
 constexpr int64_t kOffSmall = kOffPartial + kPartial;
 constexpr int64_t kWords = kOffSmall + kSmall;
-// inside the small block (doubles): CgScalars[3] twice, AlphaJob, dots[12], done[3]
+// inside the small block (doubles): CgScalars[3], AlphaJob, dots[12], done[3]
 constexpr int64_t kSmallScal = 0;
-constexpr int64_t kSmallScal2 = 32;
 constexpr int64_t kSmallJob = 64;
 constexpr int64_t kSmallDots = 128;
 constexpr int64_t kSmallDone = 192;
-static_assert(3 * sizeof(CgScalars) <= 8 * (kSmallScal2 - kSmallScal), "CgScalars block");
-static_assert(3 * sizeof(CgScalars) <= 8 * (kSmallJob - kSmallScal2), "second CgScalars block");
+static_assert(3 * sizeof(CgScalars) <= 8 * (kSmallJob - kSmallScal), "CgScalars block");
 static_assert(sizeof(AlphaJob) <= 8 * (kSmallDots - kSmallJob), "AlphaJob slot");
 static_assert(3 * sizeof(int) <= 8 * (kSmall - kSmallDone), "flag block");
 
@@ -110,7 +108,6 @@ extern "C" sem_status sem_pcg_solve_noalloc(double *x, const double *b, int nfie
     W.partial_len = (4 * (int64_t)nfields + 3) * nb;
     W.nb = nb;
     W.scal = (CgScalars *)(small + kSmallScal);
-    W.scal2 = (CgScalars *)(small + kSmallScal2);
     W.job64 = (AlphaJob *)(small + kSmallJob);
     W.dots = small + kSmallDots;
     W.done = (int *)(small + kSmallDone);

@@ -80,7 +80,7 @@ struct CgUpdateArgs {
     const T *w;
     const T *dinv;
     const uint8_t *owner;
-    const CgScalars *scal;
+    CgScalars *scal;
     double *partial;  // [2][field][grid]
     int64_t n;
     int nfields;
@@ -94,8 +94,8 @@ struct CgUpdateArgs {
     // length (nm = 0: it is in scal)
     const double *mpart = nullptr;
     int64_t nm = 0;
-    // with nm: the state, only read in scal, is written here with the step length (not the same
-    // array: a workgroup of the launch may still have to read its stop flag)
+    // with nm: the state is read from scal and, with the step length, written here (not the same
+    // array; nullptr: the step length, or a breakdown, is set in scal)
     CgScalars *scal_out = nullptr;
     int keep = 0;  // what an iteration touches fits the last-level cache
 };
@@ -120,8 +120,6 @@ struct CgFinishArgs {
     int hist_len;
     int nfields;
     int settle = 0;   // only fields whose update's sums wait (primed), which is then cleared
-    // where the state before is read when not in scal (every field then goes to scal)
-    const CgScalars *src = nullptr;
 };
 
 // Per-field state of the reliable-update mixed solve (device resident).

@@ -1222,14 +1222,19 @@ __global__ __launch_bounds__(VT) void k_cg_update_gather(CgUpdateArgs<T> A, unsi
         pw = full ? (a[0] + a[1]) + (a[2] + a[3]) : (a[0] + a[1]) + a[2];
         sp[threadIdx.x] = pw;
     }
-    const CgScalars &sc = A.scal[f];
+    CgScalars &sc = A.scal[f];
     double rz = 0.0, rr = 0.0;
-    if (NM > 0 && sc.stop && lb == 0 && threadIdx.x == 0) A.scal_out[f] = sc;
-    if (!sc.stop) {
-        T *x = A.x + off, *r = A.r + off;
-        const T *p = A.p + off, *w = A.w + off;
-        T di[UV], xv[UV], pv[UV], rv[UV], v[UV][4];
-        List4 g[UV];
+    // With NM > 0 and no scal_out the first workgroup sets the flag in place on a breakdown, and
+    // waves may read it on either side of that: no barrier is under it.  A wave that sees it
+    // set updates nothing; one that does not finds the breakdown itself and updates nothing.
+    const bool live = !__builtin_amdgcn_readfirstlane(
+        __hip_atomic_load(&sc.stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    if (NM > 0 && A.scal_out && !live && lb == 0 && threadIdx.x == 0) A.scal_out[f] = sc;
+    T *x = A.x + off, *r = A.r + off;
+    const T *p = A.p + off, *w = A.w + off;
+    T di[UV], xv[UV], pv[UV], rv[UV], v[UV][4];
+    List4 g[UV];
+    if (live) {
 #pragma unroll
         for (int u = 0; u < UV; ++u) {
             const int64_t t = min(t0 + (int64_t)u * VT, A.n - 1);
@@ -1262,23 +1267,31 @@ __global__ __launch_bounds__(VT) void k_cg_update_gather(CgUpdateArgs<T> A, unsi
                 if ((o & 31) >= 6) v[u][3] = w[g[u].e[3] & 0x7fffffffu];
             }
         }
+    }
+    if constexpr (NM > 0) __syncthreads();
+    if (live) {
         T alpha;
         bool ok = true;
         if constexpr (NM > 0) {
-            __syncthreads();
             pw = (sp[lane] + sp[lane + 128]) + (sp[lane + 64] + sp[lane + 192]);
             pw = wave_sum(pw);
             const double rz0 = sc.rz;
-            // every workgroup finds the same, and on a breakdown none updates anything; the state
-            // with the step length or the breakdown in it goes to another place than the one
-            // that they all read, so the branch and the barrier in it are uniform
-            ok = pw > 0.0 && isfinite(pw) && isfinite(rz0);
+            ok = pw > 0.0 && isfinite(pw) && isfinite(rz0);  // the same in every workgroup
             alpha = ok ? (T)(rz0 / pw) : T(0);
             if (lb == 0 && threadIdx.x == 0) {
-                CgScalars S = sc;
-                cg_set_alpha(S, pw);
-                S.primed = !S.stop;
-                A.scal_out[f] = S;
+                if (A.scal_out) {
+                    CgScalars S = sc;
+                    cg_set_alpha(S, pw);
+                    S.primed = !S.stop;
+                    A.scal_out[f] = S;
+                } else if (ok) {
+                    sc.alpha = rz0 / pw;
+                } else {
+                    sc.status = 2;
+                    sc.alpha = 0.0;
+                    sc.pend = 0;
+                    __hip_atomic_store(&sc.stop, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
             }
         } else {
             alpha = (T)sc.alpha;
@@ -1572,19 +1585,14 @@ __global__ __launch_bounds__(RT) void k_cg_finish(CgFinishArgs A)
 {
     __shared__ double sh[2 * (RT / 64)];
     const int f = blockIdx.x;
-    const CgScalars &from = A.src ? A.src[f] : A.scal[f];
-    if (from.stop || (A.settle && !from.primed)) {
-        if (A.src && threadIdx.x == 0) A.scal[f] = from;
-        return;
-    }
+    CgScalars &s = A.scal[f];
+    if (s.stop || (A.settle && !s.primed)) return;
     double rz, rr;
     block_sum2_fixed<RT>(A.partial + (0 * A.nfields + f) * A.nblk, A.partial + (1 * A.nfields + f) * A.nblk, A.nblk, sh,
                          rz, rr);
     if (threadIdx.x == 0) {
-        CgScalars s = from;
         cg_end_iteration(s, rz, rr);
-        s.primed = 0;
-        A.scal[f] = s;
+        if (A.settle) s.primed = 0;
         if (A.hist && s.iter < A.hist_len) A.hist[(int64_t)f * A.hist_len + s.iter] = sqrt(rr / s.bb);
     }
 }
@@ -1997,8 +2005,7 @@ template <typename T>
 static hipError_t launch_gather(const CgUpdateArgs<T> *A, unsigned grid, hipStream_t st)
 {
     if ((int64_t)grid * VT * UpdChunk<T>::GV < A->n) return hipErrorInvalidValue;
-    if (A->nm > GATHER_NM || (A->nm > 0 && (!A->mpart || !A->scal_out || A->scal_out == A->scal)))
-        return hipErrorInvalidValue;
+    if (A->nm > GATHER_NM || (A->nm > 0 && (!A->mpart || A->scal_out == A->scal))) return hipErrorInvalidValue;
     const int run = grid > 4096 ? 4 : 2;
     const unsigned per = 8u << run;
     const dim3 g((grid + per - 1) / per * per, A->nfields);

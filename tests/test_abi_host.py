@@ -172,5 +172,5 @@ def test_gathering_update_refuses_what_it_cannot_run(L, f32, n):
 
     assert launch(args(), grid - 1, None) == 1
     assert launch(args(nm=0), grid - 1, None) == 1
-    for bad in (dict(nm=most + 1), dict(mpart=None), dict(scal_out=None), dict(scal_out=4096)):
+    for bad in (dict(nm=most + 1), dict(mpart=None), dict(scal_out=4096)):
         assert launch(args(**bad), grid, None) == 1, bad
