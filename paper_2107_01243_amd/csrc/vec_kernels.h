@@ -95,7 +95,7 @@ struct CgUpdateArgs {
     const double *mpart = nullptr;
     int64_t nm = 0;
     // with nm: the state is read from scal and, with the step length, written here (not the same
-    // array; nullptr: the step length, or a breakdown, is set in scal)
+    // array; nullptr: the step length, or the status of a breakdown, is set in scal)
     CgScalars *scal_out = nullptr;
     int keep = 0;  // what an iteration touches fits the last-level cache
 };

@@ -1224,17 +1224,12 @@ __global__ __launch_bounds__(VT) void k_cg_update_gather(CgUpdateArgs<T> A, unsi
     }
     CgScalars &sc = A.scal[f];
     double rz = 0.0, rr = 0.0;
-    // With NM > 0 and no scal_out the first workgroup sets the flag in place on a breakdown, and
-    // waves may read it on either side of that: no barrier is under it.  A wave that sees it
-    // set updates nothing; one that does not finds the breakdown itself and updates nothing.
-    const bool live = !__builtin_amdgcn_readfirstlane(
-        __hip_atomic_load(&sc.stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    if (NM > 0 && A.scal_out && !live && lb == 0 && threadIdx.x == 0) A.scal_out[f] = sc;
-    T *x = A.x + off, *r = A.r + off;
-    const T *p = A.p + off, *w = A.w + off;
-    T di[UV], xv[UV], pv[UV], rv[UV], v[UV][4];
-    List4 g[UV];
-    if (live) {
+    if (NM > 0 && A.scal_out && sc.stop && lb == 0 && threadIdx.x == 0) A.scal_out[f] = sc;
+    if (!sc.stop) {  // (no workgroup of this launch writes the flag: the barrier below is uniform)
+        T *x = A.x + off, *r = A.r + off;
+        const T *p = A.p + off, *w = A.w + off;
+        T di[UV], xv[UV], pv[UV], rv[UV], v[UV][4];
+        List4 g[UV];
 #pragma unroll
         for (int u = 0; u < UV; ++u) {
             const int64_t t = min(t0 + (int64_t)u * VT, A.n - 1);
@@ -1267,16 +1262,15 @@ __global__ __launch_bounds__(VT) void k_cg_update_gather(CgUpdateArgs<T> A, unsi
                 if ((o & 31) >= 6) v[u][3] = w[g[u].e[3] & 0x7fffffffu];
             }
         }
-    }
-    if constexpr (NM > 0) __syncthreads();
-    if (live) {
         T alpha;
         bool ok = true;
         if constexpr (NM > 0) {
+            __syncthreads();
             pw = (sp[lane] + sp[lane + 128]) + (sp[lane + 64] + sp[lane + 192]);
             pw = wave_sum(pw);
             const double rz0 = sc.rz;
-            ok = pw > 0.0 && isfinite(pw) && isfinite(rz0);  // the same in every workgroup
+            // every workgroup finds the same; on a breakdown none updates anything
+            ok = pw > 0.0 && isfinite(pw) && isfinite(rz0);
             alpha = ok ? (T)(rz0 / pw) : T(0);
             if (lb == 0 && threadIdx.x == 0) {
                 if (A.scal_out) {
@@ -1286,11 +1280,10 @@ __global__ __launch_bounds__(VT) void k_cg_update_gather(CgUpdateArgs<T> A, unsi
                     A.scal_out[f] = S;
                 } else if (ok) {
                     sc.alpha = rz0 / pw;
-                } else {
+                } else {  // (cg_set_alpha but for the flag, which the finish sets)
                     sc.status = 2;
                     sc.alpha = 0.0;
                     sc.pend = 0;
-                    __hip_atomic_store(&sc.stop, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
             }
         } else {
@@ -1587,6 +1580,11 @@ __global__ __launch_bounds__(RT) void k_cg_finish(CgFinishArgs A)
     const int f = blockIdx.x;
     CgScalars &s = A.scal[f];
     if (s.stop || (A.settle && !s.primed)) return;
+    if (s.status == 2) {  // a breakdown that the update found (uniform: nothing wrote it here yet)
+        __syncthreads();
+        if (threadIdx.x == 0) s.stop = 1;
+        return;
+    }
     double rz, rr;
     block_sum2_fixed<RT>(A.partial + (0 * A.nfields + f) * A.nblk, A.partial + (1 * A.nfields + f) * A.nblk, A.nblk, sh,
                          rz, rr);
