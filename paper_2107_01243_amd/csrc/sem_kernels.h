@@ -93,8 +93,12 @@ __host__ __device__ inline void cg_end_iteration(CgScalars &s, double rz, double
 // in 13824 182 / 188 (412 / 437), in 32768 421 / 428 (1015 / 1065), 9^3 in 10648 212 / 214
 // (582 / 602), 12^3 in 8000 341 / 354; 7^3 in 17576 with h2 184 / 182, 6^3 in 64000 380 / 372,
 // 5^3 with three fields 610 / 598.  Three fields at lx = 12 have no registers left for x (28
-// spilled: 1047 / 890).  FP32 of one field at lx = 9 139 / 135.
-constexpr bool cg_matvec_takes_x(int lx, bool f64, int nf) { return f64 && lx >= 8 && !(lx == 12 && nf == 3); }
+// spilled: 1047 / 890), and one field at lx = 11 is slower at every size (11^3 in 1000 elements
+// 54.4 / 52.9, in 5832 235.5 / 233.1, in 10648 415.9 / 409.6).  FP32 of one field at lx = 9 139 / 135.
+constexpr bool cg_matvec_takes_x(int lx, bool f64, int nf)
+{
+    return f64 && lx >= 8 && !(lx == 12 && nf == 3) && !(lx == 11 && nf == 1);
+}
 
 // p = dinv r + beta p;  w = A_L p;  per-workgroup partial sums of p.w.
 // Single-reduction form: u = dinv r;  w = A_L u;  partial sums of u.w.

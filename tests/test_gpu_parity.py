@@ -1418,3 +1418,20 @@ def test_pcg_streamed_and_gathered(nx, lx, nf):
             assert np.abs(host(x[k * P.n:(k + 1) * P.n]) - ref).max() <= 1e-12 * iters * np.abs(ref).max()
     P.coef.set_helmholtz(1.0, 0.0)
     O.set_coef(1.0, 0.0)
+
+
+@pytest.mark.parametrize("nx,nf", [(8, 1), (8, 3), (15, 1)])
+def test_pcg_lx11_x_in_update(nx, nf):
+    """At lx = 11 the update completes x of one field and the matvec that of three, where the
+    set is kept (681,472 points) and streamed (4,492,125): steps equal to the oracle's PCG,
+    1e-12 a step."""
+    say(f"[lx 11] nx={nx} nf={nf}")
+    P, O = pair(nx, 11)
+    one = to_dev(workloads.uniform(P.n, workloads.SEED_RHS))
+    b = P.assemble(torch.cat([one * (k + 1.0) for k in range(nf)]), nf)
+    for iters in (1, 4):
+        x, info = P.solve(b, nfields=nf, rtol=0.0, max_iter=iters)
+        xo = O.pcg(host(b[:P.n]), rtol=0.0, max_iter=iters)[0]
+        for k in range(nf):
+            assert info[k]["iters"] == iters
+            assert np.abs(host(x[k * P.n:(k + 1) * P.n]) - (k + 1.0) * xo).max() <= 1e-12 * iters * (k + 1.0) * np.abs(xo).max()
