@@ -928,13 +928,19 @@ __device__ __forceinline__ void div_nb(const DS &D, const T (&wr)[LX], const T (
 //  * NB: LDS element buffers, 4 (grad4 / div4: four barriers per field pass) or 2
 //    (grad_lean / div_lean: eight); in FP64 four would halve the workgroups a compute
 //    unit holds.
-//  * MINW: waves per SIMD the register allocation is held to.
+//  * minw: waves per SIMD the register allocation is held to.  Three FP64 fields of lx = 13
+//    without a mass term need 170 registers unless held to the 168 of three waves: 12.8 million
+//    points, Poisson 432 -> 364 us, h1 field 472 -> 402.
 template <int LX, typename T, int NF, bool CG>
 struct LeanCfg {
     static constexpr bool F32 = sizeof(T) == 4;
     static constexpr bool HOLD = NF > 1 && !CG && LX <= (F32 ? 12 : 11);
     static constexpr int NB = F32 ? 4 : 2;
-    static constexpr int MINW = HOLD ? (F32 ? 3 : 2) : Shape<LX, T>::MINW;
+    static constexpr int minw(int kind)
+    {
+        if (!CG && NF == 3 && !F32 && LX == 13 && kind_mass(kind) == 0) return 3;
+        return HOLD ? (F32 ? 3 : 2) : Shape<LX, T>::MINW;
+    }
 };
 
 template <int LX, typename T, int NB>
@@ -1012,7 +1018,7 @@ __device__ __forceinline__ void ax_lean_body(const DS &D, const AxArgs<T> &A)
 
 // DMem in FP64 (the even-odd D does not fit the scalar registers), DArg in FP32.
 template <int LX, typename T, int NF, int KIND>
-__global__ SEM_BOUNDS2((Shape<LX, T>::NT), (LeanCfg<LX, T, NF, false>::MINW)) void k_ax_helm_lean(
+__global__ SEM_BOUNDS2((Shape<LX, T>::NT), (LeanCfg<LX, T, NF, false>::minw(KIND))) void k_ax_helm_lean(
     AxArgs<T> A, DEo<LX, T> D, const DEo<LX, T> *__restrict__ Dg)
 {
     if constexpr (sizeof(T) == 8) ax_lean_body<LX, T, NF, KIND>(DMem<LX, T>{Dg}, A);
@@ -1101,7 +1107,7 @@ __device__ __forceinline__ void cg_lean_body(const DS &D, const CgMatvecArgs<T> 
 }
 
 template <int LX, typename T, int NF, int KIND, bool CG1>
-__global__ SEM_BOUNDS2((Shape<LX, T>::NT), (LeanCfg<LX, T, NF, true>::MINW)) void k_cg_matvec_lean(
+__global__ SEM_BOUNDS2((Shape<LX, T>::NT), (LeanCfg<LX, T, NF, true>::minw(KIND))) void k_cg_matvec_lean(
     CgMatvecArgs<T> A, DEo<LX, T> D, const DEo<LX, T> *__restrict__ Dg)
 {
     if constexpr (sizeof(T) == 8) cg_lean_body<LX, T, NF, KIND, CG1>(DMem<LX, T>{Dg}, A);

@@ -1435,3 +1435,10 @@ def test_pcg_lx11_x_in_update(nx, nf):
         for k in range(nf):
             assert info[k]["iters"] == iters
             assert np.abs(host(x[k * P.n:(k + 1) * P.n]) - (k + 1.0) * xo).max() <= 1e-12 * iters * (k + 1.0) * np.abs(xo).max()
+
+
+@pytest.mark.parametrize("lx", [13, 15])
+def test_ax_coefficient_forms_odd_high_order(lx):
+    """The six coefficient forms at the odd orders above 11, as test_ax_coefficient_forms_high_order
+    has them at the others, with its bounds."""
+    test_ax_coefficient_forms_high_order(lx)
