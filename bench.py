@@ -267,8 +267,8 @@ def cpu_baseline(wl, gpu_iters, full_solve=False, mixed=None):
 LX12_KERNELS = {"ax_f64_poisson_1field": "sem::k_ax_helm_tile<12, double, 1, 0>",
                 "ax_f64_helmholtz_1field": "sem::k_ax_helm_tile<12, double, 1, 2>",
                 "ax_f64_helmholtz_3field": "sem::k_ax_helm_tile<12, double, 3, 2>",
-                "ax_f32_helmholtz_3field": "sem::k_ax_helm_lean<12, float, 3, 2>",
-                "adjoint_f64": "sem::k_ax_adjoint_lean<12, double>"}
+                "ax_f32_helmholtz_3field": "sem::k_ax_helm_lean<12, float, 3, 2, true>",
+                "adjoint_f64": "sem::k_ax_adjoint_lean<12, double, false>"}
 LX12_WORDS = {"ax_f64_poisson_1field": (8, 8), "ax_f64_helmholtz_1field": (9, 8),
               "ax_f64_helmholtz_3field": (13, 8), "ax_f32_helmholtz_3field": (13, 4),
               "adjoint_f64": (9, 8)}

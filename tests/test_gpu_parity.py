@@ -1442,3 +1442,31 @@ def test_ax_coefficient_forms_odd_high_order(lx):
     """The six coefficient forms at the odd orders above 11, as test_ax_coefficient_forms_high_order
     has them at the others, with its bounds."""
     test_ax_coefficient_forms_high_order(lx)
+
+
+@pytest.mark.parametrize("nx,lx", [(16, 6), (27, 7), (9, 12), (8, 13), (20, 5), (33, 6), (21, 10), (19, 11)])
+def test_ax_geometry_read_both_ways(nx, lx):
+    """The operator and the h1-adjoint where G is left to the cache and where it is streamed (0.9 to
+    9.3 million points, the lines of reads_plainly between them): sampled elements, first and last
+    included, equal to the same elements applied as a small problem, FP64 to 1e-13 and FP32 to
+    2e-6 of the largest value (the same arithmetic in kernels that may contract differently)."""
+    say(f"[G both ways] nx={nx} lx={lx}")
+    P = sem.BoxProblem.build(nx, lx, 0.05, fp32=True)
+    e = np.unique(np.linspace(0, nx ** 3 - 1, 27).astype(np.int64))
+    pts = to_dev((e[:, None] * lx ** 3 + np.arange(lx ** 3)[None, :]).reshape(-1), torch.int64)
+    msh = sem.Mesh(e.size, lx, np.arange(e.size * lx ** 3))
+    small = sem.Coef(P.Xh, msh, xyz=P.xyz.view(3, -1)[:, pts].contiguous().view(-1), fp32=True)
+    u = to_dev(workloads.uniform(P.n, 1)), to_dev(workloads.uniform(P.n, 2)), to_dev(workloads.uniform(P.n, 3))
+    for h2 in (0.0, 30.0):
+        P.coef.set_helmholtz(0.7, h2)
+        small.set_helmholtz(0.7, h2)
+        for dt, tol in ((torch.float64, 1e-13), (torch.float32, 2e-6)):
+            U = [v.to(dt) for v in u]
+            S = [v[pts] for v in U]
+            ref = sem.ax_helm(torch.empty_like(torch.cat(S)), torch.cat(S), small, msh, P.Xh, 3).view(3, -1)
+            W = P.ax(torch.cat(U), 3).view(3, -1)[:, pts]
+            for k in range(3):
+                assert float((P.ax(U[k])[pts] - ref[k]).abs().max()) <= tol * float(ref[k].abs().max())
+                assert float((W[k] - ref[k]).abs().max()) <= tol * float(ref[k].abs().max())
+            g = sem.ax_helm_adjoint(torch.empty_like(S[0]), S[0], S[1], small, msh, P.Xh)
+            assert float((P.adjoint(U[0], U[1])[pts] - g).abs().max()) <= tol * float(g.abs().max())
