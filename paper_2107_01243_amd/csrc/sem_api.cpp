@@ -171,23 +171,47 @@ sem_status gs_gather_map(sem_gs g, hipStream_t st)
     return SEM_OK;
 }
 
-// One pass (k_assemble) or copy, gather-scatter and mask.  Up to 2M points the launches are
-// what costs; beyond, points with copies are the dearer ones of the pass, and their share
-// falls with lx.  Measured, us, one pass against three: FP64 lx = 5 at 8M points 71 / 59, lx = 7
-// at 6M 39 / 41, lx = 8 at 16.8M 122 / 135; FP32 lx = 7 at 6M with three fields 82 / 66, lx = 8
-// at 16.8M 72 / 63, lx = 12 at 13.8M 46 / 47, three fields 123 / 160; at 2.1M, lx = 8: FP64
-// 14.7 / 23.5, FP32 10.5 / 18.5.
+// One pass (k_assemble) or copy, gather-scatter and mask.  Small problems are bound by the
+// launches; beyond, points with copies are the dearer ones of the pass, and their share falls
+// with lx; the three passes gain where input and output together just fill the last-level cache
+// (fields of 95 to 125 MB), in which they find each other's results.  Time of the three over
+// that of one, with cold operands / operands from the call before:
+//  * one field: FP64 lx = 2 to 6 at 2 million points 1.04 to 1.33 / 1.06 to 1.31, at 4 million
+//    lx = 4 0.80 / 0.85, 5 0.93 / 1.02, 6 1.03 / 1.11, 7 1.03 / 1.13; lx = 7 at 9.3 million 0.85 /
+//    0.98, 8 0.95 / 1.11, 9 0.94 / 1.08, 10 1.02 / 1.16; at 13.8 million lx = 8 0.85 / 0.78, 10 0.92 /
+//    0.86, 12 1.02 / 0.96; at 16 million 7 1.04 / 1.03, 10 1.10 / 1.13, 16 1.11 / 1.12.  FP32 lx = 2 at
+//    1.6 million 1.10 / 1.13, 2.1 million 0.91 / 0.93; lx = 8 at 8 million 0.91 / 1.05; lx = 9 at 6
+//    million 1.01 / 1.15, 9 million 0.88 / 1.01; lx = 10 to 16 at 9 million 0.93 to 1.02 / 1.07 to
+//    1.15, at 16 million 0.83 to 0.90 / 0.96 to 1.08.
+//  * three fields: FP64 lx = 3 at 0.6 million 0.99 / 1.00, 0.8 million 0.95 / 0.94, 4 at 0.8 million
+//    1.03 / 1.04, 1.3 million 0.84 / 0.94, 5 at 1.2 million 0.95 / 1.07, 1.5 million 0.91 / 1.07, 6 at 2
+//    million 0.90 / 1.10, 7 at 4.7 million 0.87 / 0.98, 9 at 5 million 0.96 / 1.02; at 8 million
+//    lx = 7 to 16 1.04 to 1.36.  FP32 lx = 2 at 0.6 million 1.10 / 1.14, 0.8 million 0.92 / 0.96, 9 at 8.9
+//    million 0.85 / 0.94, 11 at 9.1 million 0.90 / 0.95, 12 at 8.5 million 1.09 / 1.26; at 16 million
+//    lx = 9 to 16 1.16 to 1.28.
 template <typename T>
-static bool assembles_in_one_pass(sem_mesh msh)
+static bool assembles_in_one_pass(sem_mesh msh, int nf)
 {
-    return msh->n <= (1 << 21) || msh->lx >= (sizeof(T) == 8 ? 7 : 9);
+    const int lx = msh->lx;
+    const int64_t n = msh->n, field = n * nf * (int64_t)sizeof(T);
+    const int64_t few = nf == 1 ? (lx == 2 ? 3 << 19 : 1 << 21)
+                                : (lx <= 3 ? 600000 : lx == 4 ? 800000 : lx == 5 ? 1200000 : 1 << 21);
+    if (n <= few) return true;
+    const bool fills = field > 95000000 && field < 125000000;
+    if (sizeof(T) == 8) {
+        if (lx < 7) return false;
+        if (fills) return lx >= (nf == 1 ? 12 : 8);
+        return lx > 7 || nf == 3 || field <= 40000000 || field >= 125000000;
+    }
+    if (lx < 9) return false;
+    return nf == 1 ? field <= (lx == 9 ? 24000000 : 42000000) : lx >= 12 || !fills;
 }
 
 template <typename T>
 static sem_status assemble_t(T *b, const T *u, int nf, sem_mesh msh, sem_gs g, hipStream_t st)
 {
     int32_t *pmap = nullptr;
-    if (assembles_in_one_pass<T>(msh)) {
+    if (assembles_in_one_pass<T>(msh, nf)) {
         pmap = g->d_pmap.load(std::memory_order_acquire);
         if (!pmap) {
             SEM_TRY(gs_gather_map(g, st));

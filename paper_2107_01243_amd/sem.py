@@ -552,7 +552,11 @@ class BoxProblem:
     def apply(self, u, nfields=1):
         """mask QQ^T A_L u."""
         w = self.ax(u, nfields)
-        if self.n <= 1 << 20 and self.gs.msh is self.msh:  # bound by its launches: one less of them
+        # Bound by its launches: one less of them.  Three fields of low order only while they are
+        # small: in place the two passes took 30, out of place the one 37 us at lx = 2 and 0.8
+        # million points, 26 and 26 at 0.44, 26 and 21 at 0.29 (FP64; lx = 8 35 and 35 at 0.88).
+        if self.n <= 1 << 20 and self.gs.msh is self.msh and (
+                nfields == 1 or self.lx >= 8 or w.numel() * w.element_size() <= 6 << 20):
             return _assemble(torch.empty_like(w), w, self.msh, self.gs, nfields)
         self.gs.op(w, nfields)
         return mask(w, self.msh, nfields)

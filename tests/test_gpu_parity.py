@@ -1470,3 +1470,19 @@ def test_ax_geometry_read_both_ways(nx, lx):
                 assert float((W[k] - ref[k]).abs().max()) <= tol * float(ref[k].abs().max())
             g = sem.ax_helm_adjoint(torch.empty_like(S[0]), S[0], S[1], small, msh, P.Xh)
             assert float((P.adjoint(U[0], U[1])[pts] - g).abs().max()) <= tol * float(g.abs().max())
+
+
+@pytest.mark.parametrize("nx,lx", [(42, 2), (43, 2), (58, 2), (28, 3), (29, 3), (23, 4), (24, 4), (21, 5), (22, 5),
+                                   (24, 7), (25, 7), (18, 9), (19, 9), (20, 10), (22, 10)])
+def test_assembly_on_both_sides_of_its_lines(nx, lx):
+    """assemble() and apply(), whichever passes they take at this size, equal to the bit a copy (or
+    the operator) followed by gather-scatter and mask."""
+    say(f"[assembly lines] nx={nx} lx={lx}")
+    P = sem.BoxProblem.build(nx, lx, 0.05, fp32=True)
+    for nf in (1, 3):
+        for dt in (torch.float64, torch.float32):
+            u = to_dev(workloads.uniform(P.n * nf, workloads.SEED_RHS), dt)
+            for f, out in ((u, P.assemble(u, nf)), (P.ax(u, nf), P.apply(u, nf))):
+                ref = f.clone()
+                P.gs.op(ref, nf)
+                assert torch.equal(out, sem.mask(ref, P.msh, nf))
