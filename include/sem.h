@@ -27,8 +27,16 @@
  *   owned by the library and released by the matching *_destroy call.
  * Streams.  `stream` is a hipStream_t passed as void* (NULL = the null stream).
  *   sem_ax_helm, sem_gs_op, sem_mask, sem_assemble and sem_ax_helm_adjoint only enqueue
- *   work (the first call on a handle also uploads its maps)
- *   and return.  sem_pcg_solve synchronises the stream to poll convergence.
+ *   work and return, but for the first calls on a handle: the first one uploads the handle's
+ *   maps, and the first sem_assemble in its one-pass form, or the first solve that sums copies
+ *   where it reads them, builds a map from the uploaded ones on the caller's stream and waits
+ *   for that stream.  The map takes 4 bytes per local point and stays until sem_gs_destroy;
+ *   where that memory is not to be had, these calls run the gather-scatter, now and
+ *   later, with the same results.  sem_pcg_solve synchronises the stream to poll convergence.
+ * Capture.  A stream under capture can neither allocate nor wait: handles have to be uploaded
+ *   before (by any of these calls), and a sem_assemble captured before the map is there records
+ *   a copy, the gather-scatter and the mask, which the graph keeps; one call outside a capture
+ *   first lets it record the one pass.
  * Errors.  Every call returns a sem_status; nothing aborts or throws.  Invalid
  *   arguments are rejected before any launch.  sem_last_error() returns a
  *   thread-local description of the last failure.

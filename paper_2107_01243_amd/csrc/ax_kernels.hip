@@ -645,8 +645,10 @@ __global__ SEM_BOUNDS2((Shape<LX, T>::NT), (Shape<LX, T>::MINW)) void k_cg_matve
 // and s derivatives run one after the other, and one element is one workgroup.  The
 // registers saved let two (FP64) or four (FP32) waves share a SIMD, so the loads of
 // one workgroup overlap the arithmetic of others.  With three fields the chunks are
-// read again for every field with ordinary (cached) loads: the first field brings
-// them from HBM, the other two find them in the cache.
+// read again for every field, mostly from memory: those of the elements in flight on an
+// XCD do not stay in its L2 (41.7 GB fetched for 15.3 GB needed, three FP64 Helmholtz fields of
+// 191 million points at lx = 12).  Where G fits the registers it is held instead (LeanCfg::HOLD,
+// and the matrix-core variants below).
 
 template <bool NTL, typename T>
 __device__ __forceinline__ T ldx(const T *p)
@@ -952,9 +954,9 @@ __device__ __forceinline__ void div_nb(const DS &D, const T (&wr)[LX], const T (
 //    they fit: the FP32 operator up to lx = 12, the FP64 operator at lx = 10 and 11 at two
 //    waves per SIMD (three Helmholtz fields, 20 million points: 635 -> 467 us and 676 ->
 //    492 us; with h1 and h2 fields 1690 -> 508 and 2000 -> 649 us; FP32 at lx = 12 with
-//    h1 and h2 fields 389 -> 294 us).  The FP32 CG matvec,
-//    which also holds p, is faster reading chunks at three waves per SIMD (4.6 -> 3.7 ms at
-//    48^3 x lx = 12).
+//    h1 and h2 fields 389 -> 294 us).  The FP32 CG matvec, which also holds p, is faster
+//    reading chunks (48^3 elements, lx = 12: 4.6 ms held, 3.7 in chunks at the three waves per
+//    SIMD that it gets; four are asked for, and 159 to 168 registers leave three).
 //  * NB: LDS element buffers, 4 (grad4 / div4: four barriers per field pass) or 2
 //    (grad_lean / div_lean: eight); in FP64 four would halve the workgroups a compute
 //    unit holds.
@@ -1364,10 +1366,11 @@ __device__ __forceinline__ void tile_div(const TL &L, const Mat<LX, T> &Dt, cons
 
 // Where the matrix-core kernels are used, waves per element W and waves per SIMD EU.
 //  * FP64, lx = 12: 12^2 pencils are nine whole tiles of three whole rows, three tiles to a
-//    wave, and a lane's 9 points of G are 108 of its 256 registers.  48^3-type elements at
-//    21 million points, us before -> now: one field Poisson 260 -> 252, Helmholtz 297 ->
-//    272, h1 field 321 -> 299, h1 and h2 fields 544 -> 335; three fields Helmholtz 714 ->
-//    524 (G was read from memory three times, at 6.8 TB/s), h1 and h2 fields 2600 -> 553.
+//    wave, and a lane's 9 points of G are 108 of its 256 registers.  Curved elements, 21
+//    million points, us with the pencil kernels -> with these: one field Poisson 260 -> 252,
+//    Helmholtz 297 -> 272, h1 field 321 -> 299, h1 and h2 fields 544 -> 335; three fields
+//    Helmholtz 714 -> 524 (G was read from memory three times, at 6.8 TB/s), h1 and h2
+//    fields 2600 -> 553.
 //  * FP32, lx = 16, three fields: sixteen whole tiles of four rows; 558 -> 262 us.
 // Elsewhere the pencil kernels are faster: the padding of a tile (lx = 10: 16 pencils by 12
 // rows for 14.3 by 10) costs up to half of the lanes (467 against 690 us for three fields

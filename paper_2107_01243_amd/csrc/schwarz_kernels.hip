@@ -7,8 +7,8 @@
 // solved by fast diagonalisation: with, per direction, the eigenvectors S (row-major
 // [node][mode]) and eigenvalues of the 1-D generalised problem K S = M S Lambda,
 //   z = (St x Ss x Sr) diag(1 / (h1 (lr_i + ls_j + lt_k) + h2)) (St x Ss x Sr)^T r.
-// Two boxes: the element's own lx^3 points (k_fdm), and those points plus one layer
-// of extension points beyond every face (k_fdm_ov, (lx + 2)^3 points: the minimal
+// Two boxes: the element's own lx^3 points (k_fdm<LX, false>), and those points plus one
+// layer of extension points beyond every face (k_fdm<LX, true>, (lx + 2)^3 points: the minimal
 // overlap of one point, the extension layer's right-hand side gathered from the face
 // neighbour; only the element's own points are written back).
 //
@@ -45,7 +45,8 @@ namespace sem {
 // points below and above (lx, lx + 1): the inverse transforms then form the tiles of the
 // own points only.
 //
-// 32^3 elements, lx = 8: element box 99 -> 78 us, box with overlap 234 -> 205 us.  Now
+// 32^3 elements, lx = 8, in a solve: element box 99 us with the multiply-adds on the vector
+// units, 78 in this form; box with overlap 234 and 216.  Now
 // neither a memory nor a matrix bound: the matrix cores are busy 38% of the time, the
 // vector units (the FP64 divisions, addresses, the gathers of the overlap) 35%, LDS 43%.
 template <int LX, bool OV>
@@ -55,7 +56,7 @@ struct FdmShape {
     static constexpr int T = (X + 3) / 4, TL = (LX + 3) / 4;       // tiles of all / own nodes
     // Waves per element W, tiles in flight per wave HG and waves per SIMD the registers
     // leave room for EU, measured per box size X at 9 to 17 million points (whole
-    // application without the coarse steps, before -> now): X = 4 355 -> 300 us, 5 249 ->
+    // application without the coarse steps, multiply-adds on the vector units -> here): X = 4 355 -> 300 us, 5 249 ->
     // 238, 6 262 -> 266 (EU 4: 276), 7 158 -> 160, 8 271 -> 249, 9 316 -> 306, 10 313 ->
     // 319 (W 2, HG 4: 330), 12 256 -> 230, 16 285 -> 260; with overlap X = 6 517 -> 483,
     // 7 380 -> 338, 8 347 -> 340, 9 298 -> 240, 10 416 -> 386 (W 1: 408, W 4: 397), 11

@@ -209,8 +209,8 @@ struct sem_gs_s {
     int32_t *d_blk_idx = nullptr;
     uint8_t *d_owner = nullptr;
     uint32_t *d_ent_word = nullptr;  // entry-parallel list, one packed word per entry
-    // per-point map of the kernels that gather (see CgUpdateArgs), built by the first solve
-    // that uses it; stays nullptr where it cannot be built
+    // per-point map of the kernels that gather (see CgUpdateArgs), built by the first solve,
+    // assembly or application that uses it; stays nullptr where it cannot be built
     std::mutex pmap_mu;
     bool pmap_tried = false;
     std::atomic<int32_t *> d_pmap{nullptr};

@@ -133,8 +133,10 @@ struct RelState {
     int last_iter; // iteration count at the latest replacement
 };
 
-// r32 = (float) r64, x32 = 0 (optionally p32 = 0), partials of (r32, dinv r32),
-// (r32, r32) and (r64, r64) over owned points, for fields not done.
+// r = b - w (w = A x in FP64, summed over the copies here where pmap is set, assembled before
+// where it is not; r = 0 on Dirichlet points, and r = b for x = 0): r32 = (float) r, x32 = 0
+// (optionally p32 = 0), partials of (r32, (float) dinv r32), (r32, r32) and (r, r) over owned
+// points, for fields not done.
 struct RelRestartArgs {
     const double *b;
     const double *w;   // A x, or nullptr for x = 0

@@ -1346,8 +1346,9 @@ __global__ __launch_bounds__(VT) void k_cg_update_gather(CgUpdateArgs<T> A, unsi
 // order) and writes the masked sum, one pass where copy, gather-scatter and mask take three.
 // A lane's points are VT apart and all fields share a point's index and flag; every load
 // of one level is requested before the next.  4^3 to 8^3 elements: 18 us for the three calls,
-// 8.6 for this one; 8^3 points in 32768 elements: 135 -> 122 us, 12^3 in 8000: 84 -> 78, with
-// three fields 304 -> 215.  The rate is that of the copies' separate cache requests (138
+// 8.6 for this one; 8^3 points in 32768 elements: 131 -> 121 us whether the operand is in the
+// cache or not, 12^3 in 8000: 83 -> 82 from memory and 76 -> 79 from the cache, with three fields
+// 303 -> 215.  The rate is that of the copies' separate cache requests (138
 // points per ns at lx = 8, 177 at 12), not of memory: 1, 2 and 4 points a lane differ by 4%.
 constexpr int ASM_V = 2;
 template <typename T, int NF>
@@ -1603,9 +1604,9 @@ __global__ __launch_bounds__(RT) void k_cg_finish(CgFinishArgs A)
 // rounds of VT points and all fields, which share the point's index, dinv and owner, so that
 // few partial sums are left.  Three fields of 13.8M points at lx = 12: 281 us (4.1 TB/s of
 // what it must move: the chain index -> entries -> copies bounds it, as in the gathering
-// update), against 143 for the gather-scatter, 209 for the residual and 231 for the restart
-// as passes of their own.  Chunks of 512 to 2048 points, runs of 4 or 16, the indices of all
-// rounds loaded first: 275 to 306 us.
+// update), against 143 + 209 + 231 for the three passes that it stands for (gather-scatter;
+// residual, stored in FP64; restart from it).  Chunks of 512 to 2048 points, runs of 4 or 16,
+// the indices of all rounds loaded first: 275 to 306 us.
 constexpr int REL_R = 8, REL_RUN = 4;
 template <int NF, bool GA>
 __global__ __launch_bounds__(VT) void k_rel_restart(RelRestartArgs A, unsigned nblk)
