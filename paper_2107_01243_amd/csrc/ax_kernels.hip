@@ -328,8 +328,8 @@ __device__ __forceinline__ void load_row(T (&r)[LX], const T *__restrict__ p, bo
 // rows of lx^2 values that are not whole lines: a line read non-temporally is dropped after
 // its first use, and the part of it that another of the wave's loads wants is fetched again.
 // reads_plainly has the rule by size.  (STREAM is not for the CG matvecs, which pass their
-// vectors to the next kernels through the cache: FP32 of one field at lx = 9 gains, 135 -> 123 us an iteration, but at lx = 12 196 -> 217, of three at lx = 9
-// 282 -> 304, FP64 at lx = 5 231 -> 247.)
+// vectors to the next kernels through the cache: FP32 of one field at lx = 9 gains, 135 -> 123 us
+// an iteration, but at lx = 12 196 -> 217, of three at lx = 9 282 -> 304, FP64 at lx = 5 231 -> 247.)
 template <int LX, typename T, int NF>
 constexpr bool STREAM = sizeof(T) == 4 ? (LX & (LX - 1)) == 0 && !(LX == 16 && NF == 3)
                                        : LX != 5 && !(NF == 1 && (LX == 10 || LX == 11 || LX == 13));
@@ -1774,7 +1774,8 @@ const T *dense_d(const void *deo)
 // field (with three fields read in chunks, G is read plainly in any case).
 template <typename T, int NF>
 struct PlainG {
-    static constexpr bool LEAN = sem::Shape<SEM_LX, T>::LEAN, CHUNKS3 = NF == 3 && !sem::LeanCfg<SEM_LX, T, NF, false>::HOLD;
+    static constexpr bool LEAN = sem::Shape<SEM_LX, T>::LEAN;
+    static constexpr bool CHUNKS3 = NF == 3 && !sem::LeanCfg<SEM_LX, T, NF, false>::HOLD;
     static constexpr bool POSSIBLE = !LEAN || (!sem::STREAM<SEM_LX, T, NF> && !CHUNKS3);
 };
 
